@@ -11,6 +11,7 @@
 // the CO layer or the grid) changes no channel, so a wave skips the channel
 // loop of a sample where none of its rays has opacity there (a ballot over
 // the lanes marching).  The cube is the same either way.
+#include <algorithm>
 #include <type_traits>
 
 #include "rt_kernels.h"
@@ -149,6 +150,160 @@ __global__ __launch_bounds__(256) void march_fwd_group(Geometry g, Shade s, Chan
 #pragma unroll
     for (int c = 0; c < CB; ++c)
         if (cl + c < ch.n) cube[(size_t)(cl + c) * ch_stride + pix] = I[c];
+}
+
+// Smallest and largest x of the wave, as scalars (every lane active).
+__device__ __forceinline__ int wave_min(int x) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) x = min(x, __shfl_xor(x, d));
+    return __builtin_amdgcn_readfirstlane(x);
+}
+__device__ __forceinline__ int wave_max(int x) { return -wave_min(-x); }
+
+// Windowed march: four lanes share a pixel, lane h holding channels c0 + 4 i +
+// h (i < CB) in registers, so that a run of neighbouring channels is a run of
+// i in all four lanes.  Lane h shades every fourth sample (k + h) and the quad
+// passes the shadings around by DPP, as in march_fwd_group; then only the
+// units of channels near some ray's line at that sample are marched (rt_
+// kernels.h, "line windows"): the wave's 16 pixels move at nearly the same
+// speed, so most units are left by the whole wave.  Each lane keeps its
+// channels' velocities in registers: read from the arguments inside the
+// branches they cost a scalar load's latency per unit, and stepping d from unit
+// to unit rounds further from the reverse march's d than a fit should see.
+// UNIFORM: evenly spaced channels, whose unit masks need no comparisons.
+//
+// Bound: VALU issue (98 % of the cycles at 4 cycles an instruction: the shading
+// of a sample about 640 cycles a wave, a faint channel slot 23, a thin one 32).
+// Measured, disks of the full-size family, us: 512^2 x 64 x 512 1417 -> 616,
+// 222^2 x 115 x 256 592 -> 130, 256^2 x 48 x 256 390 -> 96 (march_fwd_group
+// and march_fwd -> march_win); without the faint loop 512^2 took 760, with
+// units of two channels a lane 761 against 703, with 4 or 16 times narrower
+// windows (2^-48, 2^-32) 4 and 7 % less.
+//
+// A workgroup's waves are nsplit consecutive parts of the rays of each 4 x 4
+// pixel tile; the parts' (I, Tr) meet in LDS (parts) and the first wave of a
+// tile composes them front to back.  A small image needs the parts to fill
+// the chip; a part per wave, not per lane, keeps a wave's lines together.
+template <int CB, bool NEURAL, bool UNIFORM>
+__global__ __launch_bounds__(512) void march_win(Geometry g, Shade s, Channels ch, Windows win, int lsplit,
+                                                 float *__restrict__ cube, int ch_stride) {
+    __shared__ float4 ztab[kZTableNodes - 1];
+    extern __shared__ float parts[];
+    stage_ztab(s, ztab);
+    constexpr int G = kLanesPerPixel, U = unit_slots(CB), NU = CB / U;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nsplit = 1 << lsplit, nsub = (int)(blockDim.x >> 6) >> lsplit;   // 4 x 4 tiles of this workgroup
+    const int split = wave & (nsplit - 1), sub = wave >> lsplit;
+    const int lane = threadIdx.x & 63, h = lane & 3, slot = lane >> 2;
+    const int tw = nsub >= 2 ? 8 : 4, th = nsub >= 4 ? 8 : 4;
+    const int tiles_x = (g.nx + tw - 1) / tw;
+    const int p = (int)(blockIdx.x % tiles_x) * tw + (sub & 1) * 4 + (slot & 3);
+    const int q = (int)(blockIdx.x / tiles_x) * th + (sub >> 1) * 4 + (slot >> 2);
+    const int c0 = blockIdx.y * CB * G, u0 = blockIdx.y * NU;
+    const bool inside = p < g.nx && q < g.ny;
+    const RaySetup r = ray_setup(g, inside ? p : 0, inside ? q : 0);
+    const bool live = inside && r.live;
+    float I[CB], Tr[CB], vc[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        I[c] = 0.0f;
+        Tr[c] = 1.0f;
+        vc[c] = ch.v[c0 + c * G + h];
+    }
+    // every lane of a wave with a live ray takes part (the lane exchanges need
+    // them all); the others' samples are off
+    if (__ballot(live) != 0) {
+        const float half = 0.5f * (float)g.nsamp;
+        const float v0 = ch.v[c0];
+        const int pix = inside ? q * g.nx + p : 0;
+        // the samples that some ray of the wave can have below the top taper
+        const int2 own_range = live ? taper_range(g, s, r) : make_int2(g.nsamp, -1);
+        const int kf = wave_min(own_range.x), kn = max(wave_max(own_range.y) + 1 - kf, 0);
+        const int len = (((kn + nsplit - 1) >> lsplit) + G - 1) / G * G;
+        const int k1 = kf + min(kn, (split + 1) * len);
+        for (int k = kf + split * len; k < k1; k += G) {
+            const int kk = min(k + h, k1 - 1);
+            const float t = ((float)kk + 0.5f - half) * r.ds;
+            const SampleQ own = shade_sample<NEURAL>(s, ztab, r.px, fmaf(t, r.wy, r.pmy), fmaf(t, r.wz, r.pmz), r.ds,
+                                                     o_index(s, kk, pix));
+            const float own_lk = flog2(own.K);
+            const unsigned mask =
+                or_over_pixels(unit_mask<NU, G * U, UNIFORM>(own, own_lk, live && k + h < k1, v0, win, u0));
+            const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < kFaintLog2K));
+            const unsigned long long thick = __builtin_amdgcn_ballot_w64(!(own_lk < kThinLog2K));
+            auto step = [&](auto jc) {
+                constexpr int J = decltype(jc)::value;
+                constexpr unsigned long long mine = 0x1111111111111111ull << J;
+                const unsigned m = (unsigned)__builtin_amdgcn_readlane((int)mask, J);
+                if (m == 0) return;
+                const float S = group_lane<G, J>(own.S), lK = group_lane<G, J>(own_lk);
+                const float a = group_lane<G, J>(own.a), b = group_lane<G, J>(own.b);
+                march_units<CB>(I, Tr, S, lK, m, (bright & mine) != 0, (thick & mine) != 0,
+                                [&](int c) { return fmaf(-vc[c], b, a); });
+            };
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
+        }
+    }
+    if (nsplit > 1) {
+        float *mine = parts + (size_t)(sub * (nsplit - 1)) * (2 * CB * 64) + lane;
+        if (split > 0) {
+            float *o = mine + (size_t)(split - 1) * (2 * CB * 64);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                o[c * 64] = I[c];
+                o[(CB + c) * 64] = Tr[c];
+            }
+        }
+        __syncthreads();
+        if (split > 0) return;
+        for (int j = 0; j < nsplit - 1; ++j) {
+            const float *o = mine + (size_t)j * (2 * CB * 64);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                I[c] = fmaf(Tr[c], o[c * 64], I[c]);
+                Tr[c] *= o[(CB + c) * 64];
+            }
+        }
+    }
+    if (!inside) return;
+    const size_t pix = (size_t)q * g.nx + p;
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+        if (c0 + c * G + h < ch.n) cube[(size_t)(c0 + c * G + h) * ch_stride + pix] = I[c];
+}
+
+template <int CB>
+static hipError_t launch_win_t(const Geometry &g, const Shade &s, const Channels &ch, const Windows &win, float *cube,
+                               bool uniform, int lsplit, hipStream_t st) {
+    const int waves = std::max(4, 1 << lsplit), nsub = waves >> lsplit;
+    const int tw = nsub >= 2 ? 8 : 4, th = nsub >= 4 ? 8 : 4;
+    dim3 grid(((g.nx + tw - 1) / tw) * ((g.ny + th - 1) / th), (ch.n + CB * kLanesPerPixel - 1) / (CB * kLanesPerPixel));
+    const size_t lds = (size_t)nsub * ((1 << lsplit) - 1) * 2 * CB * 64 * sizeof(float);
+    const int cs = g.nx * g.ny;
+    if (s.mlp_o) {
+        if (uniform) hipLaunchKernelGGL((march_win<CB, true, true>), grid, dim3(64 * waves), lds, st, g, s, ch, win, lsplit, cube, cs);
+        else hipLaunchKernelGGL((march_win<CB, true, false>), grid, dim3(64 * waves), lds, st, g, s, ch, win, lsplit, cube, cs);
+    } else {
+        if (uniform) hipLaunchKernelGGL((march_win<CB, false, true>), grid, dim3(64 * waves), lds, st, g, s, ch, win, lsplit, cube, cs);
+        else hipLaunchKernelGGL((march_win<CB, false, false>), grid, dim3(64 * waves), lds, st, g, s, ch, win, lsplit, cube, cs);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_forward_win(const Geometry &g, const Shade &s, const Channels &ch, const Windows &win, float *cube,
+                              int cb, bool uniform, int lsplit, hipStream_t st) {
+    switch (cb) {
+    case 4: return launch_win_t<4>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 8: return launch_win_t<8>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 12: return launch_win_t<12>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 16: return launch_win_t<16>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 24: return launch_win_t<24>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 32: return launch_win_t<32>(g, s, ch, win, cube, uniform, lsplit, st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <int CB, bool THIN, int NSPLIT>

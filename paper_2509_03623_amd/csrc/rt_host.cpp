@@ -390,6 +390,49 @@ bool group_shift(const double *v, int n, int G, int cb, double *shift) {
     return true;
 }
 
+bool uniform_spacing(const double *v, int n, double *dv) {
+    *dv = n > 1 ? (v[n - 1] - v[0]) / (n - 1) : 0.0;
+    double span = 0.0;
+    for (int c = 0; c < n; ++c) span = std::max(span, std::fabs(v[c] - v[0]));
+    const double tol = 1e-9 * std::max(span, 1e-12);
+    for (int c = 0; c < n; ++c)
+        if (std::fabs(v[c] - v[0] - c * *dv) > tol) return false;
+    return true;
+}
+
+void unit_windows(const Channels &ch, int cb, double dv, Windows *w) {
+    const int per = unit_slots(cb) * kLanesPerPixel;
+    w->inv_unit = dv != 0.0 ? (float)(1.0 / (per * dv)) : 0.0f;
+    for (int u = 0; u < kMaxUnits; ++u) {
+        w->lo[u] = HUGE_VALF;
+        w->hi[u] = -HUGE_VALF;
+        for (int c = u * per; c < std::min((u + 1) * per, (int)ch.n); ++c) {
+            w->lo[u] = std::min(w->lo[u], ch.v[c]);
+            w->hi[u] = std::max(w->hi[u], ch.v[c]);
+        }
+    }
+}
+
+// Launch shape of the windowed march: all channels (up to 128) in one block of
+// four lanes, so that no sample is shaded twice, and the rays in as many parts
+// (of at least 32 samples) as give 8192 waves, about 1.3 times what the chip
+// holds at six per SIMD.  Measured at 222^2 x 60 x 256, 256^2 x 48 x 256 and
+// 180 x 190 x 64 x 300 (us): 4096 waves asked for 121, 117, 82; 8192 85, 97,
+// 69; 16384 85, 105, 70.  The parts meet in LDS, 512 cb bytes a part and
+// tile: past 32 KB a workgroup they cost more waves in flight than they add
+// (222^2 x 115 x 256, cb 32: two parts 127 us, four 160).
+static void window_shape(int nch, long npix, int nsamp, int *cb, int *lsplit) {
+    static const int cands[] = {4, 8, 12, 16, 24, 32};
+    const int nblk = (nch + 127) / 128;
+    *cb = 32;
+    for (int c : cands)
+        if (c * kLanesPerPixel * nblk >= nch) { *cb = c; break; }
+    const long waves = (npix + 15) / 16 * nblk;
+    const int most = *cb <= 8 ? 3 : (*cb <= 16 ? 2 : 1);
+    *lsplit = 0;
+    while (*lsplit < most && (waves << *lsplit) < 8192 && nsamp >= (32 << *lsplit)) ++*lsplit;
+}
+
 // lanes per pixel of the forward march of 64-channel blocks.  Measured on
 // MI355X (512^2 x 64 x 512, disks 2000-2005): 2 lanes (104 VGPRs, 4 waves
 // per SIMD) 3-7 % and 4 lanes (67 VGPRs, 7 waves) 16-18 % faster than one.
@@ -401,6 +444,8 @@ rt_status march_cube(const rt_problem *p, const Geometry &g, const Shade &s, flo
     forward_shape(std::min(p->spec.nch, kLaunchChannels), (long)p->cam.nx * p->cam.ny, p->nsamp, &cb, &nsplit);
     if (g_opt_split) nsplit = (int)g_opt_split;
     const size_t plane = (size_t)p->cam.nx * p->cam.ny;
+    // a caller who sets a launch option gets the march that it names
+    const bool windows = !g_opt_cb && !g_opt_split && !g_opt_group && g_opt_thin;
     for (int c0 = 0; c0 < p->spec.nch; c0 += kLaunchChannels) {
         Channels ch;
         std::memset(&ch, 0, sizeof ch);
@@ -408,6 +453,17 @@ rt_status march_cube(const rt_problem *p, const Geometry &g, const Shade &s, flo
         for (int c = 0; c < ch.n; ++c) ch.v[c] = (float)p->spec.v_kms[c0 + c];
         double shift = 0.0;
         hipError_t e;
+        if (windows) {
+            int wcb, lsplit;
+            window_shape(ch.n, (long)plane, p->nsamp, &wcb, &lsplit);
+            // (channels at one velocity have no spacing to count units by)
+            const bool uniform = uniform_spacing(p->spec.v_kms + c0, ch.n, &shift) && shift != 0.0;
+            Windows win;
+            unit_windows(ch, wcb, uniform ? shift : 0.0, &win);
+            e = launch_forward_win(g, s, ch, win, cube + (size_t)c0 * plane, wcb, uniform, lsplit, stream);
+            if (e != hipSuccess) return fail_hip(e, "forward launch");
+            continue;
+        }
         const int G = forward_group();
         if (cb == 64 && nsplit == 1 && G > 1 && group_shift(p->spec.v_kms + c0, ch.n, G, 64 / G, &shift))
             e = launch_forward_group(g, s, ch, cube + (size_t)c0 * plane, thin_series(), G, (float)shift, stream);

@@ -28,6 +28,11 @@ void adjoint_shape(int nch, long npix, bool cube, int *cb, int *lanes, int *kseg
 // velocities v[n] uniformly spaced in groups of cb within blocks of G cb
 // channels (lane m's = lane 0's + m shift)
 bool group_shift(const double *v, int n, int G, int cb, double *shift);
+// velocities v[n] uniformly spaced by *dv (to 1e-9 of their span)
+bool uniform_spacing(const double *v, int n, double *dv);
+// the velocity range of each unit of the channels of 4 lanes of cb (dv: their
+// spacing if uniform)
+void unit_windows(const Channels &ch, int cb, double dv, Windows *w);
 bool thin_series();
 int ckpt_segment_option();
 int ray_split_option();

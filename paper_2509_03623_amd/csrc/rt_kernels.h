@@ -70,7 +70,8 @@ __device__ __forceinline__ float flog2(float x) { return __builtin_amdgcn_logf(x
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ float clampf(float x, float lo, float hi) { return fminf(fmaxf(x, lo), hi); }
+// one v_med3; a NaN gives lo, as fmin(fmax(x, lo), hi) does
+__device__ __forceinline__ float clampf(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
 
 // e^x - 1 for 0 <= x: Taylor series through x^9/9! below 1/2 (truncation
 // < 1e-8 relative), e^x - 1 above (relative error ~ 1 ulp / (1 - e^-x)).
@@ -98,6 +99,7 @@ __device__ __forceinline__ float expm1_pos(float x) {
 // at the threshold and better above.  The series needs one exp2 fewer per
 // channel than the direct form.
 constexpr float kThinK = 0.04508422002825536f;   // y = 1/32
+constexpr float kThinLog2K = -4.471233627f;      // its log2
 __device__ __forceinline__ float om_series3(float x) {
     constexpr float c1 = 0.6931471805599453f;      //  ln2
     constexpr float c2 = -0.2402265069591007f;     // -ln2^2/2
@@ -191,6 +193,27 @@ __device__ __forceinline__ RaySetup ray_setup(const Geometry &g, int p, int q) {
     return r;
 }
 
+// The samples of a live ray that can lie below the grid's top taper, |z| <
+// zeta rho with zeta one cell above the top z/r row: the others have no
+// opacity (locate's taper is 0).  Below tan i = 1/zeta they are one run, since
+// zeta^2 rho^2 - z^2 is then concave along the ray; the bound is taken 5e-4
+// wider in zeta (float's rounding of the roots is far inside that) and a
+// sample wider at each end.  In the test disks it leaves out about a third of
+// the chord through the bounding cylinder.  (first, last), first > last: none.
+__device__ __forceinline__ int2 taper_range(const Geometry &g, const Shade &s, const RaySetup &r) {
+    const float zeta = s.fnz / s.inv_dzr * 1.0005f, z2 = zeta * zeta;
+    const float A = z2 * r.wy * r.wy - r.wz * r.wz;
+    if (!(A < -1e-3f)) return make_int2(0, g.nsamp - 1);
+    const float B = z2 * r.pmy * r.wy - r.pmz * r.wz, C = fmaf(z2, fmaf(r.px, r.px, r.pmy * r.pmy), -r.pmz * r.pmz);
+    const float disc = fmaf(B, B, -A * C);
+    if (disc <= 0.0f) return make_int2(g.nsamp, -1);
+    const float mid = -B / A, ext = -sqrtf(disc) / A, c = 0.5f * (float)g.nsamp - 0.5f;
+    const float n = (float)g.nsamp;
+    const float lo = fminf(fmaxf((mid - ext) / r.ds + c - 1.0f, 0.0f), n);
+    const float hi = fmaxf(fminf((mid + ext) / r.ds + c + 2.0f, n - 1.0f), -1.0f);
+    return make_int2((int)lo, (int)hi);
+}
+
 // Where a sample falls on the grid.
 struct Locus {
     float rho, inv_rho, az;  // cylindrical radius, 1/rho, |z| [au]
@@ -204,10 +227,10 @@ __device__ __forceinline__ Locus locate(const Shade &s, float px, float py, floa
     Locus L;
     const float rho2 = px * px + py * py;
     const bool on = rho2 > 0.0f;
-    L.rho = fsqrt(rho2);
-    L.inv_rho = on ? frcp(L.rho) : 0.0f;
+    L.inv_rho = on ? frsq(rho2) : 0.0f;
+    L.rho = rho2 * L.inv_rho;
     L.az = fabsf(pz);
-    float u = (flog2(L.rho) - s.log2_rmin) * s.u_scale;
+    float u = fmaf(0.5f, flog2(rho2), -s.log2_rmin) * s.u_scale;
     float v = L.az * L.inv_rho * s.inv_dzr;
     u = on ? u : -2.0f;
     v = on ? v : 0.0f;
@@ -235,14 +258,28 @@ struct Corners {
     float l00, l01, l10, l11, t00, t01, t10, t11, v00, v01, v10, v11, zl0, zl1, zu0, zu1;
 };
 
+// two consecutive floats at a byte offset from a uniform base (any 4-byte
+// alignment; one 8-byte load, the offset in one register)
+__device__ __forceinline__ float2 load_pair(const float *base, unsigned off) {
+    typedef float pair __attribute__((ext_vector_type(2), aligned(4)));
+    const pair v = *(const pair *)((const char *)base + off);
+    return make_float2(v.x, v.y);
+}
+
 __device__ __forceinline__ Corners load_corners(const Shade &s, const Locus &L) {
-    const int n00 = L.i0 * s.nz + L.j0;
-    const int n10 = n00 + s.nz;
+    // neighbouring nodes in pairs, at 32-bit byte offsets (at most 2^30 nodes)
+    const unsigned n00 = 4u * ((unsigned)L.i0 * (unsigned)s.nz + (unsigned)L.j0), n10 = n00 + 4u * (unsigned)s.nz;
+    const unsigned i0 = 4u * (unsigned)L.i0;
     Corners c;
-    c.l00 = s.ln_n[n00]; c.l01 = s.ln_n[n00 + 1]; c.l10 = s.ln_n[n10]; c.l11 = s.ln_n[n10 + 1];
-    c.t00 = s.temp[n00]; c.t01 = s.temp[n00 + 1]; c.t10 = s.temp[n10]; c.t11 = s.temp[n10 + 1];
-    c.v00 = s.vphi[n00]; c.v01 = s.vphi[n00 + 1]; c.v10 = s.vphi[n10]; c.v11 = s.vphi[n10 + 1];
-    c.zl0 = s.zlo[L.i0]; c.zl1 = s.zlo[L.i0 + 1]; c.zu0 = s.zup[L.i0]; c.zu1 = s.zup[L.i0 + 1];
+    float2 p;
+    p = load_pair(s.ln_n, n00); c.l00 = p.x; c.l01 = p.y;
+    p = load_pair(s.ln_n, n10); c.l10 = p.x; c.l11 = p.y;
+    p = load_pair(s.temp, n00); c.t00 = p.x; c.t01 = p.y;
+    p = load_pair(s.temp, n10); c.t10 = p.x; c.t11 = p.y;
+    p = load_pair(s.vphi, n00); c.v00 = p.x; c.v01 = p.y;
+    p = load_pair(s.vphi, n10); c.v10 = p.x; c.v11 = p.y;
+    p = load_pair(s.zlo, i0); c.zl0 = p.x; c.zl1 = p.y;
+    p = load_pair(s.zup, i0); c.zu0 = p.x; c.zu1 = p.y;
     return c;
 }
 
@@ -319,8 +356,9 @@ __device__ __forceinline__ SampleQ physics(const Shade &s, const float4 *tab, co
     const float iw = s.inv_w * L.inv_rho;
     const float ea = fexp2((L.az - F.zup) * iw);
     const float eb = fexp2((F.zlo - L.az) * iw);
-    const float ra = frcp(1.0f + ea), rb = frcp(1.0f + eb);
-    const float mask = ra * rb;
+    float ra = 0.0f, rb = 0.0f;
+    if (TAPE) { ra = frcp(1.0f + ea); rb = frcp(1.0f + eb); }
+    const float mask = TAPE ? ra * rb : frcp((1.0f + ea) * (1.0f + eb));
     // LTE populations and source function
     const float rT = frcp(F.T);
     float dZ = 0.0f;
@@ -371,6 +409,127 @@ __device__ __forceinline__ void stage_ztab(const Shade &s, float4 *lds_tab) {
 
 // 1 - 2^-x given att = 2^-x, per channel: the series below kThinK
 __device__ __forceinline__ float om_select(float x, float att) { return x < kThinK ? om_series3(x) : 1.0f - att; }
+
+// ---------------------------------------------------------------- line windows
+// A channel far from the line at a sample gets nothing from it: with d in
+// line widths (log2 units, profile 2^-d^2) the windowed marches leave out the
+// channels with d^2 > 64 + max(log2 K, 0).  There the sample's depth is below
+// 2^-64 of its line-centre depth, and below 2^-64 outright on a sample thicker
+// than 1: att = 2^-x rounds to 1 in float from x < 2^-25 on, and the emission
+// left out is 2^-40 of a float's rounding of the line centre's (the cut goes
+// with the line centre, so a scene scaled to any depth keeps it).  Nor do the
+// channels with log2 K - d^2 < -127 count, whose depth is 0 in float.  At the
+// 0.13 km/s widths and 0.1 km/s channels of the test disks about 18 of 64
+// channels are left.
+//
+// Channels come in units of 4 or 8 neighbours; a wave takes or leaves a unit as
+// a whole (scalar branches, every register index static).  Each lane forms the
+// bit mask of the units its own sample's line reaches, the masks of the wave's
+// pixels are or-ed by lane exchanges, and a scalar bit test decides.
+constexpr int kLanesPerPixel = 4;             // lanes sharing a pixel in the windowed marches
+// channels per lane in a unit: one, or two where a block's bits would not fit
+constexpr __host__ __device__ int unit_slots(int cb) { return cb > 24 ? 2 : 1; }
+constexpr int kMaxUnits = kLaunchChannels / kLanesPerPixel + 32;
+struct Windows {
+    float lo[kMaxUnits], hi[kMaxUnits];       // lowest and highest velocity of each unit (+inf, -inf: padding)
+    float inv_unit;                           // 1 / (velocity span of a unit) of uniformly spaced channels
+};
+
+// Samples so faint that float arithmetic tells no difference: below 2^-26 the
+// series of 1 - 2^-x is x ln 2 and Tr (1 - (1 - 2^-x)) is Tr, to the bit.  Most
+// samples of a disk with any opacity are (the tails of its layer and of its
+// density), so they have a loop of their own, without Tr and the series.
+constexpr float kFaintLog2K = -26.0f;
+
+// Bits of the units (u0 ... u0 + NU - 1) that the line of sample q reaches; 0
+// without opacity or when `on` is false.  v0: velocity of
+// the block's first channel (UNIFORM).  NaN in q sets every unit: what a NaN
+// sample touches is what it touched without windows.
+template <int NU, int PER, bool UNIFORM>
+__device__ __forceinline__ unsigned unit_mask(const SampleQ &q, float lK, bool on, float v0, const Windows &win,
+                                              int u0) {
+    const float ib = frcp(q.b);
+    // at least sqrt(min(64 + max(lK, 0), 127 + lK)): two tangents
+    const float R = fminf(fmaf(fmaxf(lK, 0.0f), 0.0625f, 8.0f), fmaf(lK, 0.08839f, 14.0547f));
+    const float v = q.a * ib, hw = fmaf(lK, 0.0f, R) * ib;   // 0 lK: NaN for NaN and infinite K
+    unsigned m = 0;
+    if constexpr (UNIFORM) {
+        // in units of PER channels from the block's first: unit i spans
+        // [i, i + 1 - 1/PER]; [l, e) are the units reached
+        const float y = fmaf(v, win.inv_unit, -v0 * win.inv_unit), hy = fabsf(hw * win.inv_unit);
+        const int l = (int)clampf(y - hy + 1.0f / PER, 0.0f, (float)NU);
+        const int e = (int)clampf(y + hy + 1.0f, 0.0f, (float)NU);
+        m = fabsf(y) + hy < __builtin_huge_valf() ? (1u << e) - (1u << l) : (1u << NU) - 1u;
+    } else {
+#pragma unroll
+        for (int i = 0; i < NU; ++i)
+            m |= !(v - hw > win.hi[u0 + i]) && !(v + hw < win.lo[u0 + i]) ? 1u << i : 0u;
+    }
+    return on && !(lK <= -127.0f) ? m : 0u;
+}
+
+// Or of x over the lanes with the same place in their quad (every lane active).
+__device__ __forceinline__ unsigned or_over_pixels(unsigned x) {
+    x |= (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x124, 0xF, 0xF, true);   // row_ror:4
+    x |= (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xF, 0xF, true);   // row_ror:8
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = r[0] | r[1];
+    const auto t = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return t[0] | t[1];
+}
+
+// One sample of the windowed channel loop over CB channels per lane held in
+// registers, on the units of the wave-uniform mask m (march_lk's arithmetic;
+// on a faint sample I += Tr x ln2 S).  off(c) is d of channel c; bright, thick:
+// some lane's sample is not faint, has K >= kThinK (wave-uniform).
+template <int CB, class Off>
+__device__ __forceinline__ void march_units(float (&I)[CB], float (&Tr)[CB], float S, float lK, unsigned m, bool bright, bool thick,
+                                            Off off) {
+    constexpr int U = unit_slots(CB);
+    if (!bright) {
+        const float sl = S * kLn2;
+#pragma unroll
+        for (int i = 0; i < CB / U; ++i) {
+            if (!(m & (1u << i))) continue;
+#pragma unroll
+            for (int c = i * U; c < i * U + U; ++c) {
+                const float d = off(c);
+                const float x = fexp2(fmaf(-d, d, lK));
+                I[c] = fmaf(Tr[c] * x, sl, I[c]);
+            }
+        }
+        return;
+    }
+    if (!thick) {
+#pragma unroll
+        for (int i = 0; i < CB / U; ++i) {
+            if (!(m & (1u << i))) continue;
+#pragma unroll
+            for (int c = i * U; c < i * U + U; ++c) {
+                const float d = off(c);
+                const float x = fexp2(fmaf(-d, d, lK));
+                const float t = Tr[c] * om_series3(x);
+                I[c] = fmaf(t, S, I[c]);
+                Tr[c] -= t;
+            }
+        }
+        return;
+    }
+    const bool thin = lK < kThinLog2K;
+#pragma unroll
+    for (int i = 0; i < CB / U; ++i) {
+        if (!(m & (1u << i))) continue;
+#pragma unroll
+        for (int c = i * U; c < i * U + U; ++c) {
+            const float d = off(c);
+            const float x = fexp2(fmaf(-d, d, lK));
+            const float att = fexp2(-x);
+            const float t = Tr[c] * (thin ? om_series3(x) : 1.0f - att);
+            I[c] = fmaf(t, S, I[c]);
+            Tr[c] = thin ? Tr[c] - t : Tr[c] * att;
+        }
+    }
+}
 
 // One sample of the forward channel loop over CB channels held in registers:
 // d = a - v_c b, x = K 2^-d^2 = 2^(lK - d^2) with lK = log2 K (K = 0 gives
