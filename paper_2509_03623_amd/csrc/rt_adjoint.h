@@ -29,6 +29,11 @@ hipError_t launch_adj_tape(const Geometry &g, const Shade &s, float4 *tape, floa
 hipError_t launch_adj_march(int cb, int kseg, int lanes, int nsamp, int npix, int plane, const Channels &ch,
                             float shift, const float4 *tape, const int2 *span, const float *dl, const float *target,
                             float *ckpt, float4 *cot, float *cube_out, hipStream_t st);
+// reverse march over line windows (kseg 0): four lanes per pixel of cb = 4, 8,
+// 12 or 16 channels, the band's image nx x ny
+hipError_t launch_adj_march_win(int cb, int nsamp, int nx, int ny, int plane, const Channels &ch, const Windows &win,
+                                bool uniform, const float4 *tape, const int2 *span, const float *dl,
+                                const float *target, float4 *cot, float *cube_out, hipStream_t st);
 // chain passes; both read the cotangents of the samples in each ray's span
 hipError_t launch_adj_chain(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, const float4 *cot,
                             int nblk, const GradAcc &go, float4 *dO, hipStream_t st);

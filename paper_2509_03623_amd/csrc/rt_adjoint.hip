@@ -15,7 +15,8 @@
 //   giving dI/dS_k = Tr_k (1 - a_k) and dI/ddtau_k = Tr_{k+1} (S_k - J_k)
 //   without the cancellation of I minus a prefix sum.  Channel sums of the
 //   per-sample cotangents (S, ln K, a, b) are written per channel block.
-// Pass B without checkpoints (adj_march_tau<CB, G, CUBE>, the default; G
+// Pass B over line windows (adj_march_win, rt_adjoint_win.hip, the default)
+//   and pass B without checkpoints (adj_march_tau<CB, G, CUBE>, by option; G
 //   lanes per pixel): the
 //   optical depth is additive, so the transmission in front of sample k is
 //   2^-(tau_tot - tau_suf(k)) with tau_suf the depth behind it.  A first

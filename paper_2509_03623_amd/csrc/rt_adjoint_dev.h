@@ -25,6 +25,11 @@ __device__ __forceinline__ void tape_pixel(const Geometry &g, const Shade &s, co
     if (write_ray) rays[pix] = make_float4(r.px, r.pmy, r.pmz, r.live ? r.ds : 0.0f);
     const float half = 0.5f * (float)g.nsamp;
     int kf = g.nsamp, kl = -1;
+    if (span_only) {   // the samples that can lie below the top taper
+        const int2 in = r.live ? taper_range(g, s, r) : make_int2(g.nsamp, -1);
+        k0 = max(k0, in.x);
+        k1 = min(k1, in.y + 1);
+    }
     for (int k = k0; k < k1; ++k) {
         float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (r.live) {
@@ -33,7 +38,9 @@ __device__ __forceinline__ void tape_pixel(const Geometry &g, const Shade &s, co
                                                            r.ds, o_index(s, k, pix))
                                       : shade_sample<false>(s, ztab, r.px, fmaf(t, r.wy, r.pmy), fmaf(t, r.wz, r.pmz),
                                                             r.ds, 0);
-            o = make_float4(q.S, q.K, q.a, q.b);
+            // (a depth below the smallest normal float is 0 in every channel:
+            // exp2 gives no denormals)
+            o = make_float4(q.S, q.K < 1.17549435e-38f ? 0.0f : q.K, q.a, q.b);
         }
         if (o.y > 0.0f) {
             if (span_only && kl >= 0)   // the zeros since the last sample with K > 0

@@ -10,6 +10,11 @@
 
 namespace rt {
 
+// the windowed march, unless an option names another
+static bool adjoint_windows() {
+    return adjoint_block_option() == 0 && adjoint_lanes_option() == 0 && ckpt_segment_option() == 0;
+}
+
 // Reverse-march shape (measured): of (channels per lane, lanes per pixel) =
 // (32, 2), (24, 2), (16, 2), (32, 1), (24, 1), (25, 2) that still give 2048
 // waves, the one padding the fewest channels, the earlier in that order on a
@@ -19,7 +24,21 @@ namespace rt {
 // write one cotangent slice per 2 CB channels (at 512^2 x 64: 10.9 ms fused
 // with (32, 2) against 11.8 ms with (32, 1)).  The checkpointed march
 // (option) takes 8, 16 or 32 channels per lane and one lane per pixel.
+//
+// Without an adjoint option set, the windowed march instead (lanes = 4): all
+// channels, up to 64, in one block of four lanes, or up to 32 where that gives
+// fewer than 2048 waves.  A second block halves the registers but writes and
+// adds a second slice of cotangents: 512^2 x 64 x 512 4.62 against 4.96 ms,
+// 256^2 x 48 x 256 0.70 against 0.84, but 96^2 x 64 x 256 0.38 against 0.35.
 void adjoint_shape(int nch, long npix, bool cube, int *cb, int *lanes, int *kseg) {
+    if (adjoint_windows()) {
+        int nblk = (nch + 63) / 64;
+        if ((npix + 15) / 16 * nblk < 2048) nblk = (nch + 31) / 32;
+        *cb = std::min(16, ((nch + 4 * nblk - 1) / (4 * nblk) + 3) / 4 * 4);
+        *lanes = kLanesPerPixel;
+        *kseg = 0;
+        return;
+    }
     *cb = nch > 8 ? 16 : 8;
     *lanes = 1;
     static const int cand[][2] = {{32, 2}, {24, 2}, {16, 2}, {32, 1}, {24, 1}, {25, 2}};
@@ -136,6 +155,11 @@ rt_status adjoint_core(const rt_problem *p, const float *dl, const rt_grads *g, 
         ch.n = std::min(kLaunchChannels, p->spec.nch - c0);
         for (int c = 0; c < ch.n; ++c) ch.v[c] = (float)p->spec.v_kms[c0 + c];
         const int nblk = (ch.n + lanes * cb - 1) / (lanes * cb);   // cotangent slices
+        const bool windows = adjoint_windows();
+        double dv = 0.0;
+        const bool uniform = uniform_spacing(p->spec.v_kms + c0, ch.n, &dv) && dv != 0.0;
+        Windows win;
+        unit_windows(ch, cb, uniform ? dv : 0.0, &win);
         // a pair of 32- or 24-channel lanes becomes four lanes of 16 or 12
         // (same slices) when the channels are uniformly spaced in those groups
         int cb_l = cb, lanes_l = lanes;
@@ -171,10 +195,15 @@ rt_status adjoint_core(const rt_problem *p, const float *dl, const rt_grads *g, 
             if ((e = launch_adj_tape(gb, sb, tape, rays, span, kseg == 0, st)) != hipSuccess)
                 return fail_hip(e, "adjoint tape");
             const size_t off = (size_t)c0 * plane + pix0;
-            if ((e = launch_adj_march(cb_l, kseg, lanes_l, ns, bpix, (int)plane, ch, (float)shift, tape, span,
+            if (windows)
+                e = launch_adj_march_win(cb, ns, nx, rows, (int)plane, ch, win, uniform, tape, span,
+                                         dl ? dl + off : nullptr, target ? target + off : nullptr, cot,
+                                         cube_opt ? cube_opt + off : nullptr, st);
+            else
+                e = launch_adj_march(cb_l, kseg, lanes_l, ns, bpix, (int)plane, ch, (float)shift, tape, span,
                                       dl ? dl + off : nullptr, target ? target + off : nullptr, ckpt, cot,
-                                      cube_opt ? cube_opt + off : nullptr, st)) != hipSuccess)
-                return fail_hip(e, "adjoint march");
+                                     cube_opt ? cube_opt + off : nullptr, st);
+            if (e != hipSuccess) return fail_hip(e, "adjoint march");
             float4 *dOc = c0 == 0 ? dO : nullptr;
             e = lds ? launch_adj_chain_lds(gb, sb, rays, span, cot, nblk, go, dOc, st)
                     : launch_adj_chain(gb, sb, rays, span, cot, nblk, go, dOc, st);

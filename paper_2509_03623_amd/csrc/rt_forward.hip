@@ -75,14 +75,6 @@ __global__ __launch_bounds__(256) void march_fwd(Geometry g, Shade s, Channels c
         if (c0 + c < ch.n) cube[(size_t)(c0 + c) * ch_stride + pix] = I[c];
 }
 
-// Lane j of this lane's group of G (2 or 4) adjacent lanes: a DPP quad
-// permutation that gives every lane of the group the value of its member j.
-template <int G, int J>
-__device__ __forceinline__ float group_lane(float x) {
-    constexpr int sel = G == 4 ? J * 0x55 : (J == 0 ? 0xA0 : 0xF5);   // (j,j,j,j) or (j,j,2+j,2+j)
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), sel, 0xF, 0xF, false));
-}
-
 // Grouped-lane march of one 64-channel block: G adjacent lanes share one
 // pixel, lane h holding channels c0 + h CB ... c0 + h CB + CB - 1 (CB =
 // 64 / G) in registers.  Each lane shades one of every G consecutive samples
@@ -152,14 +144,6 @@ __global__ __launch_bounds__(256) void march_fwd_group(Geometry g, Shade s, Chan
         if (cl + c < ch.n) cube[(size_t)(cl + c) * ch_stride + pix] = I[c];
 }
 
-// Smallest and largest x of the wave, as scalars (every lane active).
-__device__ __forceinline__ int wave_min(int x) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x = min(x, __shfl_xor(x, d));
-    return __builtin_amdgcn_readfirstlane(x);
-}
-__device__ __forceinline__ int wave_max(int x) { return -wave_min(-x); }
-
 // Windowed march: four lanes share a pixel, lane h holding channels c0 + 4 i +
 // h (i < CB) in registers, so that a run of neighbouring channels is a run of
 // i in all four lanes.  Lane h shades every fourth sample (k + h) and the quad
@@ -173,12 +157,12 @@ __device__ __forceinline__ int wave_max(int x) { return -wave_min(-x); }
 // UNIFORM: evenly spaced channels, whose unit masks need no comparisons.
 //
 // Bound: VALU issue (98 % of the cycles at 4 cycles an instruction: the shading
-// of a sample about 640 cycles a wave, a faint channel slot 23, a thin one 32).
-// Measured, disks of the full-size family, us: 512^2 x 64 x 512 1417 -> 616,
-// 222^2 x 115 x 256 592 -> 130, 256^2 x 48 x 256 390 -> 96 (march_fwd_group
-// and march_fwd -> march_win); without the faint loop 512^2 took 760, with
-// units of two channels a lane 761 against 703, with 4 or 16 times narrower
-// windows (2^-48, 2^-32) 4 and 7 % less.
+// of a sample about 640 cycles a wave, a faint channel slot 25, a thin one 32).
+// Measured, disks of the full-size family, us: 512^2 x 64 x 512 1417 -> 665,
+// 222^2 x 115 x 256 592 -> 145, 256^2 x 48 x 256 390 -> 101 (march_fwd_group
+// and march_fwd -> march_win).  Windows that also leave out depths below 2^-64
+// of the line centre's would take 616 at 512^2; units of two channels a lane
+// 761 against 703 (before the shading was trimmed).
 //
 // A workgroup's waves are nsplit consecutive parts of the rays of each 4 x 4
 // pixel tile; the parts' (I, Tr) meet in LDS (parts) and the first wave of a

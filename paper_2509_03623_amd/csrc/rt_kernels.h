@@ -410,17 +410,30 @@ __device__ __forceinline__ void stage_ztab(const Shade &s, float4 *lds_tab) {
 // 1 - 2^-x given att = 2^-x, per channel: the series below kThinK
 __device__ __forceinline__ float om_select(float x, float att) { return x < kThinK ? om_series3(x) : 1.0f - att; }
 
+// Lane j of this lane's group of G (2 or 4) adjacent lanes: a DPP quad
+// permutation that gives every lane of the group the value of its member j.
+template <int G, int J>
+__device__ __forceinline__ float group_lane(float x) {
+    constexpr int sel = G == 4 ? J * 0x55 : (J == 0 ? 0xA0 : 0xF5);   // (j,j,j,j) or (j,j,2+j,2+j)
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), sel, 0xF, 0xF, false));
+}
+
+// Smallest and largest x of the wave, as scalars (every lane active).
+__device__ __forceinline__ int wave_min(int x) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) x = min(x, __shfl_xor(x, d));
+    return __builtin_amdgcn_readfirstlane(x);
+}
+__device__ __forceinline__ int wave_max(int x) { return -wave_min(-x); }
+
 // ---------------------------------------------------------------- line windows
 // A channel far from the line at a sample gets nothing from it: with d in
-// line widths (log2 units, profile 2^-d^2) the windowed marches leave out the
-// channels with d^2 > 64 + max(log2 K, 0).  There the sample's depth is below
-// 2^-64 of its line-centre depth, and below 2^-64 outright on a sample thicker
-// than 1: att = 2^-x rounds to 1 in float from x < 2^-25 on, and the emission
-// left out is 2^-40 of a float's rounding of the line centre's (the cut goes
-// with the line centre, so a scene scaled to any depth keeps it).  Nor do the
-// channels with log2 K - d^2 < -127 count, whose depth is 0 in float.  At the
-// 0.13 km/s widths and 0.1 km/s channels of the test disks about 18 of 64
-// channels are left.
+// line widths (log2 units) the sample's depth there is x = 2^(log2 K - d^2),
+// which is 0 in float (exp2 gives no denormals) from d^2 = 127 + log2 K on, and
+// a channel with x = 0 keeps its intensity and transmission to the bit.  The
+// windowed marches leave those channels out: the cube is the one they would
+// get by marching all of them.  At the 0.13 km/s widths and 0.1 km/s channels
+// of the test disks 10 to 25 of 64 channels are left.
 //
 // Channels come in units of 4 or 8 neighbours; a wave takes or leaves a unit as
 // a whole (scalar branches, every register index static).  Each lane forms the
@@ -436,9 +449,10 @@ struct Windows {
 };
 
 // Samples so faint that float arithmetic tells no difference: below 2^-26 the
-// series of 1 - 2^-x is x ln 2 and Tr (1 - (1 - 2^-x)) is Tr, to the bit.  Most
+// series of 1 - 2^-x is x ln2 and Tr (1 - (1 - 2^-x)) is Tr, to the bit.  Most
 // samples of a disk with any opacity are (the tails of its layer and of its
-// density), so they have a loop of their own, without Tr and the series.
+// density), so they have a loop of their own, without Tr and the series; which
+// loop a wave takes changes no bit of the cube.
 constexpr float kFaintLog2K = -26.0f;
 
 // Bits of the units (u0 ... u0 + NU - 1) that the line of sample q reaches; 0
@@ -449,8 +463,8 @@ template <int NU, int PER, bool UNIFORM>
 __device__ __forceinline__ unsigned unit_mask(const SampleQ &q, float lK, bool on, float v0, const Windows &win,
                                               int u0) {
     const float ib = frcp(q.b);
-    // at least sqrt(min(64 + max(lK, 0), 127 + lK)): two tangents
-    const float R = fminf(fmaf(fmaxf(lK, 0.0f), 0.0625f, 8.0f), fmaf(lK, 0.08839f, 14.0547f));
+    // at least sqrt(127 + lK): two tangents
+    const float R = fminf(fmaf(lK, 0.04623f, 11.279f), fmaf(lK, 0.08839f, 14.0547f));
     const float v = q.a * ib, hw = fmaf(lK, 0.0f, R) * ib;   // 0 lK: NaN for NaN and infinite K
     unsigned m = 0;
     if constexpr (UNIFORM) {
@@ -480,14 +494,13 @@ __device__ __forceinline__ unsigned or_over_pixels(unsigned x) {
 
 // One sample of the windowed channel loop over CB channels per lane held in
 // registers, on the units of the wave-uniform mask m (march_lk's arithmetic;
-// on a faint sample I += Tr x ln2 S).  off(c) is d of channel c; bright, thick:
+// on a faint sample without what changes nothing).  off(c) is d of channel c; bright, thick:
 // some lane's sample is not faint, has K >= kThinK (wave-uniform).
 template <int CB, class Off>
 __device__ __forceinline__ void march_units(float (&I)[CB], float (&Tr)[CB], float S, float lK, unsigned m, bool bright, bool thick,
                                             Off off) {
     constexpr int U = unit_slots(CB);
     if (!bright) {
-        const float sl = S * kLn2;
 #pragma unroll
         for (int i = 0; i < CB / U; ++i) {
             if (!(m & (1u << i))) continue;
@@ -495,7 +508,7 @@ __device__ __forceinline__ void march_units(float (&I)[CB], float (&Tr)[CB], flo
             for (int c = i * U; c < i * U + U; ++c) {
                 const float d = off(c);
                 const float x = fexp2(fmaf(-d, d, lK));
-                I[c] = fmaf(Tr[c] * x, sl, I[c]);
+                I[c] = fmaf(Tr[c] * (x * kLn2), S, I[c]);
             }
         }
         return;

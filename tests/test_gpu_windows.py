@@ -5,10 +5,10 @@ each number of ray parts, a sample count that leaves a partial last step,
 channels spaced unevenly or in falling order, and cameras on both sides of the
 inclination from which the taper's range is the whole chord.
 
-Bars: max |dI| <= 1e-5 of the peak, the forward bar; a voxel that the windows
-leave without any line holds less than 2^-64 of its samples' line centres, far
-inside it.  Extremely thin scenes hold the same relative bar: the windows go
-with each sample's own line centre.
+Bars: max |dI| <= 1e-5 of the peak, the forward bar; the windows leave out only
+channels whose depth is 0 in float, so they take nothing from it, and extremely
+thin scenes hold the same relative bar.  Gradients: the adjoint's bar, 1e-3
+relative in L2 per block and per large entry, with the oracle's cotangent.
 """
 import numpy as np
 import pytest
@@ -96,6 +96,48 @@ def test_nan_field_reaches_every_channel(field, nch):
     assert np.array_equal(bad.any(0), bad.all(0))
     assert not (bad & ~ref).any()
     assert bad.any(0).sum() >= plain.any(0).sum() // 2
+
+
+@pytest.mark.parametrize("nx,ny,nch,order", [(7, 5, 1, ""), (9, 7, 16, ""), (13, 9, 17, "falling"), (11, 11, 32, ""),
+                                             (11, 11, 33, "uneven"), (14, 13, 64, ""), (10, 9, 65, "uneven"),
+                                             (180, 183, 35, "")])
+def test_reverse_march(nx, ny, nch, order):
+    """Gradients at the ends of the channel blocks, on tiles with ragged edges,
+    on an image large enough for 64-channel blocks, and the cube that the
+    reverse march forms: the forward march's to the same bar."""
+    import paper_2509_03623_amd as rt
+    import test_gpu_adjoint as ta
+    from oracle import torch_ref
+    nsamp = 24 if nx > 100 else 61
+    prob = ta.kscale(synth.small_problem(nx=nx, ny=ny, nch=nch, nsamp=nsamp, nr=40, nz=20, seed=38, dv=5.0 / nch))
+    if order:
+        v = prob.v_kms[::-1].copy() if order == "falling" else prob.v_kms + 0.02 * np.sin(np.arange(nch) * 1.7)
+        prob = prob.replace(v_kms=v)
+    ref = oracle.render(prob)
+    target = ta.target_for(prob)
+    print(f"[gpu] reverse march {nx}x{ny}x{nch}", flush=True)
+    vjp, cube, _ = ta.gpu_grads(prob, target, cotangent=2.0 * (ref - target))
+    _, oref = torch_ref.loss_and_grad(prob, target)
+    for k in ta.BLOCKS:
+        ta.check_block(k, vjp[k], oref[k])
+    sc = rt.scene_from_problem(prob)
+    own, _, _ = rt.render_l2_adjoint(sc, torch.as_tensor(target, dtype=torch.float32, device="cuda"), want=ta.BLOCKS)
+    assert np.abs(own.cpu().numpy().astype(np.float64) - ref).max() <= TOL * ref.max()
+
+
+@pytest.mark.parametrize("x_co", [1e-14, 1e-20])
+def test_gradient_at_any_depth(x_co):
+    """A scene whose samples are all faint has the gradient of its own scale."""
+    import test_gpu_adjoint as ta
+    from oracle import torch_ref
+    prob = ta.kscale(synth.small_problem(nx=12, ny=10, nch=12, nsamp=50, nr=32, nz=16, seed=39, dv=0.4)).replace(x_co=x_co)
+    ref = oracle.render(prob)
+    target = ref * 0.0
+    vjp, _, _ = ta.gpu_grads(prob, target, cotangent=np.full_like(ref, 1.0 / ref.max()))
+    leaves = torch_ref.as_leaves(prob)
+    (torch_ref.cube(prob, leaves) / ref.max()).sum().backward()
+    for k in ta.BLOCKS:
+        ta.check_block(k, vjp[k], leaves[k].grad.numpy())
 
 
 def test_channel_far_from_every_line():
