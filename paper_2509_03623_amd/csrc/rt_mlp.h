@@ -27,10 +27,11 @@ struct MlpDev {
 
 size_t mlp_prep_bytes(int precision);
 hipError_t mlp_prepare(const float *flat, int precision, void *buf, MlpDev *w, hipStream_t st);
+// out is written at the points where the march reads the network
 hipError_t mlp_forward(const Geometry &g, const Shade &s, const MlpDev &w, int precision, size_t M, float4 *out,
                        hipStream_t st);
-// list: device scratch of mlp_backward_list_bytes(M) (the BF16 backward's
-// list of the passes with any dL/do != 0, and their flags)
+// list: device scratch of mlp_backward_list_bytes(M) (the list of the points
+// whose dL/do counts, with its chunks' counts)
 size_t mlp_backward_list_bytes(size_t M);
 hipError_t mlp_backward(const Geometry &g, const Shade &s, const MlpDev &w, int precision, size_t M,
                         const float4 *dO, uint32_t *list, float *dW, hipStream_t st);
