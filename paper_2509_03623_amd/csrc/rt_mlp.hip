@@ -5,16 +5,9 @@
 // evaluated at every (pixel, sample) point of the render, point index
 // m = k * npix + pix.
 //
-// The BF16 path runs mlp_fwd_rr and mlp_bwd_rr; the FP32 reference path runs
-// mlp_fwd<float> and mlp_bwd<float>.
+// The BF16 path runs mlp_fwd_rr and mlp_bwd_rr; the FP32 path runs mlp_fwd_fr
+// and mlp_bwd_fr, the same designs on v_mfma_f32_16x16x4_f32.
 //
-// mlp_fwd<T, P>: a workgroup of 8 waves evaluates a tile of P points.  Layer
-//   outputs are 16 x 16 MFMA tiles: wave w owns output columns [16w, 16w+16)
-//   for every 16-point row tile; activations go through LDS between layers
-//   (row-major, the A-operand layout); weights are read as B operands
-//   straight from the prepared layout.  Bias + SiLU are fused on the
-//   accumulators.  T = bf16 (v_mfma_f32_16x16x32_bf16) or float
-//   (v_mfma_f32_16x16x4f32), FP32 accumulation in both.
 // mlp_fwd_rr (BF16): persistent workgroups holding all hidden weights in LDS;
 //   each wave evaluates 64 points at a time with the transposed product
 //   Z^T = W H^T, output neurons as MFMA rows and points as columns.  The
@@ -30,12 +23,7 @@
 //   miss the grid or lie beyond its taper, in no pattern that would leave
 //   whole waves of consecutive points out).
 // mlp_bwd_rr (BF16): see its definition below.
-// mlp_bwd<T, P>: persistent workgroups; each recomputes the forward of its
-//   tiles (keeping pre-activations and transposed activations in LDS),
-//   backpropagates dL/do through the layers on MFMA, and accumulates the
-//   weight gradient of the whole network in its own MFMA accumulators
-//   (wave w owns rows [16w, 16w+16) of every hidden layer's dW), flushing
-//   them with atomics once at the end.
+// mlp_fwd_fr, mlp_bwd_fr (FP32): see "register-resident FP32" below.
 #include <algorithm>
 #include <cmath>
 
@@ -51,30 +39,11 @@ constexpr int kW = 128;     // hidden width
 constexpr int kF = 64;      // features
 constexpr int kLayerIn[4] = {kF, kW, kW, kW};
 
-template <typename T> struct MM;
-template <> struct MM<__bf16> {
-    static constexpr int KCH = 32;   // K per MFMA
-    static constexpr int EPL = 8;    // elements per lane per fragment
-    typedef bf16x8 frag;
-    static __device__ __forceinline__ frag load(const __bf16 *p) { return *(const bf16x8 *)p; }
-    static __device__ __forceinline__ floatx4 mfma(frag a, frag b, floatx4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
-};
-template <> struct MM<float> {
-    static constexpr int KCH = 4;
-    static constexpr int EPL = 1;
-    typedef float frag;
-    static __device__ __forceinline__ frag load(const float *p) { return *p; }
-    static __device__ __forceinline__ floatx4 mfma(frag a, frag b, floatx4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-};
-
-__device__ __forceinline__ float silu(float z) { return z * sigmoidf_(z); }
-__device__ __forceinline__ float silu_d(float z) {
-    const float s = sigmoidf_(z);
-    return s * (1.0f + z * (1.0f - s));
+__device__ __forceinline__ floatx4 mfma_bf16(bf16x8 a, bf16x8 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mfma_f32(float a, float b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 // Normalised grid coordinates of point m (same positions as the march); true if
@@ -117,107 +86,6 @@ __device__ __forceinline__ float phase2(float f, float c) {
     const float hi = f * c;
     const float lo = fmaf(f, c, -hi);
     return (hi - 2.0f * floorf(0.5f * hi)) + lo;
-}
-
-// sin(pi f c), cos(pi f c)
-template <typename T>
-__device__ __forceinline__ void write_features(T *row, const MlpDev &w, float rh, float zh) {
-#pragma unroll 4
-    for (int q = 0; q < 16; ++q) {
-        float sr, cr, sz, cz;
-        sincospif(phase2(w.freq[q], rh), &sr, &cr);
-        sincospif(phase2(w.freq[q], zh), &sz, &cz);
-        row[q] = (T)sr;
-        row[16 + q] = (T)cr;
-        row[32 + q] = (T)sz;
-        row[48 + q] = (T)cz;
-    }
-}
-
-template <typename T> struct Pad { static constexpr int v = 16 / (int)sizeof(T); };
-
-// LDS layout of one tile (P points).
-template <typename T, int P, bool BWD> struct alignas(16) TileLds {
-    static constexpr int PD = Pad<T>::v;
-    static constexpr int S0 = kF + PD, S1 = kW + PD, ST = P + PD;
-    T h0[P * S0];
-    T h[4][P * S1];                          // post-activations of the hidden layers
-    T z[BWD ? 4 : 1][BWD ? P * S1 : 1];      // pre-activations
-    T hT0[BWD ? kF * ST : 1];                // transposed features
-    T hT[BWD ? 3 : 1][BWD ? kW * ST : 1];    // transposed activations of layers 1..3
-    T d[BWD ? P * S1 : 1];                   // dL/dz of the current layer
-    T dT[BWD ? kW * ST : 1];
-    float d5[BWD ? P * 3 : 1];
-};
-
-// Forward of one tile: features of points m0..m0+P-1, hidden layers, and
-// (when out != NULL) the 3 outputs.  Caller syncs before reusing LDS.
-template <typename T, int P, bool BWD>
-__device__ void tile_forward(TileLds<T, P, BWD> &L, const Geometry &g, const Shade &s, const MlpDev &w, size_t m0,
-                             size_t M, float4 *out) {
-    typedef MM<T> mm;
-    constexpr int S0 = TileLds<T, P, BWD>::S0, S1 = TileLds<T, P, BWD>::S1, ST = TileLds<T, P, BWD>::ST;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    if (tid < P) {
-        const size_t m = m0 + tid;
-        float rh = 0.0f, zh = 0.0f;
-        if (m < M) point_coords(g, s, m, &rh, &zh);
-        write_features<T>(L.h0 + tid * S0, w, rh, zh);
-    }
-    __syncthreads();
-    if (BWD) {
-        for (int i = tid; i < P * kF; i += 512) {
-            const int mm_ = i / kF, k = i - mm_ * kF;
-            L.hT0[k * ST + mm_] = L.h0[mm_ * S0 + k];
-        }
-    }
-#pragma unroll
-    for (int l = 0; l < 4; ++l) {
-        const int K = kLayerIn[l];
-        const T *hin = l == 0 ? L.h0 : L.h[l - 1];
-        const int SI = l == 0 ? S0 : S1;
-        const T *W = (const T *)w.W[l];
-        const int n = 16 * wv + (lane & 15);
-        const float bias = w.b[l][n];
-#pragma unroll
-        for (int mt = 0; mt < P / 16; ++mt) {
-            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int kc = 0; kc < K / mm::KCH; ++kc) {
-                const int k0 = kc * mm::KCH + (lane >> 4) * mm::EPL;
-                acc = mm::mfma(mm::load(hin + (mt * 16 + (lane & 15)) * SI + k0), mm::load(W + n * K + k0), acc);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = mt * 16 + 4 * (lane >> 4) + i;
-                const float zv = acc[i] + bias;
-                const float hv = silu(zv);
-                L.h[l][m * S1 + n] = (T)hv;
-                if (BWD) {
-                    L.z[l][m * S1 + n] = (T)zv;
-                    if (l < 3) L.hT[l][n * ST + m] = (T)hv;
-                }
-            }
-        }
-        __syncthreads();
-    }
-    if (out && tid < P) {
-        const size_t m = m0 + tid;
-        float o0 = w.b5[0], o1 = w.b5[1], o2 = w.b5[2];
-        const T *hr = L.h[3] + tid * S1;
-        for (int k = 0; k < kW; ++k) {
-            const float hv = (float)hr[k];
-            o0 = fmaf(hv, w.W5[k], o0);
-            o1 = fmaf(hv, w.W5[kW + k], o1);
-            o2 = fmaf(hv, w.W5[2 * kW + k], o2);
-        }
-        if (m < M) out[m] = make_float4(o0, o1, o2, 0.0f);
-    }
-}
-
-template <typename T, int P>
-__global__ __launch_bounds__(512) void mlp_fwd(Geometry g, Shade s, MlpDev w, size_t M, float4 *__restrict__ out) {
-    __shared__ TileLds<T, P, false> L;
-    tile_forward<T, P, false>(L, g, s, w, (size_t)blockIdx.x * P, M, out);
 }
 
 // ---------------------------------------------------------------- register-resident BF16 forward
@@ -272,7 +140,6 @@ template <int NP>
 __device__ __forceinline__ void rr_layer(const bf16x8 (&hin)[4][NP], bf16x8 (&hout)[4][NP], float (&o)[3][NP],
                                          const __bf16 *sW, const float *sB, const float *sW5, int l, int lg, int lc,
                                          bool last) {
-    typedef MM<__bf16> mm;
     const int nk = l == 0 ? kF / 32 : kW / 32;
     const int row = l == 0 ? kRrRow0 : kRrRow;
     const __bf16 *Wl = sW + (l == 0 ? 0 : (size_t)kW * kRrRow0 + (size_t)(l - 1) * kW * kRrRow);
@@ -293,7 +160,7 @@ __device__ __forceinline__ void rr_layer(const bf16x8 (&hin)[4][NP], bf16x8 (&ho
             for (int h = 0; h < 2; ++h) {
                 const bf16x8 a = *(const bf16x8 *)(Wl + (size_t)(32 * cp + 16 * h + lc) * row + 32 * c + 8 * lg);
 #pragma unroll
-                for (int tp = 0; tp < NP; ++tp) acc[h][tp] = mm::mfma(a, hin[c][tp], acc[h][tp]);
+                for (int tp = 0; tp < NP; ++tp) acc[h][tp] = mfma_bf16(a, hin[c][tp], acc[h][tp]);
             }
         }
         if (!last) {
@@ -511,7 +378,6 @@ __device__ __forceinline__ void br_write_rows(__bf16 *X, const bf16x8 (&v)[4], i
 template <int NI>
 __device__ __forceinline__ void br_dw(floatx4 (&acc)[2][NI], const __bf16 *XD, const __bf16 *XH, int wv, int lg,
                                       int lc) {
-    typedef MM<__bf16> mm;
 #pragma unroll
     for (int kc = 0; kc < kBrPts / 32; ++kc) {
         const bf16x8 a0 = *(const bf16x8 *)(XD + (32 * wv + lc) * kBrStride + 32 * kc + 8 * lg);
@@ -519,8 +385,8 @@ __device__ __forceinline__ void br_dw(floatx4 (&acc)[2][NI], const __bf16 *XD, c
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
             const bf16x8 b = *(const bf16x8 *)(XH + (16 * it + lc) * kBrStride + 32 * kc + 8 * lg);
-            acc[0][it] = mm::mfma(a0, b, acc[0][it]);
-            acc[1][it] = mm::mfma(a1, b, acc[1][it]);
+            acc[0][it] = mfma_bf16(a0, b, acc[0][it]);
+            acc[1][it] = mfma_bf16(a1, b, acc[1][it]);
         }
     }
 }
@@ -687,7 +553,6 @@ __global__ __launch_bounds__(1024) void mlp_live_write(const float4 *__restrict_
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void mlp_bwd_rr(
     Geometry g, Shade s, MlpDev w, size_t M, const float4 *__restrict__ dO, const uint32_t *__restrict__ list,
     float *__restrict__ dW) {
-    typedef MM<__bf16> mm;
     // point-major rows of the backward: dL/dz' (or dL/do) rows x points, then
     // h' (or features) rows x points; in the forward, layers 1 and 3's weights
     __shared__ __attribute__((aligned(16))) __bf16 XU[2 * kW * kBrStride];
@@ -769,7 +634,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const bf16x8 a = *(const bf16x8 *)(Wl + (32 * cp + 16 * h + lc) * row + 32 * c + 8 * lg);
-                        acc[h] = mm::mfma(a, hin[c], acc[h]);
+                        acc[h] = mfma_bf16(a, hin[c], acc[h]);
                     }
                 }
                 bf16x8 zq;
@@ -837,7 +702,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         const bf16x8 b = *(const bf16x8 *)(XH + (16 * (wv + 4 * q) + lc) * kBrStride + 32 * kc + 8 * lg);
-                        g4[q][0] = mm::mfma(a, b, g4[q][0]);
+                        g4[q][0] = mfma_bf16(a, b, g4[q][0]);
                     }
                 }
                 if (wv == 0) {
@@ -872,7 +737,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
                             const bf16x8 a = *(const bf16x8 *)(WT + (32 * cp + 16 * h + lc) * kRrRow + 32 * c + 8 * lg);
-                            acc[h] = mm::mfma(a, dzu[c], acc[h]);
+                            acc[h] = mfma_bf16(a, dzu[c], acc[h]);
                         }
                     const bf16x8 zq = ZP[4 * (l - 1) + cp][tid];
 #pragma unroll
@@ -927,201 +792,549 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (wv == 0 && lane < 6 && bhalf == 0) atomicAdd(dW + w.off[4] + 3 * kW + (lane >> 1), db5);
 }
 
-template <typename T, int P>
-__global__ __launch_bounds__(512) void mlp_bwd(Geometry g, Shade s, MlpDev w, size_t M, const float4 *__restrict__ dO,
-                                               float *__restrict__ dW) {
-    typedef MM<T> mm;
-    __shared__ TileLds<T, P, true> L;
-    constexpr int S1 = TileLds<T, P, true>::S1, ST = TileLds<T, P, true>::ST;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // weight-gradient accumulators: wave wv owns rows [16 wv, 16 wv + 16) of
-    // every hidden layer; k-tiles of 16 columns
-    floatx4 a0[kF / 16], a1[kW / 16], a2[kW / 16], a3[kW / 16];
-#pragma unroll
-    for (int i = 0; i < kF / 16; ++i) a0[i] = floatx4{0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < kW / 16; ++i) { a1[i] = floatx4{0, 0, 0, 0}; a2[i] = a1[i]; a3[i] = a1[i]; }
-    float db[4] = {0, 0, 0, 0};   // bias gradients, thread tid < 128 owns row tid
-    float dw5 = 0.0f, db5 = 0.0f; // thread tid < 384 owns W5[tid / 128][tid % 128]; tid < 3 owns b5
-    const size_t ntiles = (M + P - 1) / P;
-    for (size_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const size_t m0 = tile * P;
-        tile_forward<T, P, true>(L, g, s, w, m0, M, nullptr);
-        // output layer
-        if (tid < P) {
-            const size_t m = m0 + tid;
-            const float4 d = m < M ? dO[m] : make_float4(0, 0, 0, 0);
-            L.d5[tid * 3 + 0] = d.x; L.d5[tid * 3 + 1] = d.y; L.d5[tid * 3 + 2] = d.z;
-        }
-        __syncthreads();
-        if (tid < 3 * kW) {
-            const int j = tid / kW, k = tid - j * kW;
-            float acc = 0.0f;
-            for (int m = 0; m < P; ++m) acc = fmaf(L.d5[m * 3 + j], (float)L.h[3][m * S1 + k], acc);
-            dw5 += acc;
-        }
-        if (tid < 3) {
-            float acc = 0.0f;
-            for (int m = 0; m < P; ++m) acc += L.d5[m * 3 + tid];
-            db5 += acc;
-        }
-        for (int i = tid; i < P * kW; i += 512) {
-            const int m = i / kW, n = i - m * kW;
-            const float gz = L.d5[m * 3] * w.W5[n] + L.d5[m * 3 + 1] * w.W5[kW + n] + L.d5[m * 3 + 2] * w.W5[2 * kW + n];
-            const T dv = (T)(gz * silu_d((float)L.z[3][m * S1 + n]));
-            L.d[m * S1 + n] = dv;
-            L.dT[n * ST + m] = dv;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int l = 3; l >= 0; --l) {
-            // dW_l[n][k] += sum_m d[m][n] h_{l-1}[m][k]   (rows n of this wave)
-            const int K = kLayerIn[l];
-            const T *hT = l == 0 ? L.hT0 : L.hT[l - 1];
-            const T *arow = L.dT + (16 * wv + (lane & 15)) * ST;
-#pragma unroll
-            for (int kt = 0; kt < K / 16; ++kt) {
-                floatx4 acc = l == 0 ? a0[kt % (kF / 16)] : (l == 1 ? a1[kt] : (l == 2 ? a2[kt] : a3[kt]));
-                const T *brow = hT + (16 * kt + (lane & 15)) * ST;
-                for (int mc = 0; mc < P / mm::KCH; ++mc) {
-                    const int k0 = mc * mm::KCH + (lane >> 4) * mm::EPL;
-                    acc = mm::mfma(mm::load(arow + k0), mm::load(brow + k0), acc);
-                }
-                if (l == 0) a0[kt % (kF / 16)] = acc;
-                else if (l == 1) a1[kt] = acc;
-                else if (l == 2) a2[kt] = acc;
-                else a3[kt] = acc;
-            }
-            if (tid < kW) {
-                float acc = 0.0f;
-                for (int m = 0; m < P; ++m) acc += (float)L.dT[tid * ST + m];
-                db[l] += acc;
-            }
-            if (l == 0) break;
-            // g_{l-1}[m][k] = sum_n d[m][n] W_l[n][k]   (columns k of this wave)
-            floatx4 gacc[P / 16];
-            const T *WT = (const T *)w.WT[l];
-            const int k = 16 * wv + (lane & 15);
-#pragma unroll
-            for (int mt = 0; mt < P / 16; ++mt) {
-                floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-                for (int nc = 0; nc < kW / mm::KCH; ++nc) {
-                    const int n0 = nc * mm::KCH + (lane >> 4) * mm::EPL;
-                    acc = mm::mfma(mm::load(L.d + (mt * 16 + (lane & 15)) * S1 + n0), mm::load(WT + k * kW + n0), acc);
-                }
-                gacc[mt] = acc;
-            }
-            __syncthreads();   // every wave is done reading d / dT of layer l
-#pragma unroll
-            for (int mt = 0; mt < P / 16; ++mt) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int m = mt * 16 + 4 * (lane >> 4) + i;
-                    const T dv = (T)(gacc[mt][i] * silu_d((float)L.z[l - 1][m * S1 + k]));
-                    L.d[m * S1 + k] = dv;
-                    L.dT[k * ST + m] = dv;
-                }
-            }
-            __syncthreads();
-        }
-        __syncthreads();
+// ---------------------------------------------------------------- register-resident FP32
+// mlp_fwd_fr, mlp_bwd_fr: the transposed product Z^T = W H^T on
+// v_mfma_f32_16x16x4_f32.  The accumulator of output tile t leaves lane group
+// lg (16 lanes) with neurons 16 t + 4 lg + i, i < 4, of its lane's point, and a
+// 4-deep step of the next product takes one value per lane group: step (t, i)
+// takes neurons 16 t + 4 lg + i, which is the accumulator register itself.  The
+// weights of four steps are then four consecutive values of a row, one 16-byte
+// read; rows are padded by 16 bytes against bank conflicts.  A layer's weights
+// (66 KB) go from L2 to LDS once per pass for all waves of a workgroup, issued
+// one stage ahead with loads that write LDS directly.
+//
+// Bound: the FP32 matrix rate (157 TFLOP/s; 32 cycles an instruction).  The
+// tiled kernels before these read every operand from LDS or L2 at its use, one
+// tile after another through LDS, over every point: 90 x 83 px x 128 samples
+// 5.76 -> 0.80 ms forward (65 TFLOP/s over the points that are read), 12.8 ->
+// 2.06 ms backward (one wave per SIMD: its activations, LDS rows and barriers
+// run beside nothing).
+constexpr int kFrRow0 = kF + 4, kFrRow = kW + 4;      // padded rows (floats)
+constexpr size_t kFrWeightElems = (size_t)kW * kFrRow0 + 3 * (size_t)kW * kFrRow;
+constexpr int kFrTiles = 2;                           // 16-point column tiles per wave
+constexpr int kFrThreads = 512;
+constexpr int kFrQueue = 16 * kFrTiles + 64;          // points a wave holds at most
+constexpr int kFrStride = kBrPts + 4;                 // LDS row of the point-major buffers
+constexpr int kFrSlab = 36 * 256;                     // floatx4 a workgroup parks: z of 4 layers, features
+
+__global__ void mlp_prep_fr(const float *__restrict__ flat, MlpDev w) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    float *Wr = (float *)w.Wr, *WrT = (float *)w.WrT;
+    if (i < kW * kFrRow0) {
+        const int o = i / kFrRow0, k = i - o * kFrRow0;
+        Wr[i] = k < kF ? flat[w.off[0] + o * kF + k] : 0.0f;
     }
-    // flush: flat layout per layer W [out][in] then b [out]
-    const int n_base = 16 * wv + 4 * (lane >> 4);
-#pragma unroll
-    for (int l = 0; l < 4; ++l) {
-        const int K = kLayerIn[l];
-        float *Wg = dW + w.off[l];
-        for (int kt = 0; kt < K / 16; ++kt) {
-            const floatx4 acc = l == 0 ? a0[kt % (kF / 16)] : (l == 1 ? a1[kt] : (l == 2 ? a2[kt] : a3[kt]));
-            const int k = 16 * kt + (lane & 15);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (acc[i] != 0.0f) atomicAdd(Wg + (n_base + i) * K + k, acc[i]);
+    if (i < kW * kFrRow) {
+        const int o = i / kFrRow, k = i - o * kFrRow;
+        for (int l = 1; l < 4; ++l) {
+            Wr[(size_t)kW * kFrRow0 + (size_t)(l - 1) * kW * kFrRow + i] = k < kW ? flat[w.off[l] + o * kW + k] : 0.0f;
+            WrT[(size_t)(l - 1) * kW * kFrRow + i] = k < kW ? flat[w.off[l] + k * kW + o] : 0.0f;
         }
-        if (tid < kW && db[l] != 0.0f) atomicAdd(dW + w.off[l] + kW * K + tid, db[l]);
     }
-    if (tid < 3 * kW && dw5 != 0.0f) atomicAdd(dW + w.off[4] + tid, dw5);
-    if (tid < 3 && db5 != 0.0f) atomicAdd(dW + w.off[4] + 3 * kW + tid, db5);
 }
 
-// Prepared weights from the flat float32 layout (W [out][in], b [out] per
-// layer): row-major and transposed copies in T, float biases, float output layer.
-template <typename T>
+// copy n floats (a multiple of 256) to LDS, 16 B per lane and load
+typedef const __attribute__((address_space(1))) float gfloat;
+template <int NT>
+__device__ __forceinline__ void fr_issue(float *dst, const gfloat *src, int n, int tid) {
+    typedef __attribute__((address_space(3))) void lds_void;
+    typedef const __attribute__((address_space(1))) void g_void;
+    const int wv = tid >> 6, lane = tid & 63;
+    __builtin_amdgcn_sched_barrier(0);
+    for (int c0 = 64 * wv; c0 < n / 4; c0 += NT)
+        __builtin_amdgcn_global_load_lds((g_void *)(src + 4 * (c0 + lane)), (lds_void *)(dst + 4 * c0), 16, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+}
+static_assert(kW * kFrRow0 % 256 == 0 && kW * kFrRow % 256 == 0, "whole waves of 16-byte lanes");
+
+// features 16 t + 4 lg + i of the lane's point: sin r, cos r, sin z, cos z of
+// frequencies 4 lg + i
+__device__ __forceinline__ void fr_features(floatx4 (&f)[4], const MlpDev &w, float cr, float cz, int lg) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float s, c;
+        sincospif(phase2(w.freq[4 * lg + i], cr), &s, &c);
+        f[0][i] = s;
+        f[1][i] = c;
+        sincospif(phase2(w.freq[4 * lg + i], cz), &s, &c);
+        f[2][i] = s;
+        f[3][i] = c;
+    }
+}
+
+// U output tiles from tile u0 on, over the 16 NK inputs: acc += W h
+template <int NK, int U, int NP>
+__device__ __forceinline__ void fr_product(floatx4 (&acc)[U][NP], const floatx4 (&h)[8][NP], const float *W, int row,
+                                           int u0, int lg, int lc) {
+#pragma unroll
+    for (int t = 0; t < NK; ++t) {
+        floatx4 a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = *(const floatx4 *)(W + (16 * (u0 + u) + lc) * row + 16 * t + 4 * lg);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) acc[u][p] = mfma_f32(a[u][i], h[t][p][i], acc[u][p]);
+    }
+}
+
+template <int NK, bool LAST>
+__device__ __forceinline__ void fr_layer(const floatx4 (&hin)[8][kFrTiles], floatx4 (&hout)[8][kFrTiles],
+                                         float (&o)[3][kFrTiles], const float *W, int row, const float *b,
+                                         const float *sW5, int lg, int lc) {
+#pragma unroll
+    for (int u0 = 0; u0 < 8; u0 += 2) {
+        floatx4 acc[2][kFrTiles];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int p = 0; p < kFrTiles; ++p) acc[u][p] = *(const floatx4 *)(b + 16 * (u0 + u) + 4 * lg);
+        fr_product<NK, 2, kFrTiles>(acc, hin, W, row, u0, lg, lc);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int n = 16 * (u0 + u) + 4 * lg;
+#pragma unroll
+            for (int p = 0; p < kFrTiles; ++p)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float z = acc[u][p][i], hv = z * sigmoidf_(z);
+                    if (LAST) {
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) o[j][p] = fmaf(hv, sW5[j * kW + n + i], o[j][p]);
+                    } else {
+                        hout[u0 + u][p][i] = hv;
+                    }
+                }
+        }
+    }
+}
+
+__global__ __launch_bounds__(kFrThreads) void mlp_fwd_fr(Geometry g, Shade s, MlpDev w, size_t M,
+                                                         float4 *__restrict__ out) {
+    // the weights of layers 0 and 2, and of 1 and 3
+    __shared__ __attribute__((aligned(16))) float SW[2][kW * kFrRow];
+    __shared__ __attribute__((aligned(16))) float sB[4 * kW];
+    __shared__ float sW5[3 * kW];
+    __shared__ PointEntry queues[kFrThreads / 64][kFrQueue];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lg = lane >> 4, lc = lane & 15;
+    for (int i = tid; i < 4 * kW; i += kFrThreads) sB[i] = w.b[i / kW][i % kW];
+    for (int i = tid; i < 3 * kW; i += kFrThreads) sW5[i] = w.W5[i];
+    const gfloat *Wr = (const gfloat *)(uint64_t)w.Wr;
+    fr_issue<kFrThreads>(SW[0], Wr, kW * kFrRow0, tid);
+    br_wait();
+    __syncthreads();
+    PointEntry *queue = queues[wv];
+    const unsigned takers = gridDim.x * (kFrThreads / 64), taker = blockIdx.x * (kFrThreads / 64) + wv;
+    const size_t rounds = ((M + 63) / 64 + takers - 1) / takers;
+    size_t round = 0;
+    int fill = 0;
+    for (;;) {
+        // the points the march reads, gathered as in mlp_fwd_rr; the waves of a
+        // workgroup pass through the layers together, the idle ones with no points
+        while (fill < 16 * kFrTiles && round < rounds) {
+            const size_t m = dealt_group(round++, taker, takers) * 64 + lane;
+            float rh = 0.0f, zh = 0.0f;
+            const bool read = m < M && point_coords(g, s, m, &rh, &zh);
+            const unsigned long long mk = __ballot(read);
+            if (read) queue[fill + __popcll(mk & ((1ull << lane) - 1ull))] = point_entry(m, rh, zh);
+            fill += __popcll(mk);
+        }
+        if (!__syncthreads_or(fill > 0)) break;
+        const int n = min(fill, 16 * kFrTiles);
+        floatx4 ha[8][kFrTiles], hb[8][kFrTiles];
+#pragma unroll
+        for (int p = 0; p < kFrTiles; ++p) {
+            const int e = 16 * p + lc;
+            const float cr = e < n ? queue[e].rh : 0.0f, cz = e < n ? queue[e].zh : 0.0f;
+            floatx4 f[4];
+            fr_features(f, w, cr, cz, lg);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ha[t][p] = f[t];
+        }
+        float o[3][kFrTiles];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int p = 0; p < kFrTiles; ++p) o[j][p] = 0.0f;
+        auto next = [&](int buf, size_t off, int count) { fr_issue<kFrThreads>(SW[buf], Wr + off, count, tid); };
+        auto done = [&] { br_wait(); __syncthreads(); };
+        constexpr size_t L1 = (size_t)kW * kFrRow0, LN = (size_t)kW * kFrRow;
+        next(1, L1, kW * kFrRow);
+        fr_layer<4, false>(ha, hb, o, SW[0], kFrRow0, sB, sW5, lg, lc);
+        done();
+        next(0, L1 + LN, kW * kFrRow);
+        fr_layer<8, false>(hb, ha, o, SW[1], kFrRow, sB + kW, sW5, lg, lc);
+        done();
+        next(1, L1 + 2 * LN, kW * kFrRow);
+        fr_layer<8, false>(ha, hb, o, SW[0], kFrRow, sB + 2 * kW, sW5, lg, lc);
+        done();
+        next(0, 0, kW * kFrRow0);
+        fr_layer<8, true>(hb, ha, o, SW[1], kFrRow, sB + 3 * kW, sW5, lg, lc);
+        done();
+#pragma unroll
+        for (int p = 0; p < kFrTiles; ++p) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                o[j][p] += __shfl_xor(o[j][p], 16);
+                o[j][p] += __shfl_xor(o[j][p], 32);
+            }
+            if (lg == 0 && 16 * p + lc < n)
+                out[point_index(queue[16 * p + lc])] =
+                    make_float4(o[0][p] + w.b5[0], o[1][p] + w.b5[1], o[2][p] + w.b5[2], 0.0f);
+        }
+        fill -= n;
+        if (lane < fill) {
+            const PointEntry e = queue[16 * kFrTiles + lane];
+            queue[lane] = e;
+        }
+    }
+}
+
+// h and dL/dz = dL/dh SiLU'(z) of one neuron
+__device__ __forceinline__ void fr_act_grad(float z, float dh, float *h, float *dz) {
+    const float sg = sigmoidf_(z);
+    *h = z * sg;
+    *dz = dh * (sg * (1.0f + z * (1.0f - sg)));
+}
+
+// point-major write of a lane's neurons 16 t + 4 lg + i of its point
+template <int N>
+__device__ __forceinline__ void fr_write_rows(float *X, const floatx4 (&v)[N], int lg, int col) {
+#pragma unroll
+    for (int t = 0; t < N; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) X[(16 * t + 4 * lg + i) * kFrStride + col] = v[t][i];
+}
+
+// dW slice of one hidden layer over the 64 points, as br_dw
+template <int NI>
+__device__ __forceinline__ void fr_dw(floatx4 (&acc)[2][NI], const float *XD, const float *XH, int wv, int lg, int lc) {
+#pragma unroll
+    for (int kc = 0; kc < kBrPts / 16; ++kc) {
+        const floatx4 a0 = *(const floatx4 *)(XD + (32 * wv + lc) * kFrStride + 16 * kc + 4 * lg);
+        const floatx4 a1 = *(const floatx4 *)(XD + (32 * wv + 16 + lc) * kFrStride + 16 * kc + 4 * lg);
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            const floatx4 b = *(const floatx4 *)(XH + (16 * it + lc) * kFrStride + 16 * kc + 4 * lg);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc[0][it] = mfma_f32(a0[i], b[i], acc[0][it]);
+                acc[1][it] = mfma_f32(a1[i], b[i], acc[1][it]);
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ float fr_rowsum(const float *X, int r, int half) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const floatx4 v = *(const floatx4 *)(X + r * kFrStride + 32 * half + 4 * q);
+        sum += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    return sum + __shfl_xor(sum, 1);
+}
+
+// The passes of mlp_bwd_rr in FP32: one workgroup of four waves per CU, 64
+// listed points a pass, 16 per wave; the recomputed forward parks z of every
+// layer and the features lane-privately in the workgroup's slab of global
+// memory (147 KB, 38 MB for the chip: it stays in the caches; LDS holds the
+// weights and the point-major rows), and the weight gradient accumulates in 232
+// registers of each wave over all passes.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void mlp_bwd_fr(
+    Geometry g, Shade s, MlpDev w, size_t M, const float4 *dO, const uint32_t *list, float *dW, floatx4 *slabs) {
+    // point-major rows of the backward: dL/dz (or dL/do), then h (or features);
+    // in the forward, layers 1 and 3's weights
+    __shared__ __attribute__((aligned(16))) float XU[2 * kW * kFrStride];
+    static_assert(2 * kW * kFrStride >= kW * kFrRow, "a hidden layer's weights fit the row buffers");
+    float *const XD = XU;
+    float *const XH = XU + kW * kFrStride;
+    __shared__ __attribute__((aligned(16))) float SW[kW * kFrRow];
+    __shared__ __attribute__((aligned(16))) float sB[4 * kW];
+    __shared__ __attribute__((aligned(16))) float sW5[3 * kW];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lg = lane >> 4, lc = lane & 15;
+    floatx4 *const slab = slabs + (size_t)blockIdx.x * kFrSlab + tid;
+    for (int i = tid; i < 4 * kW; i += 256) sB[i] = w.b[i / kW][i % kW];
+    for (int i = tid; i < 3 * kW; i += 256) sW5[i] = w.W5[i];
+    const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    floatx4 g0[2][4], g1[2][8], g2[2][8], g3[2][8], g4[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) g0[a][b] = zero;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) { g1[a][b] = zero; g2[a][b] = zero; g3[a][b] = zero; }
+        g4[a] = zero;
+    }
+    float db0 = 0.0f, db1 = 0.0f, db2 = 0.0f, db3 = 0.0f, db5 = 0.0f;
+    const int brow = 32 * wv + (lane >> 1), bhalf = lane & 1;     // bias row of this lane
+    const int col = 16 * wv + lc;                                 // this lane's point within the pass
+    constexpr size_t L1 = (size_t)kW * kFrRow0, LN = (size_t)kW * kFrRow;
+    fr_issue<256>(SW, (const gfloat *)(uint64_t)w.Wr, kW * kFrRow0, tid);
+    br_wait();
+    __syncthreads();
+    const uint32_t npts = list[0];
+    const uint32_t npass = (npts + kBrPts - 1) / kBrPts;
+    for (uint32_t ip = blockIdx.x; ip < npass; ip += gridDim.x) {
+        const uint32_t base = ip * kBrPts;
+        const gfloat *Wr = (const gfloat *)(uint64_t)w.Wr, *WrT = (const gfloat *)(uint64_t)w.WrT;
+        const size_t m = base + col < npts ? (size_t)list[1 + base + col] : M;   // M: no point
+        float rh = 0.0f, zh = 0.0f;
+        if (lane < 16 && m < M) point_coords(g, s, m, &rh, &zh);
+        floatx4 h[8][1];
+        {
+            floatx4 f[4];
+            fr_features(f, w, __shfl(rh, lc), __shfl(zh, lc), lg);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                slab[(32 + t) * 256] = f[t];
+                h[t][0] = f[t];
+            }
+        }
+        // ---- forward, parking z of every layer
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            // the next stage goes into the buffer that layer l does not read
+            if (l < 3) fr_issue<256>(l & 1 ? SW : XU, Wr + L1 + l * LN, kW * kFrRow, tid);
+            else fr_issue<256>(SW, WrT + 2 * LN, kW * kFrRow, tid);
+            const float *W = l & 1 ? XU : SW;
+            floatx4 hout[8];
+#pragma unroll
+            for (int u0 = 0; u0 < 8; u0 += 4) {
+                floatx4 acc[4][1];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[u][0] = *(const floatx4 *)(sB + l * kW + 16 * (u0 + u) + 4 * lg);
+                if (l == 0) fr_product<4, 4, 1>(acc, h, W, kFrRow0, u0, lg, lc);
+                else fr_product<8, 4, 1>(acc, h, W, kFrRow, u0, lg, lc);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    slab[(8 * l + u0 + u) * 256] = acc[u][0];
+                    if (l < 3) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) hout[u0 + u][i] = acc[u][0][i] * sigmoidf_(acc[u][0][i]);
+                    }
+                }
+            }
+            if (l < 3) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) h[t][0] = hout[t];
+            }
+            br_wait();
+            __syncthreads();
+        }
+        // ---- output layer: dL/dh_3 = W5^T dL/do, then h_3 and dL/dz_3
+        const float4 d = m < M ? dO[m] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        floatx4 hp[8], dz[8][1], dzu[8][1];   // h and dL/dz of the current layer, dL/dz of the layer above
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const floatx4 z = slab[(24 + u) * 256];
+            const int n = 16 * u + 4 * lg;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float dh = fmaf(sW5[n + i], d.x, fmaf(sW5[kW + n + i], d.y, sW5[2 * kW + n + i] * d.z));
+                float hv, dv;
+                fr_act_grad(z[i], dh, &hv, &dv);
+                hp[u][i] = hv;
+                dz[u][0][i] = dv;
+            }
+        }
+#pragma unroll
+        for (int l = 3; l >= 0; --l) {
+            // gradient of the layer above (the output layer when l == 3): its
+            // dL/dz and this layer's h, point-major
+            fr_write_rows<8>(XH, hp, lg, col);
+            if (l == 3) {
+                if (lg == 0) {
+                    XD[0 * kFrStride + col] = d.x;
+                    XD[1 * kFrStride + col] = d.y;
+                    XD[2 * kFrStride + col] = d.z;
+                } else {
+                    // rows 3..15 are zero padding of the 16-row tile
+#pragma unroll
+                    for (int r = 0; r < 5; ++r) {
+                        const int rr = 3 + 5 * (lg - 1) + r;
+                        if (rr < 16) XD[rr * kFrStride + col] = 0.0f;
+                    }
+                }
+            } else {
+                floatx4 v[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v[t] = dzu[t][0];
+                fr_write_rows<8>(XD, v, lg, col);
+            }
+            __syncthreads();
+            // SW is free: the transposed weights of the next product down, or
+            // after the last one the next pass's layer 0
+            if (l == 2 || l == 1) fr_issue<256>(SW, WrT + (l - 1) * LN, kW * kFrRow, tid);
+            else if (l == 0) fr_issue<256>(SW, Wr, kW * kFrRow0, tid);
+            if (l == 3) {
+#pragma unroll
+                for (int kc = 0; kc < kBrPts / 16; ++kc) {
+                    const floatx4 a = *(const floatx4 *)(XD + lc * kFrStride + 16 * kc + 4 * lg);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const floatx4 b = *(const floatx4 *)(XH + (16 * (wv + 4 * q) + lc) * kFrStride + 16 * kc + 4 * lg);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) g4[q] = mfma_f32(a[i], b[i], g4[q]);
+                    }
+                }
+                if (wv == 0) {
+                    const float v = fr_rowsum(XD, (lane >> 1) & 15, bhalf);   // rows 0..2 are dL/do
+                    if (lane < 6) db5 += v;
+                }
+            } else if (l == 2) {
+                fr_dw<8>(g3, XD, XH, wv, lg, lc);
+                db3 += fr_rowsum(XD, brow, bhalf);
+            } else if (l == 1) {
+                fr_dw<8>(g2, XD, XH, wv, lg, lc);
+                db2 += fr_rowsum(XD, brow, bhalf);
+            } else {
+                fr_dw<8>(g1, XD, XH, wv, lg, lc);
+                db1 += fr_rowsum(XD, brow, bhalf);
+            }
+            if (l != 0) br_wait();
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < 8; ++t) dzu[t][0] = dz[t][0];
+            // dL/dh of the layer below through the transposed weights, and at
+            // once its h and dL/dz
+            if (l >= 1) {
+#pragma unroll
+                for (int u0 = 0; u0 < 8; u0 += 4) {
+                    floatx4 acc[4][1] = {{zero}, {zero}, {zero}, {zero}};
+                    fr_product<8, 4, 1>(acc, dzu, SW, kFrRow, u0, lg, lc);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const floatx4 z = slab[(8 * (l - 1) + u0 + u) * 256];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            float hv, dv;
+                            fr_act_grad(z[i], acc[u][0][i], &hv, &dv);
+                            hp[u0 + u][i] = hv;
+                            dz[u0 + u][0][i] = dv;
+                        }
+                    }
+                }
+            }
+        }
+        // ---- layer 0: features and dz_0
+        {
+            floatx4 f[4], v[8];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) f[t] = slab[(32 + t) * 256];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] = dz[t][0];
+            fr_write_rows<4>(XH, f, lg, col);
+            fr_write_rows<8>(XD, v, lg, col);
+        }
+        __syncthreads();
+        fr_dw<4>(g0, XD, XH, wv, lg, lc);
+        db0 += fr_rowsum(XD, brow, bhalf);
+        br_wait();   // the next pass's layer-0 weights
+        __syncthreads();
+    }
+    // ---- flush: flat layout per layer W [out][in] then b [out]
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int o = 32 * wv + 16 * a + 4 * lg + i;
+#pragma unroll
+            for (int it = 0; it < 4; ++it) atomicAdd(dW + w.off[0] + o * kF + 16 * it + lc, g0[a][it][i]);
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                atomicAdd(dW + w.off[1] + o * kW + 16 * it + lc, g1[a][it][i]);
+                atomicAdd(dW + w.off[2] + o * kW + 16 * it + lc, g2[a][it][i]);
+                atomicAdd(dW + w.off[3] + o * kW + 16 * it + lc, g3[a][it][i]);
+            }
+        }
+    if (bhalf == 0) {
+        atomicAdd(dW + w.off[0] + kW * kF + brow, db0);
+        atomicAdd(dW + w.off[1] + kW * kW + brow, db1);
+        atomicAdd(dW + w.off[2] + kW * kW + brow, db2);
+        atomicAdd(dW + w.off[3] + kW * kW + brow, db3);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = 4 * lg + i;
+            if (j < 3) atomicAdd(dW + w.off[4] + j * kW + 16 * (wv + 4 * q) + lc, g4[q][i]);
+        }
+    if (wv == 0 && lane < 6 && bhalf == 0) atomicAdd(dW + w.off[4] + 3 * kW + (lane >> 1), db5);
+}
+
+// biases and output layer in float, both paths
 __global__ void mlp_prep(const float *__restrict__ flat, MlpDev w) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    for (int l = 0; l < 4; ++l) {
-        const int K = kLayerIn[l];
-        if (i < kW * K) {
-            const int n = i / K, k = i - n * K;
-            const float v = flat[w.off[l] + i];
-            ((T *)w.W[l])[i] = (T)v;
-            ((T *)w.WT[l])[k * kW + n] = (T)v;
-        }
-        if (i < kW) ((float *)w.b[l])[i] = flat[w.off[l] + kW * K + i];
-    }
+    for (int l = 0; l < 4; ++l)
+        if (i < kW) ((float *)w.b[l])[i] = flat[w.off[l] + kW * kLayerIn[l] + i];
     if (i < 3 * kW) ((float *)w.W5)[i] = flat[w.off[4] + i];
     if (i < 3) ((float *)w.b5)[i] = flat[w.off[4] + 3 * kW + i];
 }
 
 size_t mlp_prep_bytes(int precision) {
-    const size_t es = precision == RT_MLP_BF16 ? 2 : 4;
-    size_t n = 0;
-    for (int l = 0; l < 4; ++l) n += 2 * es * (size_t)kW * kLayerIn[l] + 4 * kW;
-    if (precision == RT_MLP_BF16) n += 2 * kRrWeightElems + 256 + 2 * 3 * (size_t)kW * kRrRow + 256;
-    return n + 4 * (3 * kW + 3) + 256 * 8;
+    const size_t hid = precision == RT_MLP_BF16 ? 2 * (kRrWeightElems + 3 * (size_t)kW * kRrRow)
+                                                : 4 * (kFrWeightElems + 3 * (size_t)kW * kFrRow);
+    return hid + 4 * (4 * kW + 3 * kW + 3) + 256 * 8;
 }
 
 hipError_t mlp_prepare(const float *flat, int precision, void *buf, MlpDev *w, hipStream_t st) {
-    const size_t es = precision == RT_MLP_BF16 ? 2 : 4;
     char *p = (char *)buf;
     auto take = [&](size_t b) { char *q = p; p += (b + 255) / 256 * 256; return q; };
     int off = 0;
     for (int l = 0; l < 4; ++l) {
         w->off[l] = off;
         off += kW * kLayerIn[l] + kW;
-        w->W[l] = take(es * kW * kLayerIn[l]);
-        w->WT[l] = take(es * kW * kLayerIn[l]);
         w->b[l] = (const float *)take(4 * kW);
     }
     w->off[4] = off;
     w->W5 = (const float *)take(4 * 3 * kW);
     w->b5 = (const float *)take(4 * 3);
-    w->Wr = precision == RT_MLP_BF16 ? take(2 * kRrWeightElems) : nullptr;
-    w->WrT = precision == RT_MLP_BF16 ? take(2 * 3 * (size_t)kW * kRrRow) : nullptr;
+    const bool bf16 = precision == RT_MLP_BF16;
+    w->Wr = take(bf16 ? 2 * kRrWeightElems : 4 * kFrWeightElems);
+    w->WrT = take(bf16 ? 2 * 3 * (size_t)kW * kRrRow : 4 * 3 * (size_t)kW * kFrRow);
     for (int q = 0; q < 16; ++q) w->freq[q] = (float)std::exp2(3.0 * q / 15.0);
-    const int n = kW * kW;
-    if (precision == RT_MLP_BF16) {
-        hipLaunchKernelGGL(mlp_prep<__bf16>, dim3((n + 255) / 256), dim3(256), 0, st, flat, *w);
-        const int nr = kW * kRrRow;
-        hipLaunchKernelGGL(mlp_prep_rr, dim3((nr + 255) / 256), dim3(256), 0, st, flat, *w);
-    } else
-        hipLaunchKernelGGL(mlp_prep<float>, dim3((n + 255) / 256), dim3(256), 0, st, flat, *w);
+    hipLaunchKernelGGL(mlp_prep, dim3(2), dim3(256), 0, st, flat, *w);
+    const int n = kW * (bf16 ? kRrRow : kFrRow);
+    if (bf16) hipLaunchKernelGGL(mlp_prep_rr, dim3((n + 255) / 256), dim3(256), 0, st, flat, *w);
+    else hipLaunchKernelGGL(mlp_prep_fr, dim3((n + 255) / 256), dim3(256), 0, st, flat, *w);
     return hipGetLastError();
 }
 
 hipError_t mlp_forward(const Geometry &g, const Shade &s, const MlpDev &w, int precision, size_t M, float4 *out,
                        hipStream_t st) {
+    int dev = 0, ncu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
     if (precision == RT_MLP_BF16) {
-        int dev = 0, ncu = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
         constexpr int NP = kRrTiles, NT = kRrThreads;
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)mlp_fwd_rr<NP, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)kRrLds);
+        e = hipFuncSetAttribute((const void *)mlp_fwd_rr<NP, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kRrLds);
         if (e != hipSuccess) return e;
         constexpr size_t pts = NT / 64 * NP * 16;
         const unsigned grid = (unsigned)std::min<size_t>((M + pts - 1) / pts, (size_t)ncu);
         hipLaunchKernelGGL((mlp_fwd_rr<NP, NT>), dim3(grid), dim3(NT), kRrLds, st, g, s, w, M, out);
     } else {
-        constexpr int P = 32;
-        hipLaunchKernelGGL((mlp_fwd<float, P>), dim3((unsigned)((M + P - 1) / P)), dim3(512), 0, st, g, s, w, M, out);
+        constexpr size_t pts = kFrThreads / 64 * kFrTiles * 16;
+        const unsigned grid = (unsigned)std::min<size_t>((M + pts - 1) / pts, (size_t)ncu);
+        hipLaunchKernelGGL(mlp_fwd_fr, dim3(grid), dim3(kFrThreads), 0, st, g, s, w, M, out);
     }
     return hipGetLastError();
 }
 
-size_t mlp_backward_list_bytes(size_t M) { return sizeof(uint32_t) * (1 + M + 3 * (size_t)kLiveChunks); }
+// workgroups of the FP32 backward, each with a slab to park its pre-activations
+static size_t fr_bwd_groups(size_t M) { return std::min<size_t>((M + kBrPts - 1) / kBrPts, 256); }
+
+size_t mlp_backward_list_bytes(size_t M, int precision) {
+    const size_t list = (sizeof(uint32_t) * (1 + M + 3 * (size_t)kLiveChunks) + 255) / 256 * 256;
+    return list + (precision == RT_MLP_BF16 ? 0 : sizeof(floatx4) * kFrSlab * fr_bwd_groups(M));
+}
 
 hipError_t mlp_backward(const Geometry &g, const Shade &s, const MlpDev &w, int precision, size_t M,
                         const float4 *dO, uint32_t *list, float *dW, hipStream_t st) {
@@ -1129,23 +1342,22 @@ hipError_t mlp_backward(const Geometry &g, const Shade &s, const MlpDev &w, int 
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
+    const size_t passes = (M + kBrPts - 1) / kBrPts;
+    // chunks of at least 1024 points, at most kLiveChunks of them
+    const size_t chunk = std::max<size_t>(1024, (M + kLiveChunks - 1) / kLiveChunks);
+    const int nb = (int)((M + chunk - 1) / chunk);
+    uint32_t *counts = list + 1 + M, *offsets = counts + kLiveChunks, *peaks = offsets + kLiveChunks;
+    hipLaunchKernelGGL(mlp_live_max, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks);
+    hipLaunchKernelGGL(mlp_live_count, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks, counts);
+    hipLaunchKernelGGL(mlp_live_scan, dim3(1), dim3(1024), 0, st, counts, nb, offsets, list);
+    hipLaunchKernelGGL(mlp_live_write, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks, offsets, list);
     if (precision == RT_MLP_BF16) {
-        const size_t passes = (M + kBrPts - 1) / kBrPts;
-        // chunks of at least 1024 points, at most kLiveChunks of them
-        const size_t chunk = std::max<size_t>(1024, (M + kLiveChunks - 1) / kLiveChunks);
-        const int nb = (int)((M + chunk - 1) / chunk);
-        uint32_t *counts = list + 1 + M, *offsets = counts + kLiveChunks, *peaks = offsets + kLiveChunks;
-        hipLaunchKernelGGL(mlp_live_max, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks);
-        hipLaunchKernelGGL(mlp_live_count, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks, counts);
-        hipLaunchKernelGGL(mlp_live_scan, dim3(1), dim3(1024), 0, st, counts, nb, offsets, list);
-        hipLaunchKernelGGL(mlp_live_write, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks, offsets, list);
         const unsigned grid = (unsigned)std::min<size_t>(passes, (size_t)ncu);
         hipLaunchKernelGGL(mlp_bwd_rr, dim3(grid), dim3(256), 0, st, g, s, w, M, dO, list, dW);
     } else {
-        constexpr int P = 16;
-        const size_t ntiles = (M + P - 1) / P;
-        const unsigned grid = (unsigned)std::min<size_t>(ntiles, (size_t)ncu);
-        hipLaunchKernelGGL((mlp_bwd<float, P>), dim3(grid), dim3(512), 0, st, g, s, w, M, dO, dW);
+        const size_t list_b = (sizeof(uint32_t) * (1 + M + 3 * (size_t)kLiveChunks) + 255) / 256 * 256;
+        hipLaunchKernelGGL(mlp_bwd_fr, dim3((unsigned)fr_bwd_groups(M)), dim3(256), 0, st, g, s, w, M, dO, list, dW,
+                           (floatx4 *)((char *)list + list_b));
     }
     return hipGetLastError();
 }

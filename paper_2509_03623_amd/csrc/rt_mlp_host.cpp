@@ -27,7 +27,7 @@ static rt_status mlp_setup(const rt_problem *p, Geometry *geo, Shade *sh, MlpDev
     const size_t prep = (mlp_prep_bytes(prec) + 255) / 256 * 256;
     const size_t ob = sizeof(float4) * M;
     // with the per-point extra (the backward's dL/do) comes the backward's pass list
-    const size_t list_b = extra ? mlp_backward_list_bytes(M) : 0;
+    const size_t list_b = extra ? mlp_backward_list_bytes(M, prec) : 0;
     ws->st = st;
     hipError_t e = hipMallocAsync(&ws->p, prep + ob + extra_point_bytes * M + list_b, st);
     if (e != hipSuccess) { ws->p = nullptr; return fail_hip(e, "network scratch"); }
