@@ -457,11 +457,10 @@ constexpr float kFaintLog2K = -26.0f;
 
 // Bits of the units (u0 ... u0 + NU - 1) that the line of sample q reaches; 0
 // without opacity or when `on` is false.  v0: velocity of
-// the block's first channel (UNIFORM).  NaN in q sets every unit: what a NaN
+// the block's first channel (UNIFORM); win: a Windows or the like.  NaN in q sets every unit: what a NaN
 // sample touches is what it touched without windows.
-template <int NU, int PER, bool UNIFORM>
-__device__ __forceinline__ unsigned unit_mask(const SampleQ &q, float lK, bool on, float v0, const Windows &win,
-                                              int u0) {
+template <int NU, int PER, bool UNIFORM, class Win>
+__device__ __forceinline__ unsigned unit_mask(const SampleQ &q, float lK, bool on, float v0, const Win &win, int u0) {
     const float ib = frcp(q.b);
     // at least sqrt(127 + lK): two tangents
     const float R = fminf(fmaf(lK, 0.04623f, 11.279f), fmaf(lK, 0.08839f, 14.0547f));

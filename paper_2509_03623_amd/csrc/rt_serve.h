@@ -7,19 +7,23 @@
 namespace rt {
 
 // workgroups (256 lanes each) per compute unit of the persistent forward
-// launch; an item covers kServeTile x kServeTile pixels with kServeSplit
-// lanes per pixel
+// launch; an item covers kServeTile x kServeTile pixels and a block of
+// kServeBlock channels, four lanes per pixel
 constexpr int kServeWorkgroupsPerCU = 4;
-constexpr int kServeTile = 8;
+constexpr int kServeTile = 4;
+constexpr int kServeCB = 8;
+constexpr int kServeBlock = kServeCB * kLanesPerPixel;
+// lanes per pixel and 16 channels that the routing rule counts for a request
 constexpr int kServeSplit = 4;
 
 // One request of a persistent forward batch.
 struct ServeDesc {
     Geometry g;
     Shade s;
-    const float *vch;     // channel velocities, padded to a multiple of 16
+    const float *vch;     // channel velocities, padded to a multiple of kServeBlock
     float *cube;          // [nch][ny][nx]
-    int32_t nch, nblk, tiles_x;   // channel blocks of 16, item tiles across
+    int32_t nch, nblk, tiles_x;   // channel blocks of kServeBlock, item tiles across
+    float inv_unit;       // 1 / (velocity span of a unit) of evenly spaced channels, 0: not
     uint32_t item0;       // first work item of this request in the batch
     const float *target;  // L = sum (cube - target)^2 into *loss (NULL: no loss)
     double *loss;

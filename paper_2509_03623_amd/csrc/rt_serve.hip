@@ -2,25 +2,119 @@
 // launch over the work items of every request in a batch, and the fused L2
 // loss / cotangent of forward+adjoint requests.
 //
-// A batch holds up to max_slots requests; its work items are (request,
-// 8 x 8 pixel tile, 16-channel block) in request order.  The four adjacent
-// lanes of a pixel march consecutive quarters of its ray and compose them by
-// shuffles at the end (front-to-back composition is associative), so an
-// item's latency is a quarter of its ray.  The launch has a fixed number of
-// workgroups; each pulls the next item index from a device counter until the
-// batch is exhausted, so items of small and large requests of the batch share
-// the GPU.  Every wave exits once the counter passes the item count.
+// A batch holds up to max_slots requests; its work items are (request, 4 x 4
+// pixel tile, 32-channel block) in request order.  An item is the windowed
+// march of rt_forward.hip on one tile: the workgroup's four waves take
+// consecutive quarters of the samples that can lie below the top taper, and
+// the first composes the quarters front to back through LDS (the composition
+// is associative), so an item's latency is a quarter of its rays'.  The launch
+// has a fixed number of workgroups; each pulls the next item index from a
+// device counter until the batch is exhausted, so items of small and large
+// requests of the batch share the GPU.  Every wave exits once the counter
+// passes the item count.
+//
+// Bound: VALU issue, as the forward march.  60 walkers at 128^2 x 32 x 256:
+// 875 -> 295 us a launch (of about ten that overlap).  With blocks of 64
+// channels (152 VGPRs, three waves per SIMD) an iteration took 4.9 ms against
+// 4.2, and 64-channel requests no less.
+#include <type_traits>
+
 #include "rt_host.h"
 #include "rt_serve.h"
 
 namespace rt {
 
-constexpr int kServeCB = 16;
-static_assert(kServeTile * kServeTile * kServeSplit == 256, "one item per 256-lane workgroup");
+static_assert(kServeTile * kServeTile * kLanesPerPixel == 64, "one tile per wave");
+
+// the unit ranges of a block in LDS (unevenly spaced channels)
+struct ServeWindows {
+    float lo[kServeCB], hi[kServeCB];
+    float inv_unit;
+};
+
+template <bool UNIFORM>
+__device__ __forceinline__ void serve_item(const ServeDesc &D, const float4 *ztab, const ServeWindows &win, int blk,
+                                           int tile, float *parts) {
+    constexpr int CB = kServeCB, G = kLanesPerPixel;
+    const Geometry &g = D.g;
+    const int split = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, h = lane & 3, slot = lane >> 2;
+    const int p = (tile % D.tiles_x) * kServeTile + (slot & 3), q = (tile / D.tiles_x) * kServeTile + (slot >> 2);
+    const int c0 = blk * kServeBlock;
+    const bool inside = p < g.nx && q < g.ny;
+    const RaySetup r = ray_setup(g, inside ? p : 0, inside ? q : 0);
+    const bool live = inside && r.live;
+    float I[CB], Tr[CB], vc[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        I[c] = 0.0f;
+        Tr[c] = 1.0f;
+        vc[c] = D.vch[c0 + c * G + h];
+    }
+    if (__ballot(live) != 0) {
+        const float half = 0.5f * (float)g.nsamp;
+        const float v0 = D.vch[c0];
+        const int2 own_range = live ? taper_range(g, D.s, r) : make_int2(g.nsamp, -1);
+        const int kf = wave_min(own_range.x), kn = max(wave_max(own_range.y) + 1 - kf, 0);
+        const int len = ((kn + 3) / 4 + G - 1) / G * G;
+        const int k1 = kf + min(kn, (split + 1) * len);
+        for (int k = kf + split * len; k < k1; k += G) {
+            const int kk = min(k + h, k1 - 1);
+            const float t = ((float)kk + 0.5f - half) * r.ds;
+            const SampleQ own = shade_sample<false>(D.s, ztab, r.px, fmaf(t, r.wy, r.pmy), fmaf(t, r.wz, r.pmz), r.ds, 0);
+            const float own_lk = flog2(own.K);
+            const unsigned mask =
+                or_over_pixels(unit_mask<CB, G, UNIFORM>(own, own_lk, live && k + h < k1, v0, win, 0));
+            const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < kFaintLog2K));
+            const unsigned long long thick = __builtin_amdgcn_ballot_w64(!(own_lk < kThinLog2K));
+            auto step = [&](auto jc) {
+                constexpr int J = decltype(jc)::value;
+                constexpr unsigned long long mine = 0x1111111111111111ull << J;
+                const unsigned m = (unsigned)__builtin_amdgcn_readlane((int)mask, J);
+                if (m == 0) return;
+                const float S = group_lane<G, J>(own.S), lK = group_lane<G, J>(own_lk);
+                const float a = group_lane<G, J>(own.a), b = group_lane<G, J>(own.b);
+                march_units<CB>(I, Tr, S, lK, m, (bright & mine) != 0, (thick & mine) != 0,
+                                [&](int c) { return fmaf(-vc[c], b, a); });
+            };
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
+        }
+    }
+    if (split > 0) {
+        float *o = parts + (size_t)(split - 1) * (2 * CB * 64) + lane;
+#pragma unroll
+        for (int c = 0; c < CB; ++c) {
+            o[c * 64] = I[c];
+            o[(CB + c) * 64] = Tr[c];
+        }
+    }
+    __syncthreads();
+    if (split == 0) {
+        for (int j = 0; j < 3; ++j) {
+            const float *o = parts + (size_t)j * (2 * CB * 64) + lane;
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                I[c] = fmaf(Tr[c], o[c * 64], I[c]);
+                Tr[c] *= o[(CB + c) * 64];
+            }
+        }
+        if (inside) {
+            const size_t plane = (size_t)g.nx * g.ny, pix = (size_t)q * g.nx + p;
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                if (c0 + c * G + h < D.nch) D.cube[(size_t)(c0 + c * G + h) * plane + pix] = I[c];
+        }
+    }
+}
 
 __global__ __launch_bounds__(256) void serve_fwd(const ServeDesc *__restrict__ descs, int nreq, uint32_t nitems,
                                                  uint32_t *__restrict__ counter) {
     __shared__ float4 ztab[kZTableNodes - 1];
+    __shared__ float parts[3 * 2 * kServeCB * 64];
+    __shared__ ServeWindows win;
     __shared__ uint32_t s_item;
     __shared__ const float4 *s_tab;
     if (threadIdx.x == 0) s_tab = nullptr;
@@ -39,59 +133,34 @@ __global__ __launch_bounds__(256) void serve_fwd(const ServeDesc *__restrict__ d
         // the request index is the same for every lane: keep its descriptor in
         // scalar registers for the whole item
         const ServeDesc D = descs[__builtin_amdgcn_readfirstlane(lo)];
-        if (s_tab != D.s.ztab) {     // uniform: every lane reads the same s_tab
-            __syncthreads();
-            for (int i = threadIdx.x; i < kZTableNodes - 1; i += 256) ztab[i] = D.s.ztab[i];
-            __syncthreads();
-            if (threadIdx.x == 0) s_tab = D.s.ztab;
-        }
         const uint32_t local = item - D.item0;
         const int blk = (int)(local % (uint32_t)D.nblk);
         const int tile = (int)(local / (uint32_t)D.nblk);
-        const Geometry &g = D.g;
-        const int split = threadIdx.x % kServeSplit, slot = threadIdx.x / kServeSplit;
-        const int p = (tile % D.tiles_x) * kServeTile + slot % kServeTile;
-        const int q = (tile / D.tiles_x) * kServeTile + slot / kServeTile;
-        const int c0 = blk * kServeCB;
-        const bool inside = p < g.nx && q < g.ny;
-        float I[kServeCB], Tr[kServeCB];
-#pragma unroll
-        for (int c = 0; c < kServeCB; ++c) { I[c] = 0.0f; Tr[c] = 1.0f; }
-        float vc[kServeCB];
-#pragma unroll
-        for (int c = 0; c < kServeCB; ++c) vc[c] = D.vch[c0 + c];
-        const RaySetup r = ray_setup(g, inside ? p : 0, inside ? q : 0);
-        if (inside && r.live) {
-            const float half = 0.5f * (float)g.nsamp;
-            const int len = (g.nsamp + kServeSplit - 1) / kServeSplit;
-            const int k0 = split * len, k1 = min(g.nsamp, k0 + len);
-            for (int k = k0; k < k1; ++k) {
-                const float t = ((float)k + 0.5f - half) * r.ds;
-                const SampleQ sq = shade_sample<false>(D.s, ztab, r.px, fmaf(t, r.wy, r.pmy),
-                                                       fmaf(t, r.wz, r.pmz), r.ds, 0);
-                // no ray of the wave with opacity at this sample: no channel changes
-                if (__ballot(sq.K > 0.0f) == 0) continue;
-                march_sample<kServeCB, true>(I, Tr, sq, [&](int c) { return vc[c]; });
-            }
-        }
-        // compose the quarters front to back (every lane takes part in the shuffles)
-#pragma unroll
-        for (int d = 1; d < kServeSplit; d <<= 1) {
-#pragma unroll
-            for (int c = 0; c < kServeCB; ++c) {
-                const float Ib = __shfl_down(I[c], d, kServeSplit);
-                const float Tb = __shfl_down(Tr[c], d, kServeSplit);
-                if ((split & (2 * d - 1)) == 0) {
-                    I[c] = fmaf(Tr[c], Ib, I[c]);
-                    Tr[c] *= Tb;
+        const bool new_tab = s_tab != D.s.ztab;     // uniform: every lane reads the same s_tab
+        const bool uniform = D.inv_unit != 0.0f;
+        if (new_tab || !uniform) {
+            __syncthreads();
+            if (new_tab)
+                for (int i = threadIdx.x; i < kZTableNodes - 1; i += 256) ztab[i] = D.s.ztab[i];
+            if (threadIdx.x < kServeCB) {
+                const int c = blk * kServeBlock + threadIdx.x * kLanesPerPixel;
+                float a = __builtin_huge_valf(), b = -a;
+                for (int j = c; j < min(c + kLanesPerPixel, D.nch); ++j) {
+                    a = fminf(a, D.vch[j]);
+                    b = fmaxf(b, D.vch[j]);
                 }
+                win.lo[threadIdx.x] = a;
+                win.hi[threadIdx.x] = b;
             }
+            __syncthreads();
+            if (threadIdx.x == 0) s_tab = D.s.ztab;
         }
-        if (inside && split == 0) {
-            const size_t plane = (size_t)g.nx * g.ny, pix = (size_t)q * g.nx + p;
-#pragma unroll
-            for (int c = 0; c < kServeCB; ++c)
-                if (c0 + c < D.nch) D.cube[(size_t)(c0 + c) * plane + pix] = I[c];
+        if (uniform) {
+            ServeWindows w;
+            w.inv_unit = D.inv_unit;
+            serve_item<true>(D, ztab, w, blk, tile, parts);
+        } else {
+            serve_item<false>(D, ztab, win, blk, tile, parts);
         }
     }
 }

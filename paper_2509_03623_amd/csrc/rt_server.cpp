@@ -181,7 +181,7 @@ rt_status lane_vch_capacity(Lane &L, size_t n) {
 // one persistent launch over every request of the batch
 rt_status launch_batch(rt_server *sv, Lane &L, std::vector<Req *> &batch) {
     size_t nv = 0;
-    for (Req *r : batch) nv += (size_t)(r->rq.problem.spec.nch + 15) / 16 * 16;
+    for (Req *r : batch) nv += (size_t)(r->rq.problem.spec.nch + kServeBlock - 1) / kServeBlock * kServeBlock;
     rt_status rs = lane_vch_capacity(L, nv);
     if (rs != RT_OK) return rs;
     uint32_t items = 0;
@@ -193,13 +193,15 @@ rt_status launch_batch(rt_server *sv, Lane &L, std::vector<Req *> &batch) {
         std::memset(&D, 0, sizeof D);
         rs = build_launch(&p, &D.g, &D.s);
         if (rs != RT_OK) return rs;
-        const int nch = p.spec.nch, padded = (nch + 15) / 16 * 16;
+        const int nch = p.spec.nch, padded = (nch + kServeBlock - 1) / kServeBlock * kServeBlock;
         for (int c = 0; c < padded; ++c) L.h_vch[vo + c] = c < nch ? (float)p.spec.v_kms[c] : 0.0f;
         D.vch = L.d_vch + vo;
         vo += padded;
+        double dv = 0.0;
+        D.inv_unit = uniform_spacing(p.spec.v_kms, nch, &dv) && dv != 0.0 ? (float)(1.0 / (kLanesPerPixel * dv)) : 0.0f;
         D.cube = batch[i]->rq.cube;
         D.nch = nch;
-        D.nblk = padded / 16;
+        D.nblk = padded / kServeBlock;
         D.tiles_x = (p.cam.nx + kServeTile - 1) / kServeTile;
         D.item0 = items;
         if (batch[i]->rq.kind == RT_REQ_FWD_LOSS) {

@@ -98,6 +98,33 @@ def test_nan_field_reaches_every_channel(field, nch):
     assert bad.any(0).sum() >= plain.any(0).sum() // 2
 
 
+@pytest.mark.parametrize("order", ["", "falling", "uneven"])
+def test_served_blocks(order):
+    """Requests at the ends of the server's 32-channel blocks and 4 x 4 tiles,
+    in one batch, each against the oracle."""
+    import paper_2509_03623_amd as rt
+    probs = []
+    for i, (nx, ny, nch, nsamp) in enumerate([(4, 4, 1, 1), (5, 3, 31, 7), (8, 9, 32, 33), (17, 12, 33, 64),
+                                              (20, 20, 64, 50), (12, 11, 65, 101)]):
+        prob = synth.small_problem(nx=nx, ny=ny, nch=nch, nsamp=nsamp, nr=40, nz=20, seed=40 + i, dv=6.0 / nch,
+                                   incl=30.0 + 9 * i)
+        if order:
+            v = prob.v_kms[::-1].copy() if order == "falling" else prob.v_kms + 0.02 * np.sin(np.arange(nch) * 1.7)
+            prob = prob.replace(v_kms=v)
+        probs.append(prob)
+    scenes = [rt.scene_from_problem(p) for p in probs]
+    cubes = [torch.full((s.nch, s.ny, s.nx), float("nan"), device="cuda") for s in scenes]
+    torch.cuda.synchronize()
+    print(f"[gpu] served blocks {order}", flush=True)
+    with rt.Server(max_slots=8, streams=2) as sv:
+        tickets = [sv.submit(s, c) for s, c in zip(scenes, cubes)]
+        assert all(sv.wait(t)["state"] == "done" for t in tickets)
+    torch.cuda.synchronize()
+    for p, c in zip(probs, cubes):
+        ref = oracle.render(p)
+        assert np.abs(c.cpu().numpy().astype(np.float64) - ref).max() <= TOL * ref.max()
+
+
 @pytest.mark.parametrize("nx,ny,nch,order", [(7, 5, 1, ""), (9, 7, 16, ""), (13, 9, 17, "falling"), (11, 11, 32, ""),
                                              (11, 11, 33, "uneven"), (14, 13, 64, ""), (10, 9, 65, "uneven"),
                                              (180, 183, 35, "")])
