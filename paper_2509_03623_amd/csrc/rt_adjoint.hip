@@ -30,9 +30,11 @@
 //   pixel-sample inside its ray's span that has a cotangent has its shading
 //   recomputed with its local derivatives, the cotangents chained to the
 //   interpolated fields and added to the grid nodes (one field per pass
-//   privatised in LDS and flushed once, the T pass from terms the first pass
+//   privatised in LDS, the most visited rows as doubles, and flushed once, the T pass from terms the first pass
 //   stored when ln n and T are asked for; adj_chain scatters with global
 //   atomics; the surface vectors in LDS either way).
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "rt_adjoint.h"
@@ -297,18 +299,78 @@ __global__ __launch_bounds__(256) void adj_chain(Geometry g, Shade s, const floa
 // lanes per workgroup of the privatised chain pass: one workgroup fills a CU's
 // LDS, so it brings sixteen waves to keep the CU busy
 constexpr int kChainThreads = 1024;
-// pixel rotation from one sample plane to the next in the chain pass (an odd
-// number of workgroup spans)
-constexpr int kChainTurn = 37 * kChainThreads;
+
+// The (sample plane, run of 1024 pixels) items of a workgroup of the chain
+// passes, dealt round robin, the runs of plane k turned by 37 k: a workgroup
+// sees every depth along the rays and does not keep the same rays (the disk's
+// centre or the empty corners) for every plane.  Stepped, not divided: two
+// 64-bit divisions per lane and item cost as much as the shading.
+struct ChainItems {
+    int runs, k, c, dk, dc;
+    __device__ __forceinline__ ChainItems(int npix) {
+        runs = (npix + kChainThreads - 1) / kChainThreads;
+        k = (int)(blockIdx.x / (unsigned)runs);
+        c = (int)(blockIdx.x % (unsigned)runs);
+        dk = (int)(gridDim.x / (unsigned)runs);
+        dc = (int)(gridDim.x % (unsigned)runs);
+    }
+    __device__ __forceinline__ int pixel() const {
+        return (int)(((unsigned)c + (unsigned)k % (unsigned)runs * 37u) % (unsigned)runs) * kChainThreads +
+               (int)threadIdx.x;
+    }
+    __device__ __forceinline__ void next() {
+        k += dk;
+        c += dc;
+        if (c >= runs) { c -= runs; ++k; }
+    }
+};
+
+// One field of the grid in LDS.  A float add to LDS takes the CU three cycles
+// a lane whatever the addresses (about 200 a wave, 260 where sixteen lanes
+// share one), a double add 28 a wave at scattered addresses, 61 with four lanes
+// on one, 195 with sixteen (random and grouped adds into 128 KB, all CUs; both
+// passes were bound by their float adds: 512^2 x 64 x 512 1.58 -> 0.93 ms and
+// 0.81 -> 0.50 ms).  So as many rows as fit hold doubles: win rows
+// from w0 on, the most visited ones, the others floats.  256 x 128 nodes leave
+// room for about 40 rows of doubles, which take most of the samples of a whole
+// disk; 128 x 64 fit whole.
+struct FieldLds {
+    double *d;     // [win][nz]
+    float *f;      // [nr - win][nz]: rows below w0, then rows from w0 + win on
+    int nr, nz, w0, win;
+    __device__ __forceinline__ void clear() const {
+        for (int i = threadIdx.x; i < win * nz; i += kChainThreads) d[i] = 0.0;
+        for (int i = threadIdx.x; i < (nr - win) * nz; i += kChainThreads) f[i] = 0.0f;
+    }
+    // a and b to nodes j and j + 1 of row i
+    __device__ __forceinline__ void add(int i, int j, float a, float b) const {
+        const int r = i - w0;
+        if ((unsigned)r < (unsigned)win) {
+            unsafeAtomicAdd(d + r * nz + j, (double)a);
+            unsafeAtomicAdd(d + r * nz + j + 1, (double)b);
+        } else {
+            float *p = f + (r < 0 ? i : i - win) * nz + j;
+            atomicAdd(p, a);
+            atomicAdd(p + 1, b);
+        }
+    }
+    __device__ __forceinline__ void scatter(int i0, int j0, float g, float fu, float fv) const {
+        add(i0, j0, g * (1.0f - fu) * (1.0f - fv), g * (1.0f - fu) * fv);
+        add(i0 + 1, j0, g * fu * (1.0f - fv), g * fu * fv);
+    }
+    template <typename A> __device__ __forceinline__ void flush(A *dst) const {
+        for (int i = threadIdx.x; i < win * nz; i += kChainThreads)
+            if (d[i] != 0.0) atomicAdd(dst + w0 * nz + i, (A)d[i]);
+        for (int i = threadIdx.x; i < (nr - win) * nz; i += kChainThreads)
+            if (f[i] != 0.0f) atomicAdd(dst + i + (i >= w0 * nz ? win * nz : 0), (A)f[i]);
+    }
+};
 
 // Chain pass with the gradient of one field privatised in LDS.  Persistent
-// workgroups take runs of 1024 consecutive pixel-samples in grid-stride
-// order, so every workgroup sees every depth along the rays (with one
-// contiguous share each, the few whose samples crossed the disk did the work
-// while those beyond it, where the cotangents vanish, sat idle), accumulate
-// field FIELD (0 ln n, 1 T, 2 v_phi, 3 none) over the whole grid in LDS
-// (float), and flush it once with atomics into the accumulators of type A;
-// the FIRST pass also accumulates the two surface vectors (LDS, float) and
+// workgroups take their items (ChainItems), accumulate
+// field FIELD (0 ln n, 1 T, 2 v_phi, 3 none) over the whole grid in LDS, and
+// flush it once with atomics into the accumulators of type A;
+// the FIRST pass also accumulates the two surface vectors (LDS, double) and
 // writes dL/do.
 // With STORE (the first pass, FIELD 0) each sample inside a ray's run also
 // leaves the temperature term of its chain in slice 0 of the cotangents,
@@ -319,28 +381,23 @@ constexpr int kChainTurn = 37 * kChainThreads;
 template <int FIELD, bool FIRST, typename A, bool STORE = false>
 __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade s, const float4 *__restrict__ rays,
                                                      const int2 *__restrict__ span, float4 *__restrict__ cot,
-                                                     int nblk, GradAcc go, float4 *__restrict__ dO) {
-    extern __shared__ float dyn[];               // [2 nr] surfaces (FIRST), then [nr nz] field
+                                                     int nblk, GradAcc go, float4 *__restrict__ dO, int w0,
+                                                     int win) {
+    // [2 nr] surfaces (FIRST), then the field's doubles and floats
+    extern __shared__ double dyn[];
     __shared__ float4 ztab[kZTableNodes - 1];
-    const int nr = s.nr, nn = s.nr * s.nz;
-    float *surf = dyn;
-    float *field = dyn + (FIRST ? 2 * nr : 0);
+    const int nr = s.nr;
+    double *surf = dyn;
+    double *fd = dyn + (FIRST ? 2 * nr : 0);
+    const FieldLds field{fd, (float *)(fd + (FIELD < 3 ? win * s.nz : 0)), nr, s.nz, w0, win};
     for (int i = threadIdx.x; i < kZTableNodes - 1; i += kChainThreads) ztab[i] = s.ztab[i];
-    if (FIELD < 3) for (int i = threadIdx.x; i < nn; i += kChainThreads) field[i] = 0.0f;
-    if (FIRST) for (int i = threadIdx.x; i < 2 * nr; i += kChainThreads) surf[i] = 0.0f;
+    if (FIELD < 3) field.clear();
+    if (FIRST) for (int i = threadIdx.x; i < 2 * nr; i += kChainThreads) surf[i] = 0.0;
     __syncthreads();
     const int npix = g.nx * g.ny;
-    const size_t total = (size_t)g.nsamp * npix;
-    // sample plane k is visited with its pixels rotated by k kChainTurn: a
-    // lane's pixel moves across the image from one plane to the next, so no
-    // workgroup keeps the same rays (the disk's centre or the empty corners)
-    // for every sample when the grid stride is a multiple of the image
-    const int turn = (int)((size_t)kChainTurn % (size_t)npix);
-    for (size_t idx = (size_t)blockIdx.x * kChainThreads + threadIdx.x; idx < total;
-         idx += (size_t)gridDim.x * kChainThreads) {
-        const int k = (int)(idx / npix);
-        int pix = (int)(idx - (size_t)k * npix) + (int)(((long)k * turn) % npix);
-        if (pix >= npix) pix -= npix;
+    for (ChainItems it(npix); it.k < g.nsamp; it.next()) {
+        const int k = it.k, pix = it.pixel();
+        if (pix >= npix) continue;
         // samples outside the ray's run of K > 0 have no cotangents (the
         // march leaves them unwritten)
         const int2 ks = span_of(span[pix], g.nsamp);
@@ -397,18 +454,18 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
             }
             if (FIELD == 2) gv = ga * q.b * tp.vfac;
             const float fu = L.fu, fv = L.fv;
-            if (FIELD < 3 && gv != 0.0f) {
-                const int n00 = L.i0 * s.nz + L.j0, n10 = n00 + s.nz;
-                atomicAdd(field + n00, gv * (1.0f - fu) * (1.0f - fv));
-                atomicAdd(field + n00 + 1, gv * (1.0f - fu) * fv);
-                atomicAdd(field + n10, gv * fu * (1.0f - fv));
-                atomicAdd(field + n10 + 1, gv * fu * fv);
-            }
+            if (FIELD < 3 && gv != 0.0f) field.scatter(L.i0, L.j0, gv, fu, fv);
             if (FIRST && !s.mlp_o) {
                 const float gzu = gKK * tp.sa * tp.iw * kLn2;
                 const float gzl = -gKK * tp.sb * tp.iw * kLn2;
-                if (gzl != 0.0f) { atomicAdd(surf + L.i0, gzl * (1.0f - fu)); atomicAdd(surf + L.i0 + 1, gzl * fu); }
-                if (gzu != 0.0f) { atomicAdd(surf + nr + L.i0, gzu * (1.0f - fu)); atomicAdd(surf + nr + L.i0 + 1, gzu * fu); }
+                if (go.zlo && gzl != 0.0f) {
+                    unsafeAtomicAdd(surf + L.i0, (double)(gzl * (1.0f - fu)));
+                    unsafeAtomicAdd(surf + L.i0 + 1, (double)(gzl * fu));
+                }
+                if (go.zup && gzu != 0.0f) {
+                    unsafeAtomicAdd(surf + nr + L.i0, (double)(gzu * (1.0f - fu)));
+                    unsafeAtomicAdd(surf + nr + L.i0 + 1, (double)(gzu * fu));
+                }
             }
         }
         if (FIRST && dO) dO[o_index(s, k, pix)] = dout;
@@ -416,13 +473,11 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
     }
     __syncthreads();
     A *dst = (A *)(FIELD == 0 ? go.ln_n : (FIELD == 1 ? go.temp : (FIELD == 2 ? go.vphi : nullptr)));
-    if (FIELD < 3 && dst)
-        for (int i = threadIdx.x; i < nn; i += kChainThreads)
-            if (field[i] != 0.0f) atomicAdd(dst + i, (A)field[i]);
+    if (FIELD < 3 && dst) field.flush(dst);
     if (FIRST)
         for (int i = threadIdx.x; i < nr; i += kChainThreads) {
-            if (go.zlo && surf[i] != 0.0f) atomicAdd((A *)go.zlo + i, (A)surf[i]);
-            if (go.zup && surf[nr + i] != 0.0f) atomicAdd((A *)go.zup + i, (A)surf[nr + i]);
+            if (go.zlo && surf[i] != 0.0) atomicAdd((A *)go.zlo + i, (A)surf[i]);
+            if (go.zup && surf[nr + i] != 0.0) atomicAdd((A *)go.zup + i, (A)surf[nr + i]);
         }
 }
 
@@ -431,47 +486,26 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
 // LDS and one flush, in the first pass's order of the samples.
 template <typename A>
 __global__ __launch_bounds__(kChainThreads) void adj_chain_lds_stored(Geometry g, Shade s, const int2 *__restrict__ span,
-                                                             const float4 *__restrict__ cot, GradAcc go) {
-    extern __shared__ float field[];   // [nr nz]
-    const int nn = s.nr * s.nz;
-    for (int i = threadIdx.x; i < nn; i += kChainThreads) field[i] = 0.0f;
+                                                             const float4 *__restrict__ cot, GradAcc go, int w0,
+                                                             int win) {
+    extern __shared__ double dyn[];
+    const FieldLds field{dyn, (float *)(dyn + win * s.nz), s.nr, s.nz, w0, win};
+    field.clear();
     __syncthreads();
     const int npix = g.nx * g.ny;
-    const size_t total = (size_t)g.nsamp * npix;
-    const int turn = (int)((size_t)kChainTurn % (size_t)npix);
-    for (size_t idx = (size_t)blockIdx.x * kChainThreads + threadIdx.x; idx < total;
-         idx += (size_t)gridDim.x * kChainThreads) {
-        const int k = (int)(idx / npix);
-        int pix = (int)(idx - (size_t)k * npix) + (int)(((long)k * turn) % npix);
-        if (pix >= npix) pix -= npix;
+    for (ChainItems it(npix); it.k < g.nsamp; it.next()) {
+        const int k = it.k, pix = it.pixel();
+        if (pix >= npix) continue;
         const int2 ks = span_of(span[pix], g.nsamp);
         if (k < ks.x || k > ks.y) continue;
         const float4 t = cot[(size_t)k * npix + pix];
-        const float gv = t.x;
-        if (gv != 0.0f) {
-            const int n00 = __float_as_int(t.y), n10 = n00 + s.nz;
-            const float fu = t.z, fv = t.w;
-            atomicAdd(field + n00, gv * (1.0f - fu) * (1.0f - fv));
-            atomicAdd(field + n00 + 1, gv * (1.0f - fu) * fv);
-            atomicAdd(field + n10, gv * fu * (1.0f - fv));
-            atomicAdd(field + n10 + 1, gv * fu * fv);
+        if (t.x != 0.0f) {
+            const unsigned n00 = __float_as_uint(t.y), i0 = n00 / (unsigned)s.nz;
+            field.scatter((int)i0, (int)(n00 - i0 * (unsigned)s.nz), t.x, t.z, t.w);
         }
     }
     __syncthreads();
-    A *dst = (A *)go.temp;
-    for (int i = threadIdx.x; i < nn; i += kChainThreads)
-        if (field[i] != 0.0f) atomicAdd(dst + i, (A)field[i]);
-}
-
-template <int FIELD, bool FIRST, typename A, bool STORE = false>
-static hipError_t launch_chain_lds_t(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, float4 *cot,
-                                     int nblk, const GradAcc &go, float4 *dO, int nwg, size_t shmem, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute((const void *)adj_chain_lds<FIELD, FIRST, A, STORE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((adj_chain_lds<FIELD, FIRST, A, STORE>), dim3(nwg), dim3(kChainThreads), shmem, st, g, s, rays,
-                       span, cot, nblk, go, dO);
-    return hipGetLastError();
+    field.flush((A *)go.temp);
 }
 
 // largest dynamic LDS the privatised chain may use (the LDS of a CU, less
@@ -479,41 +513,70 @@ static hipError_t launch_chain_lds_t(const Geometry &g, const Shade &s, const fl
 constexpr size_t kChainLdsMax = 160 * 1024 - sizeof(float4) * (kZTableNodes - 1) - 1024;
 
 bool chain_lds_fits(int nr, int nz) {
-    return (size_t)nr * nz * sizeof(float) + 2 * (size_t)nr * sizeof(float) <= kChainLdsMax;
+    return (size_t)nr * nz * sizeof(float) + 2 * (size_t)nr * sizeof(double) <= kChainLdsMax;
+}
+
+// Rows of doubles in `bytes` of LDS: as many as fit, below the radius that the
+// image's corner sees in the midplane (whole disks: the outermost; samples per
+// row grow with its area).
+static void chain_window(const Geometry &g, const Shade &s, size_t bytes, int *w0, int *win) {
+    const size_t row = sizeof(float) * (size_t)s.nz, all = row * s.nr;
+    *win = (int)std::min<size_t>((size_t)s.nr, bytes > all ? (bytes - all) / row : 0);
+    const double half = 0.5 * g.d_pix * std::hypot(2.0 * g.xc, 2.0 * g.xc);
+    const double rho = half / std::max(0.1f, g.ci);
+    const double top = (std::log2(rho) - s.log2_rmin) * s.u_scale + 2.0;
+    *w0 = std::max(0, (int)std::min<double>(s.nr, std::max(0.0, top)) - *win);
+}
+
+template <int FIELD, bool FIRST, typename A, bool STORE = false>
+static hipError_t launch_chain_lds_t(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, float4 *cot,
+                                     int nblk, const GradAcc &go, float4 *dO, int nwg, hipStream_t st) {
+    const size_t sb = FIRST ? 2 * (size_t)s.nr * sizeof(double) : 0;
+    int w0 = 0, win = 0;
+    if (FIELD < 3) chain_window(g, s, kChainLdsMax - sb, &w0, &win);
+    const size_t fb = FIELD < 3 ? sizeof(float) * (size_t)s.nz * (s.nr + win) : 0;
+    hipError_t e = hipFuncSetAttribute((const void *)adj_chain_lds<FIELD, FIRST, A, STORE>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)(fb + sb));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((adj_chain_lds<FIELD, FIRST, A, STORE>), dim3(nwg), dim3(kChainThreads), fb + sb, st, g, s, rays,
+                       span, cot, nblk, go, dO, w0, win);
+    return hipGetLastError();
 }
 
 template <typename A>
 static hipError_t chain_lds_passes(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span,
                                    float4 *cot, int nblk, const GradAcc &go, float4 *dO, int nwg, hipStream_t st) {
-    const size_t fb = (size_t)s.nr * s.nz * sizeof(float), sb = 2 * (size_t)s.nr * sizeof(float);
     const bool want[3] = {go.ln_n != nullptr, go.temp != nullptr, go.vphi != nullptr};
     if (want[0] && want[1] && !want[2]) {
         // ln n and T: the first pass leaves the T terms for the second
-        hipError_t e = launch_chain_lds_t<0, true, A, true>(g, s, rays, span, cot, nblk, go, dO, nwg, fb + sb, st);
+        hipError_t e = launch_chain_lds_t<0, true, A, true>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
         if (e != hipSuccess) return e;
+        int w0, win;
+        chain_window(g, s, 160 * 1024 - 1024, &w0, &win);
+        const size_t fb = sizeof(float) * (size_t)s.nz * (s.nr + win);
         e = hipFuncSetAttribute((const void *)adj_chain_lds_stored<A>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)fb);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(adj_chain_lds_stored<A>, dim3(nwg), dim3(kChainThreads), fb, st, g, s, span, cot, go);
+        hipLaunchKernelGGL(adj_chain_lds_stored<A>, dim3(nwg), dim3(kChainThreads), fb, st, g, s, span, cot, go, w0,
+                           win);
         return hipGetLastError();
     }
     bool first = true;
     hipError_t e = hipSuccess;
     for (int f = 0; f < 3; ++f) {
         if (!want[f]) continue;
-        const size_t shmem = fb + (first ? sb : 0);
         if (first) {
-            e = f == 0 ? launch_chain_lds_t<0, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, shmem, st)
-              : f == 1 ? launch_chain_lds_t<1, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, shmem, st)
-                       : launch_chain_lds_t<2, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, shmem, st);
+            e = f == 0 ? launch_chain_lds_t<0, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
+              : f == 1 ? launch_chain_lds_t<1, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
+                       : launch_chain_lds_t<2, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
         } else {
-            e = f == 1 ? launch_chain_lds_t<1, false, A>(g, s, rays, span, cot, nblk, go, dO, nwg, shmem, st)
-                       : launch_chain_lds_t<2, false, A>(g, s, rays, span, cot, nblk, go, dO, nwg, shmem, st);
+            e = f == 1 ? launch_chain_lds_t<1, false, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
+                       : launch_chain_lds_t<2, false, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
         }
         if (e != hipSuccess) return e;
         first = false;
     }
-    if (first) e = launch_chain_lds_t<3, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, sb, st);
+    if (first) e = launch_chain_lds_t<3, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
     return e;
 }
 
@@ -523,8 +586,8 @@ hipError_t launch_adj_chain_lds(const Geometry &g, const Shade &s, const float4 
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const size_t total = (size_t)g.nsamp * g.nx * g.ny;
-    const int nwg = (int)std::min<size_t>((size_t)ncu, (total + kChainThreads - 1) / kChainThreads);
+    const size_t items = (size_t)g.nsamp * (((size_t)g.nx * g.ny + kChainThreads - 1) / kChainThreads);
+    const int nwg = (int)std::min<size_t>((size_t)ncu, items);
     return grad_accum_double() ? chain_lds_passes<double>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
                                : chain_lds_passes<float>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
 }

@@ -152,6 +152,36 @@ def test_reverse_march(nx, ny, nch, order):
     assert np.abs(own.cpu().numpy().astype(np.float64) - ref).max() <= TOL * ref.max()
 
 
+@pytest.mark.parametrize("nr,nz,fov", [(24, 12, None), (256, 128, None), (256, 128, 90.0), (290, 125, None), (300, 128, None),
+                                       (40, 900, None)])
+@pytest.mark.parametrize("double", [0, 1])
+def test_chain_rows(nr, nz, fov, double):
+    """The chain's gradient grid in LDS with all its rows in double (small grids),
+    some (256 x 128: whole disk, and an image of its inner 90 au, where the rows
+    of doubles are others), none (300 x 128), and too large for LDS (scatter to
+    memory), into either kind of accumulator."""
+    import paper_2509_03623_amd as rt
+    import test_gpu_adjoint as ta
+    from oracle import torch_ref
+    from paper_2509_03623_amd import _lib as L
+    kw = dict(fov=fov) if fov else {}
+    prob = ta.kscale(synth.small_problem(nx=16, ny=15, nch=9, nsamp=48, nr=nr, nz=nz, seed=47, dv=0.6, **kw))
+    ref = oracle.render(prob)
+    target = ta.target_for(prob)
+    rt.set_option(L.RT_OPT_GRAD_ACCUM, double)
+    try:
+        vjp, _, _ = ta.gpu_grads(prob, target, cotangent=2.0 * (ref - target))
+        two, _, _ = ta.gpu_grads(prob, target, want=("ln_nh2", "temp_k"), cotangent=2.0 * (ref - target))
+    finally:
+        rt.set_option(L.RT_OPT_GRAD_ACCUM, 0)
+    _, oref = torch_ref.loss_and_grad(prob, target)
+    for k in ta.BLOCKS:
+        if np.abs(oref[k]).max() > 0:
+            ta.check_block(k, vjp[k], oref[k])
+    for k in two:
+        ta.check_block(k, two[k], oref[k])
+
+
 @pytest.mark.parametrize("x_co", [1e-14, 1e-20])
 def test_gradient_at_any_depth(x_co):
     """A scene whose samples are all faint has the gradient of its own scale."""
