@@ -27,7 +27,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
 # leaving uniform regions as they are it needs none (80 VGPRs).
 UNIFORM_REGIONS = ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]
 FILE_FLAGS = {"rt_forward.hip": UNIFORM_REGIONS, "rt_adjoint_win.hip": UNIFORM_REGIONS,
-              "rt_serve.hip": UNIFORM_REGIONS}
+              "rt_serve.hip": UNIFORM_REGIONS, "rt_render3d.hip": UNIFORM_REGIONS}
 
 
 def _compile(src: str, verbose: bool) -> str:

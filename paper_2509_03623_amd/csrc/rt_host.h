@@ -33,7 +33,10 @@ bool uniform_spacing(const double *v, int n, double *dv);
 // the velocity range of each unit of the channels of 4 lanes of cb (dv: their
 // spacing if uniform)
 void unit_windows(const Channels &ch, int cb, double dv, Windows *w);
+// channels per lane and log2 of the ray parts of the windowed marches
+void window_shape(int nch, long npix, int nsamp, int *cb, int *lsplit);
 bool thin_series();
+int forward_group_option();
 int ckpt_segment_option();
 int ray_split_option();
 int channel_block_option();

@@ -193,25 +193,30 @@ __device__ __forceinline__ RaySetup ray_setup(const Geometry &g, int p, int q) {
     return r;
 }
 
-// The samples of a live ray that can lie below the grid's top taper, |z| <
-// zeta rho with zeta one cell above the top z/r row: the others have no
-// opacity (locate's taper is 0).  Below tan i = 1/zeta they are one run, since
-// zeta^2 rho^2 - z^2 is then concave along the ray; the bound is taken 5e-4
-// wider in zeta (float's rounding of the roots is far inside that) and a
+// The samples of a ray that can lie in |z| < zeta rho, the others being beyond
+// the grid's taper, with no opacity.  The ray is (px, pmy + t wy, pmz + t wz)
+// with t = (k + 1/2 - nsamp/2) ds.  Below tan i = 1/zeta they are one run,
+// since zeta^2 rho^2 - z^2 is then concave along the ray; the bound is taken
+// 5e-4 wider in zeta (float's rounding of the roots is far inside that) and a
 // sample wider at each end.  In the test disks it leaves out about a third of
 // the chord through the bounding cylinder.  (first, last), first > last: none.
-__device__ __forceinline__ int2 taper_range(const Geometry &g, const Shade &s, const RaySetup &r) {
-    const float zeta = s.fnz / s.inv_dzr * 1.0005f, z2 = zeta * zeta;
-    const float A = z2 * r.wy * r.wy - r.wz * r.wz;
-    if (!(A < -1e-3f)) return make_int2(0, g.nsamp - 1);
-    const float B = z2 * r.pmy * r.wy - r.pmz * r.wz, C = fmaf(z2, fmaf(r.px, r.px, r.pmy * r.pmy), -r.pmz * r.pmz);
+__device__ __forceinline__ int2 cone_range(float zeta, float px, float pmy, float pmz, float wy, float wz, float ds,
+                                           int nsamp) {
+    const float z2 = zeta * zeta * 1.001f;
+    const float A = z2 * wy * wy - wz * wz;
+    if (!(A < -1e-3f)) return make_int2(0, nsamp - 1);
+    const float B = z2 * pmy * wy - pmz * wz, C = fmaf(z2, fmaf(px, px, pmy * pmy), -pmz * pmz);
     const float disc = fmaf(B, B, -A * C);
-    if (disc <= 0.0f) return make_int2(g.nsamp, -1);
-    const float mid = -B / A, ext = -sqrtf(disc) / A, c = 0.5f * (float)g.nsamp - 0.5f;
-    const float n = (float)g.nsamp;
-    const float lo = fminf(fmaxf((mid - ext) / r.ds + c - 1.0f, 0.0f), n);
-    const float hi = fmaxf(fminf((mid + ext) / r.ds + c + 2.0f, n - 1.0f), -1.0f);
+    if (disc <= 0.0f) return make_int2(nsamp, -1);
+    const float n = (float)nsamp, mid = -B / A, ext = -sqrtf(disc) / A, c = 0.5f * n - 0.5f;
+    const float lo = fminf(fmaxf((mid - ext) / ds + c - 1.0f, 0.0f), n);
+    const float hi = fmaxf(fminf((mid + ext) / ds + c + 2.0f, n - 1.0f), -1.0f);
     return make_int2((int)lo, (int)hi);
+}
+
+// the same for the (r, z/r) grid: zeta one cell above the top z/r row
+__device__ __forceinline__ int2 taper_range(const Geometry &g, const Shade &s, const RaySetup &r) {
+    return cone_range(s.fnz / s.inv_dzr, r.px, r.pmy, r.pmz, r.wy, r.wz, r.ds, g.nsamp);
 }
 
 // Where a sample falls on the grid.
@@ -415,6 +420,17 @@ __device__ __forceinline__ float om_select(float x, float att) { return x < kThi
 template <int G, int J>
 __device__ __forceinline__ float group_lane(float x) {
     constexpr int sel = G == 4 ? J * 0x55 : (J == 0 ? 0xA0 : 0xF5);   // (j,j,j,j) or (j,j,2+j,2+j)
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), sel, 0xF, 0xF, false));
+}
+
+// the same of a quad for an integer, and the value of the lane X apart in the quad
+template <int J>
+__device__ __forceinline__ int group_lane_i(int x) {
+    return __builtin_amdgcn_mov_dpp(x, J * 0x55, 0xF, 0xF, false);
+}
+template <int X>
+__device__ __forceinline__ float quad_xor(float x) {
+    constexpr int sel = X == 1 ? 0xB1 : 0x4E;   // (1,0,3,2) or (2,3,0,1)
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), sel, 0xF, 0xF, false));
 }
 

@@ -18,8 +18,9 @@
 // velocity v . w from the three components and the local unit vectors.  The
 // channel loop, the lanes-per-ray split and its front-to-back composition
 // are those of the axisymmetric march.  A sample beyond the fade (density
-// and depth exactly 0) stops after its indices, and a wave skips the channel
-// loop of a sample where none of its rays has opacity; the cube is the same.
+// and depth exactly 0) stops after its indices.  The march goes over line
+// windows (march3_win); march3_fwd, all channels of a block at every sample
+// with opacity, is what a chosen channel block or ray split runs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,6 +29,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/rtcube.h"
@@ -78,6 +80,7 @@ struct Shade3 {
     float c_k;                  // as the axisymmetric c_k, without x_CO (a field here)
     float c_alpha, sqrt_log2e;
     float si, ci, vsys;
+    float zeta;                 // |z| / rho beyond which every sample is past the fade (0: not a wedge)
 };
 
 // Z(T): the table lookup of the axisymmetric march reads only the table's
@@ -91,76 +94,66 @@ __device__ __forceinline__ float partition3(const Shade3 &s, const float4 *tab, 
 
 // Channel-independent shading of one sample (cf. physics() of the
 // axisymmetric march): S, line-centre depth K (log2 units), and d = a - v b.
-__device__ __forceinline__ SampleQ shade3(const Shade3 &s, const float4 *tab, float px, float py, float pz,
-                                          float ds) {
-    const float rho2 = fmaf(px, px, py * py);
-    const float r2 = fmaf(pz, pz, rho2);
-    const float rho = fsqrt(rho2);
+// Where a sample falls on the grid: its cell and the fractions in it, valid
+// indices for a sample beyond the fade too (taper 0).
+struct Cell3 {
+    float rho2, r2, rho, taper;
+    float fu, fw, fs;           // radial, polar and azimuthal fraction
+    uint32_t n0, n1;            // nodes (i, j, k) and (i, j, k + 1)
+};
+
+__device__ __forceinline__ void locate3(const Shade3 &s, float px, float py, float pz, Cell3 &c, int &i0, float &fr,
+                                        float &w) {
+    c.rho2 = fmaf(px, px, py * py);
+    c.r2 = fmaf(pz, pz, c.rho2);
+    c.rho = fsqrt(c.rho2);
     // Radial index.  A float index near 500 carries ~3e-5 of a cell of
     // rounding and log2 of r^2 ~ 1e5 an absolute error that the cell scale
     // multiplies; so the cell comes from the coarse index and the fraction
     // from log2 of r^2 / r_i^2, a ratio near 1.  The coarse index is within
     // 1e-4 of a cell: one re-centring step suffices.  r = 0 gives a fraction
     // of -inf: clamped fetch, zero taper, zero depth.
-    const float uco = fmaf(0.5f, flog2(r2), -s.log2_rmin) * s.u_scale;
-    int i0 = (int)clampf(uco, 0.0f, s.fnr - 2.0f);
-    float fr = flog2(1.0f + fmaf(r2, s.inv_r2n[i0], -1.0f)) * s.h_r;
+    const float uco = fmaf(0.5f, flog2(c.r2), -s.log2_rmin) * s.u_scale;
+    i0 = (int)clampf(uco, 0.0f, s.fnr - 2.0f);
+    fr = flog2(1.0f + fmaf(c.r2, s.inv_r2n[i0], -1.0f)) * s.h_r;
     if (fr < 0.0f && i0 > 0) { --i0; fr += 1.0f; }
     else if (fr >= 1.0f && i0 < s.nr - 2) { ++i0; fr -= 1.0f; }
     // Polar index from the angle to the middle node direction theta_c, which
     // is small over a wedge about the midplane (finer float spacing than theta).
-    const float a1 = fmaf(rho, s.cth_c, -pz * s.sth_c);   // r sin(theta - theta_c)
-    const float a2 = fmaf(pz, s.cth_c, rho * s.sth_c);    // r cos(theta - theta_c)
-    const float w = fmaf(atan2f(a1, a2), s.inv_dth, s.half_nt1);
+    const float a1 = fmaf(c.rho, s.cth_c, -pz * s.sth_c);   // r sin(theta - theta_c)
+    const float a2 = fmaf(pz, s.cth_c, c.rho * s.sth_c);    // r cos(theta - theta_c)
+    w = fmaf(atan2f(a1, a2), s.inv_dth, s.half_nt1);
     // fade one cell beyond the node ranges (radially from the cell and its
     // fraction, exact near both ends); beyond the fade the density and the
     // depth are exactly 0: no azimuth, no fetch, no physics
-    const float taper = clampf((float)i0 + fr + 1.0f, 0.0f, 1.0f) * clampf((s.fnr - (float)i0) - fr, 0.0f, 1.0f) *
+    c.taper = clampf((float)i0 + fr + 1.0f, 0.0f, 1.0f) * clampf((s.fnr - (float)i0) - fr, 0.0f, 1.0f) *
                         clampf(w + 1.0f, 0.0f, 1.0f) * clampf(s.fnt - w, 0.0f, 1.0f);
-    if (taper <= 0.0f) {
-        SampleQ z;
-        z.S = 0.0f; z.K = 0.0f; z.a = 0.0f; z.b = 0.0f;
-        return z;
-    }
+}
+
+// the rest of the cell, which only a sample with taper > 0 needs
+__device__ __forceinline__ void locate3_nodes(const Shade3 &s, float px, float py, Cell3 &c, int i0, float fr,
+                                              float w) {
     float sp = atan2f(py, px) * s.inv_dph;
     sp = sp < 0.0f ? sp + s.fnp : sp;
-    const float fu = clampf(fr, 0.0f, 1.0f);
+    c.fu = clampf(fr, 0.0f, 1.0f);
     const float wc = clampf(w, 0.0f, s.fnt - 1.0f);
     const int j0 = min((int)wc, s.nt - 2);
-    const float fw = wc - (float)j0;
+    c.fw = wc - (float)j0;
     int k0 = (int)sp;
-    const float fs = sp - (float)k0;
+    c.fs = sp - (float)k0;
     k0 = k0 >= s.np ? k0 - s.np : k0;       // sp may round up to np
     const int k1 = k0 + 1 >= s.np ? 0 : k0 + 1;
-    const uint32_t np = (uint32_t)s.np, plane = (uint32_t)s.nt * np;
-    const uint32_t b00 = ((uint32_t)i0 * (uint32_t)s.nt + (uint32_t)j0) * np;
-    const uint32_t base[4] = {b00, b00 + np, b00 + plane, b00 + plane + np};   // (i,j), (i,j+1), (i+1,j), (i+1,j+1)
-    float4 A[8], B[8];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const size_t n0 = 2 * (size_t)(base[c] + (uint32_t)k0), n1 = 2 * (size_t)(base[c] + (uint32_t)k1);
-        A[2 * c] = s.node[n0];
-        B[2 * c] = s.node[n0 + 1];
-        A[2 * c + 1] = s.node[n1];
-        B[2 * c + 1] = s.node[n1 + 1];
-    }
-    // trilinear weights, in the corner order of the loads
-    const float gu = 1.0f - fu, gw = 1.0f - fw, gs = 1.0f - fs;
-    const float cuw[4] = {gu * gw, gu * fw, fu * gw, fu * fw};
-    float wt[8];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) { wt[2 * c] = cuw[c] * gs; wt[2 * c + 1] = cuw[c] * fs; }
-    float ln_n = 0.0f, T = 0.0f, xco = 0.0f, vr = 0.0f, vt = 0.0f, vp = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        ln_n = fmaf(wt[c], A[c].x, ln_n);
-        T = fmaf(wt[c], A[c].y, T);
-        xco = fmaf(wt[c], A[c].z, xco);
-        vr = fmaf(wt[c], A[c].w, vr);
-        vt = fmaf(wt[c], B[c].x, vt);
-        vp = fmaf(wt[c], B[c].y, vp);
-    }
-    const float nco = xco * fexp2(ln_n * kLog2E) * taper;
+    const uint32_t b00 = ((uint32_t)i0 * (uint32_t)s.nt + (uint32_t)j0) * (uint32_t)s.np;
+    c.n0 = b00 + (uint32_t)k0;
+    c.n1 = b00 + (uint32_t)k1;
+}
+
+// The line physics of the fields of a sample, A = (ln n, T, x_CO, v_r), vt and vp.
+__device__ __forceinline__ SampleQ physics3(const Shade3 &s, const float4 *tab, const Cell3 &c, float4 A, float vt,
+                                            float vp, float px, float py, float pz, float ds) {
+    const float ln_n = A.x, T = A.y, xco = A.z, vr = A.w;
+    const float rho2 = c.rho2, r2 = c.r2, rho = c.rho;
+    const float nco = xco * fexp2(ln_n * kLog2E) * c.taper;
     // LTE populations and source function
     const float rT = frcp(T);
     const float Z = partition3(s, tab, flog2(T));
@@ -182,6 +175,92 @@ __device__ __forceinline__ SampleQ shade3(const Shade3 &s, const float4 *tab, fl
     const float vlos = fmaf(vp, ep, fmaf(vt, et, fmaf(vr, er, s.vsys)));
     q.a = vlos * q.b;
     return q;
+}
+
+__device__ __forceinline__ SampleQ shade3(const Shade3 &s, const float4 *tab, float px, float py, float pz,
+                                          float ds) {
+    Cell3 cell;
+    int i0;
+    float fr, w;
+    locate3(s, px, py, pz, cell, i0, fr, w);
+    if (cell.taper <= 0.0f) {
+        SampleQ z;
+        z.S = 0.0f; z.K = 0.0f; z.a = 0.0f; z.b = 0.0f;
+        return z;
+    }
+    locate3_nodes(s, px, py, cell, i0, fr, w);
+    const uint32_t np = (uint32_t)s.np, plane = (uint32_t)s.nt * np;
+    const uint32_t off[4] = {0u, np, plane, plane + np};   // (i,j), (i,j+1), (i+1,j), (i+1,j+1)
+    float4 A[8], B[8];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const size_t n0 = 2 * (size_t)(off[c] + cell.n0), n1 = 2 * (size_t)(off[c] + cell.n1);
+        A[2 * c] = s.node[n0];
+        B[2 * c] = s.node[n0 + 1];
+        A[2 * c + 1] = s.node[n1];
+        B[2 * c + 1] = s.node[n1 + 1];
+    }
+    // trilinear weights, in the corner order of the loads
+    const float fu = cell.fu, fw = cell.fw, fs = cell.fs;
+    const float gu = 1.0f - fu, gw = 1.0f - fw, gs = 1.0f - fs;
+    const float cuw[4] = {gu * gw, gu * fw, fu * gw, fu * fw};
+    float wt[8];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { wt[2 * c] = cuw[c] * gs; wt[2 * c + 1] = cuw[c] * fs; }
+    float4 f = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float vt = 0.0f, vp = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        f.x = fmaf(wt[c], A[c].x, f.x);
+        f.y = fmaf(wt[c], A[c].y, f.y);
+        f.z = fmaf(wt[c], A[c].z, f.z);
+        f.w = fmaf(wt[c], A[c].w, f.w);
+        vt = fmaf(wt[c], B[c].x, vt);
+        vp = fmaf(wt[c], B[c].y, vp);
+    }
+    return physics3(s, tab, cell, f, vt, vp, px, py, pz, ds);
+}
+
+// The fields of the four samples of a quad, one a lane (every lane active).
+// Each sample's eight records are four runs of 64 bytes (nodes k and k + 1);
+// the four lanes read a run together, a float4 each, and the weighted sums of
+// the four samples are then handed to their lanes: a load touches 16 lines of
+// memory instead of the 64 that lanes reading their own records would.
+__device__ __forceinline__ void gather3(const Shade3 &s, const Cell3 &cell, int h, float4 &A, float &vt, float &vp) {
+    const size_t np = (size_t)s.np, plane = (size_t)s.nt * np;
+    const float fu = cell.fu, fw = cell.fw, gu = 1.0f - fu, gw = 1.0f - fw;
+    const float cuw[4] = {gu * gw, gu * fw, fu * gw, fu * fw};
+    const bool hi = (h & 2) != 0, odd = (h & 1) != 0;   // this lane's piece: node k + 1, second half of the record
+    const float4 *base = s.node + (odd ? 1 : 0);
+    float4 sum[4];
+    auto one = [&](auto jc) {
+        constexpr int J = decltype(jc)::value;
+        const int n0 = group_lane_i<J>((int)cell.n0), n1 = group_lane_i<J>((int)cell.n1);
+        const float fs = group_lane<4, J>(cell.fs), ws = hi ? fs : 1.0f - fs;
+        const float4 *p = base + 2 * (size_t)(uint32_t)(hi ? n1 : n0);
+        const float4 v0 = p[0], v1 = p[2 * np], v2 = p[2 * plane], v3 = p[2 * (plane + np)];
+        const float w0 = group_lane<4, J>(cuw[0]) * ws, w1 = group_lane<4, J>(cuw[1]) * ws;
+        const float w2 = group_lane<4, J>(cuw[2]) * ws, w3 = group_lane<4, J>(cuw[3]) * ws;
+        sum[J].x = fmaf(w3, v3.x, fmaf(w2, v2.x, fmaf(w1, v1.x, w0 * v0.x)));
+        sum[J].y = fmaf(w3, v3.y, fmaf(w2, v2.y, fmaf(w1, v1.y, w0 * v0.y)));
+        sum[J].z = fmaf(w3, v3.z, fmaf(w2, v2.z, fmaf(w1, v1.z, w0 * v0.z)));
+        sum[J].w = fmaf(w3, v3.w, fmaf(w2, v2.w, fmaf(w1, v1.w, w0 * v0.w)));
+    };
+    one(std::integral_constant<int, 0>{});
+    one(std::integral_constant<int, 1>{});
+    one(std::integral_constant<int, 2>{});
+    one(std::integral_constant<int, 3>{});
+    // node k + node k + 1 (lanes two apart), then first and second halves (lanes one apart)
+    auto keep = [&](float a, float b) { return (hi ? b : a) + quad_xor<2>(hi ? a : b); };
+    const float4 e = make_float4(keep(sum[0].x, sum[2].x), keep(sum[0].y, sum[2].y), keep(sum[0].z, sum[2].z),
+                                 keep(sum[0].w, sum[2].w));      // sample 0 or 2
+    const float4 o = make_float4(keep(sum[1].x, sum[3].x), keep(sum[1].y, sum[3].y), keep(sum[1].z, sum[3].z),
+                                 keep(sum[1].w, sum[3].w));      // sample 1 or 3
+    const float rx = quad_xor<1>(odd ? e.x : o.x), ry = quad_xor<1>(odd ? e.y : o.y);
+    const float rz = quad_xor<1>(odd ? e.z : o.z), rw = quad_xor<1>(odd ? e.w : o.w);
+    A = make_float4(odd ? rx : e.x, odd ? ry : e.y, odd ? rz : e.z, odd ? rw : e.w);
+    vt = odd ? o.x : rx;
+    vp = odd ? o.y : ry;
 }
 
 // One lane = one pixel (or a sub-chord of it, NSPLIT lanes per ray) x CB
@@ -248,6 +327,163 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CB <= 16 ? 
 #pragma unroll
     for (int c = 0; c < CB; ++c)
         if (c0 + c < ch.n) cube[(size_t)(c0 + c) * ch_stride + pix] = I[c];
+}
+
+// Windowed march (rt_forward.hip, march_win): four lanes per pixel with the
+// channels interleaved over them, 4 x 4 pixels a wave, the rays in parts over
+// the waves of a workgroup, over the samples that can lie in the polar wedge;
+// a wave passes over steps beyond the fade and steps without CO.  Bound: half
+// the time the vector units (cells and physics of the samples inside the
+// fade), the rest the latency of the gathers and waves of unequal work.
+// 512 x 96 x 256 grid, 256^2 x 512 samples, 64 channels: 1.30 ms as
+// march3_fwd, 0.43 ms with windows, 0.39 ms with the quad's gather (gather3),
+// 0.29 ms with the work order below.
+//
+// Block b runs on XCD b % 8, so consecutive work goes to an XCD in chunks of
+// 16 tiles: their neighbours share its L2's lines.  One run of tiles per XCD,
+// an eighth of the image, leaves the XCDs of the image's edge idle: 0.39 ms
+// against 0.29 (chunks of 16) and 0.36 (of 1); 512^2 x 20 channels 0.90, 0.65
+// and 0.81 ms.  A launch under 1024 blocks takes smaller chunks, 8 per XCD.
+// 128 VGPRs (four waves a SIMD) hold the 16-channel form without spills: 0.39
+// against 0.43 ms at its natural 132; 24 and 32 channels would spill.
+template <int CB, bool UNIFORM>
+__global__ __launch_bounds__(512, CB <= 16 ? 4 : 2) void march3_win(Geometry3 g, Shade3 s, Channels ch, Windows win, int lsplit,
+                                                  float *__restrict__ cube, int ch_stride, int nchb, int nwork,
+                                                  int chunk) {
+    const int L = blockIdx.x;
+    const int work = ((L / 8) / chunk * 8 + L % 8) * chunk + (L / 8) % chunk;
+    if (work >= nwork) return;                       // whole workgroup: padding of the grid to 8 x chunk
+    __shared__ float4 ztab[kZTableNodes - 1];
+    extern __shared__ float parts[];
+    for (int i = threadIdx.x; i < kZTableNodes - 1; i += blockDim.x) ztab[i] = s.ztab[i];
+    __syncthreads();
+    constexpr int G = kLanesPerPixel, U = unit_slots(CB), NU = CB / U;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nsplit = 1 << lsplit, nsub = (int)(blockDim.x >> 6) >> lsplit;   // 4 x 4 tiles of this workgroup
+    const int split = wave & (nsplit - 1), sub = wave >> lsplit;
+    const int lane = threadIdx.x & 63, h = lane & 3, slot = lane >> 2;
+    const int tw = nsub >= 2 ? 8 : 4, th = nsub >= 4 ? 8 : 4;
+    const int tiles_x = (g.nx + tw - 1) / tw;
+    const int tile = work / nchb, blk = work % nchb;
+    const int p = (tile % tiles_x) * tw + (sub & 1) * 4 + (slot & 3);
+    const int q = (tile / tiles_x) * th + (sub >> 1) * 4 + (slot >> 2);
+    const int c0 = blk * CB * G, u0 = blk * NU;
+    const bool inside = p < g.nx && q < g.ny;
+    const Chord3 cr = chord3(g, inside ? p : 0, inside ? q : 0);
+    const bool live = inside && cr.h2 > 0.0f;
+    float I[CB], Tr[CB], vc[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        I[c] = 0.0f;
+        Tr[c] = 1.0f;
+        vc[c] = ch.v[c0 + c * G + h];
+    }
+    if (__ballot(live) != 0) {
+        const float ds = live ? 2.0f * sqrtf(cr.h2) / (float)g.nsamp : 0.0f;
+        const float pmy = cr.yp * g.ci, pmz = cr.yp * g.si, wy = g.si, wz = -g.ci;
+        const float half = 0.5f * (float)g.nsamp;
+        const int2 own = !live ? make_int2(g.nsamp, -1)
+                       : s.zeta > 0.0f ? cone_range(s.zeta, cr.xp, pmy, pmz, wy, wz, ds, g.nsamp)
+                                       : make_int2(0, g.nsamp - 1);
+        const int kf = wave_min(own.x), kn = max(wave_max(own.y) + 1 - kf, 0);
+        const int len = (((kn + nsplit - 1) >> lsplit) + G - 1) / G * G;
+        const int k1 = kf + min(kn, (split + 1) * len);
+        const float v0 = ch.v[c0];
+        for (int k = kf + split * len; k < k1; k += G) {
+            const float t = ((float)min(k + h, k1 - 1) + 0.5f - half) * ds;
+            const float py = fmaf(t, wy, pmy), pz = fmaf(t, wz, pmz);
+            Cell3 cell;
+            int i0;
+            float fr, w;
+            locate3(s, cr.xp, py, pz, cell, i0, fr, w);
+            const bool in = live && k + h < k1 && cell.taper > 0.0f;
+            if (__builtin_amdgcn_ballot_w64(in) == 0) continue;
+            locate3_nodes(s, cr.xp, py, cell, i0, fr, w);
+            if (!in) cell.n0 = cell.n1 = 0;
+            float4 A;
+            float vt, vp;
+            gather3(s, cell, h, A, vt, vp);
+            // no CO at any of the wave's samples
+            if (__builtin_amdgcn_ballot_w64(in && A.z != 0.0f) == 0) continue;
+            SampleQ own = physics3(s, ztab, cell, A, vt, vp, cr.xp, py, pz, ds);
+            if (!in) own.S = own.K = own.a = own.b = 0.0f;
+            const float own_lk = flog2(own.K);
+            const unsigned mask = or_over_pixels(unit_mask<NU, G * U, UNIFORM>(own, own_lk, in, v0, win, u0));
+            const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < kFaintLog2K));
+            const unsigned long long thick = __builtin_amdgcn_ballot_w64(!(own_lk < kThinLog2K));
+            auto step = [&](auto jc) {
+                constexpr int J = decltype(jc)::value;
+                constexpr unsigned long long mine = 0x1111111111111111ull << J;
+                const unsigned m = (unsigned)__builtin_amdgcn_readlane((int)mask, J);
+                if (m == 0) return;
+                const float S = group_lane<G, J>(own.S), lK = group_lane<G, J>(own_lk);
+                const float a = group_lane<G, J>(own.a), b = group_lane<G, J>(own.b);
+                march_units<CB>(I, Tr, S, lK, m, (bright & mine) != 0, (thick & mine) != 0,
+                                [&](int c) { return fmaf(-vc[c], b, a); });
+            };
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
+        }
+    }
+    if (nsplit > 1) {
+        float *mine = parts + (size_t)(sub * (nsplit - 1)) * (2 * CB * 64) + lane;
+        if (split > 0) {
+            float *o = mine + (size_t)(split - 1) * (2 * CB * 64);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                o[c * 64] = I[c];
+                o[(CB + c) * 64] = Tr[c];
+            }
+        }
+        __syncthreads();
+        if (split > 0) return;
+        for (int j = 0; j < nsplit - 1; ++j) {
+            const float *o = mine + (size_t)j * (2 * CB * 64);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                I[c] = fmaf(Tr[c], o[c * 64], I[c]);
+                Tr[c] *= o[(CB + c) * 64];
+            }
+        }
+    }
+    if (!inside) return;
+    const size_t pix = (size_t)q * g.nx + p;
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+        if (c0 + c * G + h < ch.n) cube[(size_t)(c0 + c * G + h) * ch_stride + pix] = I[c];
+}
+
+template <int CB>
+static hipError_t launch3_win(const Geometry3 &g, const Shade3 &s, const Channels &ch, const Windows &win, float *cube,
+                              bool uniform, int lsplit, hipStream_t st) {
+    const int waves = std::max(4, 1 << lsplit), nsub = waves >> lsplit;
+    const int tw = nsub >= 2 ? 8 : 4, th = nsub >= 4 ? 8 : 4;
+    const long tiles = (long)((g.nx + tw - 1) / tw) * ((g.ny + th - 1) / th);
+    const int nchb = (ch.n + CB * kLanesPerPixel - 1) / (CB * kLanesPerPixel);
+    const long nwork = tiles * nchb;
+    if (nwork > (1L << 30)) return hipErrorInvalidValue;
+    const int chunk = (int)std::min(16L, std::max(1L, nwork / 64));
+    const int nblocks = (int)((nwork + 8 * chunk - 1) / (8 * chunk)) * (8 * chunk);
+    const size_t lds = (size_t)nsub * ((1 << lsplit) - 1) * 2 * CB * 64 * sizeof(float);
+    const int cs = g.nx * g.ny;
+    if (uniform) hipLaunchKernelGGL((march3_win<CB, true>), dim3(nblocks), dim3(64 * waves), lds, st, g, s, ch, win, lsplit, cube, cs, nchb, (int)nwork, chunk);
+    else hipLaunchKernelGGL((march3_win<CB, false>), dim3(nblocks), dim3(64 * waves), lds, st, g, s, ch, win, lsplit, cube, cs, nchb, (int)nwork, chunk);
+    return hipGetLastError();
+}
+
+static hipError_t launch_forward3_win(const Geometry3 &g, const Shade3 &s, const Channels &ch, const Windows &win,
+                                      float *cube, int cb, bool uniform, int lsplit, hipStream_t st) {
+    switch (cb) {
+    case 4: return launch3_win<4>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 8: return launch3_win<8>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 12: return launch3_win<12>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 16: return launch3_win<16>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 24: return launch3_win<24>(g, s, ch, win, cube, uniform, lsplit, st);
+    case 32: return launch3_win<32>(g, s, ch, win, cube, uniform, lsplit, st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <int CB, int NSPLIT>
@@ -331,7 +567,7 @@ static rt_status radius_table(const rt_grid3d &g, const float **out) {
     return RT_OK;
 }
 
-// Launch shape of the 3-D march.  Its shading (two atan2, sixteen scattered
+// Launch shape of march3_fwd, where one of its two options is chosen.  Its shading (two atan2, sixteen scattered
 // loads, the physics) costs ~25 channels' worth of issue slots per sample, so
 // a pixel's channels stay in one block (the smallest of 8..64 holding them,
 // never split into two 32-channel blocks as the axisymmetric march does).
@@ -491,6 +727,8 @@ static rt_status build_shade3(const rt_problem3d *p, Shade3 *s) {
     s->si = (float)g.si;
     s->ci = (float)g.ci;
     s->vsys = (float)p->spec.v_sys_kms;
+    const double edge = std::max(0.5 * kPI3 - gr.th_min, gr.th_max - 0.5 * kPI3) + dth;
+    s->zeta = edge < 1.5 ? (float)std::tan(edge) : 0.0f;
     return RT_OK;
 }
 
@@ -563,8 +801,10 @@ rt_status rt_render_cube_3d(const rt_problem3d *p, float *cube, void *stream) {
     st = build_shade3(p, &s);
     if (st != RT_OK) return st;
     const Geometry3 g = geometry3(p);
+    const long npix = (long)p->cam.nx * p->cam.ny;
+    const bool windows = !channel_block_option() && !ray_split_option();
     int cb, nsplit;
-    forward_shape3(std::min(p->spec.nch, kLaunchChannels), (long)p->cam.nx * p->cam.ny, p->nsamp, &cb, &nsplit);
+    forward_shape3(std::min(p->spec.nch, kLaunchChannels), npix, p->nsamp, &cb, &nsplit);
     if (channel_block_option()) cb = channel_block_option();
     if (ray_split_option()) nsplit = ray_split_option();
     const size_t plane = (size_t)p->cam.nx * p->cam.ny;
@@ -573,6 +813,18 @@ rt_status rt_render_cube_3d(const rt_problem3d *p, float *cube, void *stream) {
         std::memset(&ch, 0, sizeof ch);
         ch.n = std::min(kLaunchChannels, p->spec.nch - c0);
         for (int c = 0; c < ch.n; ++c) ch.v[c] = (float)p->spec.v_kms[c0 + c];
+        if (windows) {
+            int wcb, lsplit;
+            double dv = 0.0;
+            window_shape(ch.n, npix, p->nsamp, &wcb, &lsplit);
+            const bool uniform = uniform_spacing(p->spec.v_kms + c0, ch.n, &dv) && dv != 0.0;
+            Windows win;
+            unit_windows(ch, wcb, uniform ? dv : 0.0, &win);
+            const hipError_t e = launch_forward3_win(g, s, ch, win, cube + (size_t)c0 * plane, wcb, uniform, lsplit,
+                                                     (hipStream_t)stream);
+            if (e != hipSuccess) return fail_hip(e, "3-D forward launch");
+            continue;
+        }
         const hipError_t e = launch_forward3(g, s, ch, cube + (size_t)c0 * plane, cb, nsplit, (hipStream_t)stream);
         if (e != hipSuccess) return fail_hip(e, "3-D forward launch");
     }
