@@ -89,8 +89,12 @@ __device__ __forceinline__ float phase2(float f, float c) {
 }
 
 // ---------------------------------------------------------------- register-resident BF16 forward
-constexpr int kRrRow0 = kF + 8;        // padded row of layer 0 (bf16 elements)
-constexpr int kRrRow = kW + 8;         // padded row of layers 1..3
+// Rows in LDS are padded by 32 bytes: a wave's 16-byte operand reads (16 rows,
+// four 16-byte columns) then take 4.9 cycles (the same as 64 consecutive
+// pieces); any other padding measured, 16 bytes among them, takes 8.4, none 16
+// to 32.
+constexpr int kRrRow0 = kF + 16;       // padded row of layer 0 (bf16 elements)
+constexpr int kRrRow = kW + 16;        // padded row of layers 1..3
 // 16-point column tiles per wave and lanes per workgroup (one workgroup per
 // CU, the weights filling most of its LDS); 4 x 512 measured fastest of
 // 2 x 1024, 2 x 768 and 4 x 512, and the same as 3 x 512 (which spills no
@@ -304,53 +308,60 @@ __global__ __launch_bounds__(NT) void mlp_fwd_rr(Geometry g, Shade s, MlpDev w, 
 }
 
 // ---------------------------------------------------------------- register-resident BF16 backward
-// mlp_bwd_rr: one workgroup of four waves per CU, each wave with the full
-// register file of its SIMD.  A wave takes 16 points per pass (the workgroup
-// 64): it recomputes the forward with the transposed product (weights read
-// as A operands from LDS, where the workgroup stages each layer's weights
-// from L2: one copy per pass for the four waves, written by loads that go
-// to LDS directly and are issued one stage ahead into a free buffer -- the
-// forward's layers alternate between the weight buffer and the point-major
-// rows, which the forward does not use; the backward's transposed weights
-// are issued before the weight-gradient products that precede them -- so
-// their latency overlaps the matrix work), keeping z' of every layer as BF16;
-// walks back through the layers (dL/dh' of the layer below by the product
-// with the transposed weights, the SiLU derivative recomputed from z'); and
-// for the weight gradient, which sums over points, writes dL/dz' and h' of
-// the pass into LDS as point-major rows, so that after a barrier each wave
-// accumulates its own slice of every layer's gradient (32 output rows of the
-// hidden layers, two 16-column tiles of the output layer) in MFMA
+// mlp_bwd_rr: one workgroup of eight waves per CU, 64 points a pass.  Two waves
+// share 16 points, each with half of every layer's neurons: they recompute the
+// forward with the transposed product (weights read as A operands from LDS,
+// where the workgroup stages each layer's weights from L2: one copy per pass
+// for all waves, written by loads that go to LDS directly and are issued one
+// stage ahead into a free buffer -- the forward's layers alternate between the
+// weight buffer and the point-major rows, which the forward does not use; the
+// backward's transposed weights are issued before the weight-gradient products
+// that precede them -- so their latency overlaps the matrix work), pass each
+// other their halves of h' through LDS, and keep z' of every layer as BF16;
+// walk back through the layers (dL/dh' of the layer below by the product with
+// the transposed weights, the SiLU derivative recomputed from z'); and for the
+// weight gradient, which sums over points, write dL/dz' and h' of the pass
+// into LDS as point-major rows, so that after a barrier each wave accumulates
+// its own block of every layer's gradient (32 output rows by half the input
+// columns of the hidden layers, a 16-column tile of the output layer) in MFMA
 // accumulators over all 64 points.  Bias gradients are row sums of the same
 // LDS rows.  Everything is flushed with atomics once, at the end.
+//
+// Bound: issue of the vector instructions beside the matrix ones (SiLU and its
+// derivative, conversions, the row writes) and the staging of the weights (240
+// KB a pass; without it 3.5 ms where it takes 4.4).  A single wave issues no
+// more than one vector instruction in 5 cycles, two of them twice that.  256^2
+// x 256 samples: four waves with all neurons of 16 points each 6.0 ms, eight
+// waves 5.1, rows written two points at once 4.85, LDS rows without conflicts
+// 4.7, weights fetched from scalar addresses 4.4.
 constexpr int kBrPts = 64;                 // points per workgroup pass
+constexpr int kBrThreads = 512;
 // global-memory views (the pass loop launders the weight pointers, which
 // would otherwise turn their loads into flat loads)
 typedef const __attribute__((address_space(1))) __bf16 gbf16;
 typedef const __attribute__((address_space(1))) bf16x8 gbf16x8;
-constexpr int kBrStride = kBrPts + 8;      // LDS row of the point-major buffers (bf16)
+constexpr int kBrStride = kBrPts + 16;     // LDS row of the point-major buffers (bf16)
 
-__device__ __forceinline__ void br_features(bf16x8 (&feat)[2], const MlpDev &w, float cr, float cz, int lg) {
+// features of one coordinate
+__device__ __forceinline__ bf16x8 br_features(const MlpDev &w, float x0, int lg) {
     const int fb = 8 * (lg & 1) + (lg < 2 ? 0 : 4);
+    float own[4], sent[4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        float own[4], sent[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float x = w.freq[fb + q] * (c == 0 ? cr : cz);
-            const float t = 0.5f * (x - 2.0f * floorf(0.5f * x));
-            const float sv = __builtin_amdgcn_sinf(t), cv = __builtin_amdgcn_cosf(t);
-            own[q] = lg < 2 ? sv : cv;
-            sent[q] = lg < 2 ? cv : sv;
-        }
-        bf16x8 f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float r = __shfl_xor(sent[q], 32);
-            f[q] = (__bf16)(lg < 2 ? own[q] : r);
-            f[4 + q] = (__bf16)(lg < 2 ? r : own[q]);
-        }
-        feat[c] = f;
+    for (int q = 0; q < 4; ++q) {
+        const float x = w.freq[fb + q] * x0;
+        const float t = 0.5f * (x - 2.0f * floorf(0.5f * x));
+        const float sv = __builtin_amdgcn_sinf(t), cv = __builtin_amdgcn_cosf(t);
+        own[q] = lg < 2 ? sv : cv;
+        sent[q] = lg < 2 ? cv : sv;
     }
+    bf16x8 f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float r = __shfl_xor(sent[q], 32);
+        f[q] = (__bf16)(lg < 2 ? own[q] : r);
+        f[4 + q] = (__bf16)(lg < 2 ? r : own[q]);
+    }
+    return f;
 }
 
 // h' = z' sigma(z) and dL/dz' = dL/dh' SiLU'(z) of one neuron, z = ln2 z'
@@ -362,68 +373,99 @@ __device__ __forceinline__ void br_act_grad(__bf16 zq16, float dh, bf16x8 &hp, b
     dz[e] = (__bf16)(dh * (sg * (1.0f + z * (1.0f - sg))));
 }
 
-// point-major write of 32 accumulator-layout values (neurons 16t + 4lg + i,
-// t = 2cp + h, element 4h + i of pair cp) of the lane's point
-__device__ __forceinline__ void br_write_rows(__bf16 *X, const bf16x8 (&v)[4], int lg, int col) {
+// (a, b) of this lane's point and its neighbour's -> this lane's neuron of the
+// pair at both points: a of (even, odd lane) in even lanes, b in odd ones
+__device__ __forceinline__ uint32_t br_swap(uint32_t ab, uint32_t sel) {
+    const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)ab, 0xB1, 0xF, 0xF, false);
+    return __builtin_amdgcn_perm(other, ab, sel);
+}
+// v_perm_b32 selector of br_swap: even lanes (own low, other low), odd ones (other high, own high)
+__device__ __forceinline__ uint32_t br_swap_sel(int lane) { return lane & 1 ? 0x03020706u : 0x05040100u; }
+
+// point-major write of 8 consecutive-pair values of the lane's point, value j
+// in row row0(j), j even, and the next row: neighbouring lanes swap values so
+// that each writes two points of one row at once.  (One 2-byte write a value
+// took the LDS twice the instructions and 4 cycles of conflicts each.)
+template <class Row>
+__device__ __forceinline__ void br_write8(__bf16 *X, bf16x8 v, int lane, int col, Row row0) {
+    const uint32_t sel = br_swap_sel(lane);
+    union { bf16x8 h; uint32_t u[4]; } p;
+    p.h = v;
+    __bf16 *o = X + (lane & 1) * kBrStride + (col & ~1);
 #pragma unroll
-    for (int cp = 0; cp < 4; ++cp)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) X[(32 * cp + 16 * h + 4 * lg + i) * kBrStride + col] = v[cp][4 * h + i];
+    for (int q = 0; q < 4; ++q) *(uint32_t *)(o + row0(2 * q) * kBrStride) = br_swap(p.u[q], sel);
 }
 
-// dW slice of one hidden layer: rows [32 wv, 32 wv + 32) of XD against the
-// NI 16-row tiles of XH, over the 64 points
+// 16 accumulator-layout values (neurons 16t + 4lg + i, t = 2cp + h, element
+// 4h + i of pair cp = cp0, cp0 + 1) of the lane's point
+__device__ __forceinline__ void br_write_rows(__bf16 *X, const bf16x8 (&v)[2], int cp0, int lane, int col) {
+    __bf16 *o = X + (32 * cp0 + 4 * (lane >> 4)) * kBrStride;
+#pragma unroll
+    for (int cq = 0; cq < 2; ++cq)
+        br_write8(o, v[cq], lane, col, [=](int j) { return 32 * cq + 16 * (j >> 2) + (j & 3); });
+}
+
+// dW block of one hidden layer: rows [32 rq, 32 rq + 32) of XD against the NI
+// 16-row tiles of XH from tile it0, over the 64 points
 template <int NI>
-__device__ __forceinline__ void br_dw(floatx4 (&acc)[2][NI], const __bf16 *XD, const __bf16 *XH, int wv, int lg,
-                                      int lc) {
+__device__ __forceinline__ void br_dw(floatx4 (&acc)[2][NI], const __bf16 *XD, const __bf16 *XH, int rq, int it0,
+                                      int lg, int lc) {
 #pragma unroll
     for (int kc = 0; kc < kBrPts / 32; ++kc) {
-        const bf16x8 a0 = *(const bf16x8 *)(XD + (32 * wv + lc) * kBrStride + 32 * kc + 8 * lg);
-        const bf16x8 a1 = *(const bf16x8 *)(XD + (32 * wv + 16 + lc) * kBrStride + 32 * kc + 8 * lg);
+        const bf16x8 a0 = *(const bf16x8 *)(XD + (32 * rq + lc) * kBrStride + 32 * kc + 8 * lg);
+        const bf16x8 a1 = *(const bf16x8 *)(XD + (32 * rq + 16 + lc) * kBrStride + 32 * kc + 8 * lg);
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
-            const bf16x8 b = *(const bf16x8 *)(XH + (16 * it + lc) * kBrStride + 32 * kc + 8 * lg);
+            const bf16x8 b = *(const bf16x8 *)(XH + (16 * (it0 + it) + lc) * kBrStride + 32 * kc + 8 * lg);
             acc[0][it] = mfma_bf16(a0, b, acc[0][it]);
             acc[1][it] = mfma_bf16(a1, b, acc[1][it]);
         }
     }
 }
 
-// sum over the 64 points of LDS row r (two lanes per row, 32 points each);
+// sum over the 64 points of LDS row r (four lanes per row, 16 points each);
 // two values per instruction, as a dot product with (1, 1)
-__device__ __forceinline__ float br_rowsum(const __bf16 *X, int r, int half) {
+__device__ __forceinline__ float br_rowsum(const __bf16 *X, int r, int part) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
     float sum = 0.0f;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const bf16x8 v = *(const bf16x8 *)(X + r * kBrStride + 32 * half + 8 * q);
+    for (int q = 0; q < 2; ++q) {
+        const bf16x8 v = *(const bf16x8 *)(X + r * kBrStride + 16 * part + 8 * q);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bf16x2 p = {v[2 * j], v[2 * j + 1]};
             sum = __builtin_amdgcn_fdot2_f32_bf16(p, one, sum, false);
         }
     }
-    return sum + __shfl_xor(sum, 1);
+    sum += __shfl_xor(sum, 1);
+    return sum + __shfl_xor(sum, 2);
 }
 
 // copy n bf16 elements (a multiple of 8) of one layer's prepared weights
-// from global memory into the workgroup's staging buffer (256 lanes): global
+// from global memory into the workgroup's staging buffer (512 lanes): global
 // loads that write LDS directly (16 B per lane, lane i of a wave to the
 // wave's base + 16 i), so the copy holds no registers; every load is waited
 // for (br_wait) before the barrier that precedes the first read
-__device__ __forceinline__ void br_issue(__bf16 *dst, const gbf16 *src, int n, int tid) {
+// (scalar base and 32-bit lane offset: per-lane 64-bit addresses of every
+// stage would be kept, and spilled, across the pass)
+template <int N>
+__device__ __forceinline__ void br_issue(__bf16 *dst, const gbf16 *src, int wv, int lane) {
     typedef __attribute__((address_space(3))) void lds_void;
     typedef const __attribute__((address_space(1))) void g_void;
-    const int nchunk = n / 8, wv = tid >> 6, lane = tid & 63;
+    typedef const __attribute__((address_space(1))) char g_char;
+    constexpr int kChunks = N / 8;
+    static_assert(N % 8 == 0 && kChunks % 64 == 0, "whole waves of 16 bytes a lane");
     // (kept apart from the surrounding matrix code: interleaved with it, the
     // address arithmetic lengthens live ranges into spills)
     __builtin_amdgcn_sched_barrier(0);
-    for (int c0 = 64 * wv; c0 < nchunk; c0 += 256) {
-        const int c = c0 + lane;
-        if (c < nchunk) __builtin_amdgcn_global_load_lds((g_void *)(src + 8 * c), (lds_void *)(dst + 8 * c0), 16, 0, 0);
+    const uint32_t off = 16u * (uint32_t)lane;
+#pragma unroll
+    for (int i = 0; i < (kChunks + kBrThreads - 1) / kBrThreads; ++i) {
+        const int c0 = 64 * wv + i * kBrThreads;
+        if ((i + 1) * kBrThreads <= kChunks || c0 < kChunks)
+            __builtin_amdgcn_global_load_lds((g_void *)((g_char *)(src + 8 * c0) + off), (lds_void *)(dst + 8 * c0), 16,
+                                             0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
 }
@@ -550,7 +592,7 @@ __global__ __launch_bounds__(1024) void mlp_live_write(const float4 *__restrict_
     }
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void mlp_bwd_rr(
+__global__ __launch_bounds__(kBrThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_bwd_rr(
     Geometry g, Shade s, MlpDev w, size_t M, const float4 *__restrict__ dO, const uint32_t *__restrict__ list,
     float *__restrict__ dW) {
     // point-major rows of the backward: dL/dz' (or dL/do) rows x points, then
@@ -561,39 +603,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     __bf16 *const XH = XU + kW * kBrStride;
     __shared__ __attribute__((aligned(16))) float sB[4 * kW];
     __shared__ __attribute__((aligned(16))) float sW5[3 * kW];
-    // lane-private parking of z' (4 layers x 4 operand packs) and the two
-    // feature packs between the forward and the backward of a pass
+    // parking of z' (layers 0 to 2, packs 4 l + cp) and the two feature packs
+    // (16, 17) between the forward and the backward of a pass, and where the
+    // two waves of a point pass packs to each other: h' of layers 0 and 2 in
+    // packs 12.., of layer 1 in 8.. (z' of layer 2 is parked there a barrier
+    // later), dL/dz' of layer l in 4 l.. once its z' is read
     __shared__ bf16x8 ZP[18][256];
     // one layer's weights (forward) or transposed weights (backward)
     __shared__ __attribute__((aligned(16))) __bf16 SW[kW * kRrRow];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lg = lane >> 4, lc = lane & 15;
-    for (int i = tid; i < 4 * kW; i += 256) sB[i] = kLog2E * w.b[i / kW][i % kW];
-    for (int i = tid; i < 3 * kW; i += 256) sW5[i] = kLn2 * w.W5[i];
-    floatx4 g0[2][4], g1[2][8], g2[2][8], g3[2][8], g4[2][1];
+    const int pt = wv >> 1, hf = wv & 1;       // 16-point tile, half of the neurons
+    const int cp0 = 2 * hf, pl = 64 * pt + lane;
+    for (int i = tid; i < 4 * kW; i += kBrThreads) sB[i] = kLog2E * w.b[i / kW][i % kW];
+    for (int i = tid; i < 3 * kW; i += kBrThreads) sW5[i] = kLn2 * w.W5[i];
+    // this wave's blocks of the weight gradients: rows from 32 pt, half hf of
+    // the columns; columns from 16 wv of the output layer
+    floatx4 g0[2][2], g1[2][4], g2[2][4], g3[2][4], g4 = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) g0[a][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = 0; b < 2; ++b) g0[a][b] = g4;
 #pragma unroll
-        for (int b = 0; b < 8; ++b) { g1[a][b] = g0[a][0]; g2[a][b] = g0[a][0]; g3[a][b] = g0[a][0]; }
-        g4[a][0] = g0[a][0];
+        for (int b = 0; b < 4; ++b) g1[a][b] = g2[a][b] = g3[a][b] = g4;
     }
     float db0 = 0.0f, db1 = 0.0f, db2 = 0.0f, db3 = 0.0f, db5 = 0.0f;
-    const int brow = 32 * wv + (lane >> 1), bhalf = lane & 1;     // bias row of this lane
-    const int col = 16 * wv + lc;                                 // this lane's point within the pass
+    const int brow = 16 * wv + (lane >> 2), bpart = lane & 3;     // bias row of this lane
+    const int col = 16 * pt + lc;                                 // this lane's point within the pass
     // layer 0's weights for the first pass (each pass stages the next's)
-    br_issue(SW, (const gbf16 *)(uint64_t)w.Wr, kW * kRrRow0, tid);
-    br_wait();
-    __syncthreads();
-    // the points with any dL/do != 0, listed in order (list[0] of them), 64
-    // to a pass
+    br_issue<kW * kRrRow0>(SW, (const gbf16 *)(uint64_t)w.Wr, wv, lane);
+    // the points with any dL/do that counts, listed in order (list[0] of
+    // them), 64 to a pass
     const uint32_t npts = list[0];
     const uint32_t npass = (npts + kBrPts - 1) / kBrPts;
     for (uint32_t ip = blockIdx.x; ip < npass; ip += gridDim.x) {
         const uint32_t base = ip * kBrPts;
         // the weight operands are the same every pass: hide that from the
-        // compiler, or it keeps all 208 fragments in registers across passes
+        // compiler, or it keeps all their fragments in registers across passes
         uint64_t wr_u = (uint64_t)w.Wr, wrt_u = (uint64_t)w.WrT;
         asm volatile("" : "+s"(wr_u), "+s"(wrt_u));
         const gbf16 *Wr = (const gbf16 *)wr_u;
@@ -601,16 +647,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         const size_t m = base + col < npts ? (size_t)list[1 + base + col] : M;   // M: no point
         float rh = 0.0f, zh = 0.0f;
         if (lane < 16 && m < M) point_coords(g, s, m, &rh, &zh);
-        bf16x8 hin[4];
-        {
-            bf16x8 feat[2];
-            br_features(feat, w, __shfl(rh, lc), __shfl(zh, lc), lg);
-            ZP[16][tid] = feat[0];
-            ZP[17][tid] = feat[1];
-            hin[0] = feat[0];
-            hin[1] = feat[1];
-        }
+        // each wave the features of one coordinate
+        ZP[16 + hf][pl] = br_features(w, __shfl(hf ? zh : rh, lc), lg);
+        br_wait();
+        __syncthreads();
         // ---- forward, parking z' of every layer
+        bf16x8 z2[2], z3[2];
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
             const int nk = l == 0 ? kF / 32 : kW / 32;
@@ -619,12 +661,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             // other buffer, free since the barrier that ended layer l - 1:
             // layer l + 1's weights, or after layer 3 the transposed weights
             // of the backward's first product
-            if (l < 3) br_issue(l & 1 ? SW : XU, Wr + (size_t)kW * kRrRow0 + (size_t)l * kW * kRrRow, kW * kRrRow, tid);
-            else br_issue(SW, WrT + (size_t)2 * kW * kRrRow, kW * kRrRow, tid);
+            if (l < 3) br_issue<kW * kRrRow>(l & 1 ? SW : XU, Wr + (size_t)kW * kRrRow0 + (size_t)l * kW * kRrRow, wv, lane);
+            else br_issue<kW * kRrRow>(SW, WrT + (size_t)2 * kW * kRrRow, wv, lane);
             const __bf16 *Wl = l & 1 ? XU : SW;
-            bf16x8 hout[4];
+            const int in = l == 0 ? 16 : l == 2 ? 8 : 12;      // the packs of this layer's input
+            bf16x8 hin[4];
 #pragma unroll
-            for (int cp = 0; cp < 4; ++cp) {
+            for (int c = 0; c < 4; ++c)
+                if (c < nk) hin[c] = ZP[in + c][pl];
+            if (l == 3) {
+                ZP[8 + cp0][pl] = z2[0];
+                ZP[9 + cp0][pl] = z2[1];
+            }
+#pragma unroll
+            for (int cq = 0; cq < 2; ++cq) {
+                const int cp = cp0 + cq;
                 floatx4 acc[2];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) acc[h] = *(const floatx4 *)(sB + l * kW + 32 * cp + 16 * h + 4 * lg);
@@ -637,159 +688,157 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                         acc[h] = mfma_bf16(a, hin[c], acc[h]);
                     }
                 }
-                bf16x8 zq;
+                bf16x8 zq, hout;
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const float z = acc[h][i];
                         zq[4 * h + i] = (__bf16)z;
-                        if (l < 3) hout[cp][4 * h + i] = (__bf16)(z * frcp(1.0f + fexp2(-z)));
+                        if (l < 3) hout[4 * h + i] = (__bf16)(z * frcp(1.0f + fexp2(-z)));
                     }
-                ZP[4 * l + cp][tid] = zq;
-            }
-            if (l < 3) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) hin[c] = hout[c];
+                if (l == 2) z2[cq] = zq;
+                else if (l == 3) z3[cq] = zq;
+                else ZP[4 * l + cp][pl] = zq;
+                if (l < 3) ZP[(l == 1 ? 8 : 12) + cp][pl] = hout;
             }
             br_wait();
             __syncthreads();
         }
         // ---- output layer: dL/dh'_3 = W5'^T dL/do, then h'_3 and dL/dz'_3
         const float4 d = m < M ? dO[m] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        bf16x8 hp[4], dz[4], dzu[4];   // h' and dL/dz' of the current layer, dL/dz' of the layer above
+        bf16x8 hp[2], dz[2], dzu[2];   // h' and dL/dz' of the current layer, dL/dz' of the layer above
 #pragma unroll
-        for (int cp = 0; cp < 4; ++cp) {
-            const bf16x8 zq = ZP[12 + cp][tid];
+        for (int cq = 0; cq < 2; ++cq)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int n = 32 * cp + 16 * (e >> 2) + 4 * lg + (e & 3);
+                const int n = 32 * (cp0 + cq) + 16 * (e >> 2) + 4 * lg + (e & 3);
                 const float dh = fmaf(sW5[n], d.x, fmaf(sW5[kW + n], d.y, sW5[2 * kW + n] * d.z));
-                br_act_grad(zq[e], dh, hp[cp], dz[cp], e);
+                br_act_grad(z3[cq][e], dh, hp[cq], dz[cq], e);
             }
-        }
 #pragma unroll
         for (int l = 3; l >= 0; --l) {
             // gradient of the layer above (the output layer when l == 3):
             // its dL/dz' and this layer's h', point-major, into LDS
-            br_write_rows(XH, hp, lg, col);
+            br_write_rows(XH, hp, cp0, lane, col);
             if (l == 3) {
-                if (lg == 0) {
-                    XD[0 * kBrStride + col] = (__bf16)d.x;
-                    XD[1 * kBrStride + col] = (__bf16)d.y;
-                    XD[2 * kBrStride + col] = (__bf16)d.z;
-                } else {
-                    // rows 3..15 are zero padding of the 16-row tile
+                if (hf == 0) {
+                    if (lg == 0) {
+                        XD[0 * kBrStride + col] = (__bf16)d.x;
+                        XD[1 * kBrStride + col] = (__bf16)d.y;
+                        XD[2 * kBrStride + col] = (__bf16)d.z;
+                    } else {
+                        // rows 3..15 are zero padding of the 16-row tile
 #pragma unroll
-                    for (int r = 0; r < 5; ++r) {
-                        const int rr = 3 + 5 * (lg - 1) + r;
-                        if (rr < 16) XD[rr * kBrStride + col] = (__bf16)0.0f;
+                        for (int r = 0; r < 5; ++r) {
+                            const int rr = 3 + 5 * (lg - 1) + r;
+                            if (rr < 16) XD[rr * kBrStride + col] = (__bf16)0.0f;
+                        }
                     }
                 }
             } else {
-                br_write_rows(XD, dzu, lg, col);
+                br_write_rows(XD, dzu, cp0, lane, col);
+            }
+            if (l >= 1) {
+                ZP[4 * l + cp0][pl] = dz[0];
+                ZP[4 * l + cp0 + 1][pl] = dz[1];
             }
             __syncthreads();
             // SW is free (every wave's product with it came before its rows):
             // issue the transposed weights of the next product down, or after
             // the last one the next pass's layer-0 weights
-            if (l == 2 || l == 1) br_issue(SW, WrT + (size_t)(l - 1) * kW * kRrRow, kW * kRrRow, tid);
-            else if (l == 0) br_issue(SW, Wr, kW * kRrRow0, tid);
+            if (l == 2 || l == 1) br_issue<kW * kRrRow>(SW, WrT + (size_t)(l - 1) * kW * kRrRow, wv, lane);
+            else if (l == 0) br_issue<kW * kRrRow0>(SW, Wr, wv, lane);
             if (l == 3) {
 #pragma unroll
                 for (int kc = 0; kc < kBrPts / 32; ++kc) {
                     const bf16x8 a = *(const bf16x8 *)(XD + lc * kBrStride + 32 * kc + 8 * lg);
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const bf16x8 b = *(const bf16x8 *)(XH + (16 * (wv + 4 * q) + lc) * kBrStride + 32 * kc + 8 * lg);
-                        g4[q][0] = mfma_bf16(a, b, g4[q][0]);
-                    }
+                    const bf16x8 b = *(const bf16x8 *)(XH + (16 * wv + lc) * kBrStride + 32 * kc + 8 * lg);
+                    g4 = mfma_bf16(a, b, g4);
                 }
-                if (wv == 0) {
-                    const float v = br_rowsum(XD, lane >> 1, bhalf);   // rows 0..2 are dL/do
-                    if (lane < 6) db5 += v;
-                }
+                if (wv == 0) db5 += br_rowsum(XD, lane >> 2, bpart);   // rows 0..2 are dL/do
             } else if (l == 2) {
-                br_dw<8>(g3, XD, XH, wv, lg, lc);
-                db3 += br_rowsum(XD, brow, bhalf);
+                br_dw<4>(g3, XD, XH, pt, 4 * hf, lg, lc);
+                db3 += br_rowsum(XD, brow, bpart);
             } else if (l == 1) {
-                br_dw<8>(g2, XD, XH, wv, lg, lc);
-                db2 += br_rowsum(XD, brow, bhalf);
+                br_dw<4>(g2, XD, XH, pt, 4 * hf, lg, lc);
+                db2 += br_rowsum(XD, brow, bpart);
             } else {
-                br_dw<8>(g1, XD, XH, wv, lg, lc);
-                db1 += br_rowsum(XD, brow, bhalf);
+                br_dw<4>(g1, XD, XH, pt, 4 * hf, lg, lc);
+                db1 += br_rowsum(XD, brow, bpart);
             }
             if (l != 0) br_wait();
             __syncthreads();
-#pragma unroll
-            for (int c = 0; c < 4; ++c) dzu[c] = dz[c];
             // dL/dh' of the layer below through the transposed weights, and
             // at once its h' and dL/dz'
+            dzu[0] = dz[0];
+            dzu[1] = dz[1];
             if (l >= 1) {
                 // (the transposed weights are in SW, waited for before the
                 // barrier above)
                 const __bf16 *WT = SW;
+                bf16x8 up[4];
 #pragma unroll
-                for (int cp = 0; cp < 4; ++cp) {
-                        floatx4 acc[2] = {floatx4{0.0f, 0.0f, 0.0f, 0.0f}, floatx4{0.0f, 0.0f, 0.0f, 0.0f}};
+                for (int c = 0; c < 4; ++c) up[c] = ZP[4 * l + c][pl];
+#pragma unroll
+                for (int cq = 0; cq < 2; ++cq) {
+                    const int cp = cp0 + cq;
+                    floatx4 acc[2] = {floatx4{0.0f, 0.0f, 0.0f, 0.0f}, floatx4{0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
                             const bf16x8 a = *(const bf16x8 *)(WT + (32 * cp + 16 * h + lc) * kRrRow + 32 * c + 8 * lg);
-                            acc[h] = mfma_bf16(a, dzu[c], acc[h]);
+                            acc[h] = mfma_bf16(a, up[c], acc[h]);
                         }
-                    const bf16x8 zq = ZP[4 * (l - 1) + cp][tid];
+                    const bf16x8 zq = ZP[4 * (l - 1) + cp][pl];
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) br_act_grad(zq[4 * h + i], acc[h][i], hp[cp], dz[cp], 4 * h + i);
+                        for (int i = 0; i < 4; ++i) br_act_grad(zq[4 * h + i], acc[h][i], hp[cq], dz[cq], 4 * h + i);
                 }
             }
         }
         // ---- layer 0: features and dz'_0
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const bf16x8 f = ZP[16 + c][tid];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) XH[(32 * c + 8 * lg + j) * kBrStride + col] = f[j];
-        }
-        br_write_rows(XD, dz, lg, col);
+        const bf16x8 f = ZP[16 + hf][pl];
+        br_write8(XH + (32 * hf + 8 * lg) * kBrStride, f, lane, col, [](int j) { return j; });
+        br_write_rows(XD, dz, cp0, lane, col);
         __syncthreads();
-        br_dw<4>(g0, XD, XH, wv, lg, lc);
-        db0 += br_rowsum(XD, brow, bhalf);
-        br_wait();   // the next pass's layer-0 weights
-        __syncthreads();
+        br_dw<2>(g0, XD, XH, pt, 2 * hf, lg, lc);
+        db0 += br_rowsum(XD, brow, bpart);
+        // (the barrier after the next pass's features comes before anything
+        // writes the rows again)
     }
+    br_wait();   // layer 0's weights for a pass that does not come
     // ---- flush: flat layout per layer W [out][in] then b [out]
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int o = 32 * wv + 16 * a + 4 * lg + i;
+            const int o = 32 * pt + 16 * a + 4 * lg + i;
 #pragma unroll
-            for (int it = 0; it < 4; ++it) atomicAdd(dW + w.off[0] + o * kF + 16 * it + lc, kLog2E * g0[a][it][i]);
+            for (int it = 0; it < 2; ++it)
+                atomicAdd(dW + w.off[0] + o * kF + 16 * (2 * hf + it) + lc, kLog2E * g0[a][it][i]);
 #pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                atomicAdd(dW + w.off[1] + o * kW + 16 * it + lc, g1[a][it][i]);
-                atomicAdd(dW + w.off[2] + o * kW + 16 * it + lc, g2[a][it][i]);
-                atomicAdd(dW + w.off[3] + o * kW + 16 * it + lc, g3[a][it][i]);
+            for (int it = 0; it < 4; ++it) {
+                const int j = 16 * (4 * hf + it) + lc;
+                atomicAdd(dW + w.off[1] + o * kW + j, g1[a][it][i]);
+                atomicAdd(dW + w.off[2] + o * kW + j, g2[a][it][i]);
+                atomicAdd(dW + w.off[3] + o * kW + j, g3[a][it][i]);
             }
         }
-    if (bhalf == 0) {
+    if (bpart == 0) {
         atomicAdd(dW + w.off[0] + kW * kF + brow, kLog2E * db0);
         atomicAdd(dW + w.off[1] + kW * kW + brow, kLog2E * db1);
         atomicAdd(dW + w.off[2] + kW * kW + brow, kLog2E * db2);
         atomicAdd(dW + w.off[3] + kW * kW + brow, kLog2E * db3);
     }
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = 4 * lg + i;
-            if (j < 3) atomicAdd(dW + w.off[4] + j * kW + 16 * (wv + 4 * q) + lc, kLn2 * g4[q][0][i]);
-        }
-    if (wv == 0 && lane < 6 && bhalf == 0) atomicAdd(dW + w.off[4] + 3 * kW + (lane >> 1), db5);
+    for (int i = 0; i < 4; ++i) {
+        const int j = 4 * lg + i;
+        if (j < 3) atomicAdd(dW + w.off[4] + j * kW + 16 * wv + lc, kLn2 * g4[i]);
+    }
+    if (wv == 0 && lane < 12 && bpart == 0) atomicAdd(dW + w.off[4] + 3 * kW + (lane >> 2), db5);
 }
 
 // ---------------------------------------------------------------- register-resident FP32
@@ -799,7 +848,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // 4-deep step of the next product takes one value per lane group: step (t, i)
 // takes neurons 16 t + 4 lg + i, which is the accumulator register itself.  The
 // weights of four steps are then four consecutive values of a row, one 16-byte
-// read; rows are padded by 16 bytes against bank conflicts.  A layer's weights
+// read; rows are padded by 32 bytes as kRrRow is.  A layer's weights
 // (66 KB) go from L2 to LDS once per pass for all waves of a workgroup, issued
 // one stage ahead with loads that write LDS directly.
 //
@@ -809,12 +858,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // 5.76 -> 0.80 ms forward (65 TFLOP/s over the points that are read), 12.8 ->
 // 2.06 ms backward (one wave per SIMD: its activations, LDS rows and barriers
 // run beside nothing).
-constexpr int kFrRow0 = kF + 4, kFrRow = kW + 4;      // padded rows (floats)
+constexpr int kFrRow0 = kF + 8, kFrRow = kW + 8;      // padded rows (floats)
 constexpr size_t kFrWeightElems = (size_t)kW * kFrRow0 + 3 * (size_t)kW * kFrRow;
 constexpr int kFrTiles = 2;                           // 16-point column tiles per wave
 constexpr int kFrThreads = 512;
 constexpr int kFrQueue = 16 * kFrTiles + 64;          // points a wave holds at most
-constexpr int kFrStride = kBrPts + 4;                 // LDS row of the point-major buffers
+constexpr int kFrStride = kBrPts + 8;                 // LDS row of the point-major buffers
 constexpr int kFrSlab = 36 * 256;                     // floatx4 a workgroup parks: z of 4 layers, features
 
 __global__ void mlp_prep_fr(const float *__restrict__ flat, MlpDev w) {
@@ -1353,7 +1402,7 @@ hipError_t mlp_backward(const Geometry &g, const Shade &s, const MlpDev &w, int 
     hipLaunchKernelGGL(mlp_live_write, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks, offsets, list);
     if (precision == RT_MLP_BF16) {
         const unsigned grid = (unsigned)std::min<size_t>(passes, (size_t)ncu);
-        hipLaunchKernelGGL(mlp_bwd_rr, dim3(grid), dim3(256), 0, st, g, s, w, M, dO, list, dW);
+        hipLaunchKernelGGL(mlp_bwd_rr, dim3(grid), dim3(kBrThreads), 0, st, g, s, w, M, dO, list, dW);
     } else {
         const size_t list_b = (sizeof(uint32_t) * (1 + M + 3 * (size_t)kLiveChunks) + 255) / 256 * 256;
         hipLaunchKernelGGL(mlp_bwd_fr, dim3((unsigned)fr_bwd_groups(M)), dim3(256), 0, st, g, s, w, M, dO, list, dW,
