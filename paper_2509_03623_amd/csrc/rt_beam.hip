@@ -10,24 +10,38 @@
 //
 // beam_weights (one workgroup) evaluates the (2R+1)^2 weights in float,
 // normalises them by their workgroup-reduced sum and stores them.  beam_conv: one
-// workgroup per 64 x 32 output tile of one channel; the tile plus its R-wide
-// halo is staged in LDS (zeros outside the image) with the weights; each lane
-// forms 8 consecutive outputs of one row, sliding a window of 8 staged values
-// along each kernel row 8 taps at a time, so a tap costs one LDS read of data,
-// one broadcast read of the weight and 8 FMAs.  The 32 lanes of a half-wave take 32
-// different rows at one column, and the row pitch is odd, so their reads fall
-// in distinct banks.  The work is dense FMA, not HBM traffic: (2R+1)^2 FMAs per
-// output against 8 bytes moved.
+// workgroup per 64 x 64 output tile of one channel, compiled for each R; the
+// tile plus its halo is staged in LDS (zeros outside the image), all of a
+// lane's float4 loads in flight together, with the weights; each lane forms 8
+// consecutive outputs of two rows from the float4 of a tile row it reads once,
+// the taps and their window all in registers by constant index.
+//
+// Bound: FMA issue, (2R+1)^2 FMAs per output; with three registers read of
+// which two are often of one bank an FMA takes 3.3 cycles of the 2 it could.
+// 512^2 x 64 channels, R = 8: 109 us a call; 153 with 4-byte reads and stores
+// and the taps in a loop.  Same loop of calls, back to back: R = 3 55 (90), R = 4
+// 48 (88), R = 8 134 (175), R = 12 221 (280), R = 23 804 (1036); 150 x 133 x 40,
+// R = 8, 20 (22).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "../../include/rtcube.h"
 #include "rt_host.h"
 
 namespace rt {
 
-constexpr int kBeamTX = 64, kBeamTY = 32, kBeamOut = 8;   // tile and outputs per lane
+constexpr int kBeamOut = 8, kBeamRows = 2;                 // outputs of a lane: columns, rows
+constexpr int kBeamTX = 64, kBeamTY = 256 / (kBeamTX / kBeamOut) * kBeamRows;
+// halo left and right in whole float4; values of a tile row that a lane reads
+// (from its first column of the halo); half of the float4 of a tile row, stored
+// even ones first (a lane's outputs are two float4 wide, so that neighbouring
+// lanes then read neighbouring float4), and the row pitch in float4
+constexpr int beam_halo(int R) { return (R + 3) / 4 * 4; }
+constexpr int beam_values(int R) { return (beam_halo(R) + R + kBeamOut + 3) / 4 * 4; }
+constexpr int beam_half(int R) { return (kBeamTX / 4 + beam_halo(R) / 2 + 1) / 2; }
+constexpr int beam_pitch(int R) { return 2 * beam_half(R); }
 
 __global__ __launch_bounds__(256) void beam_weights(float *__restrict__ w, int R, float inv_smaj, float inv_smin,
                                                     float spa, float cpa) {
@@ -50,71 +64,115 @@ __global__ __launch_bounds__(256) void beam_weights(float *__restrict__ w, int R
     for (int i = threadIdx.x; i < nn; i += blockDim.x) w[i] = weight(i) * inv;
 }
 
+template <int R, bool VEC>
 __global__ __launch_bounds__(256) void beam_conv(const float *__restrict__ in, float *__restrict__ out,
-                                                 const float *__restrict__ w, int nx, int ny, int R) {
-    extern __shared__ float lds[];
-    const int n = 2 * R + 1;
-    const int W = kBeamTX + 2 * R, H = kBeamTY + 2 * R;
-    const int P = W | 1;                       // odd row pitch
-    float *tile = lds;
-    float *wk = lds + H * P;
+                                                 const float *__restrict__ w, int nx, int ny) {
+    constexpr int n = 2 * R + 1, NW = (n + 3) / 4 * 4;       // taps of a row, padded to whole float4
+    constexpr int RX = beam_halo(R), W4 = kBeamTX / 4 + RX / 2;   // a tile row in float4
+    constexpr int H = kBeamTY + 2 * R, P = beam_pitch(R), E = beam_half(R), NV = beam_values(R);
+    __shared__ float4 tile[H * P];
+    __shared__ __attribute__((aligned(16))) float wk[n * NW];
     const int x0 = blockIdx.x * kBeamTX, y0 = blockIdx.y * kBeamTY;
     const size_t plane = (size_t)nx * ny;
     const float *src = in + blockIdx.z * plane;
-    // the pad column (lx = W) is zeroed: the window's last refill reads it
-    for (int i = threadIdx.x; i < H * P; i += blockDim.x) {
-        const int ly = i / P, lx = i % P;
-        const int gy = y0 - R + ly, gx = x0 - R + lx;
-        tile[i] = (lx < W && gx >= 0 && gx < nx && gy >= 0 && gy < ny) ? src[(size_t)gy * nx + gx] : 0.0f;
+    constexpr int NL = (H * W4 + 255) / 256;                 // all loads of a lane in flight at once
+    float4 f[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = (int)threadIdx.x + 256 * k;
+        const int ly = i / W4, gy = y0 - R + ly, gx = x0 - RX + 4 * (i - ly * W4);
+        f[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (gy < 0 || gy >= ny || ly >= H) continue;
+        const float *p = src + (size_t)gy * nx;
+        if (VEC) {
+            if (gx >= 0 && gx < nx) f[k] = *(const float4 *)(p + gx);
+        } else {
+            if (gx >= 0 && gx < nx) f[k].x = p[gx];
+            if (gx >= -1 && gx < nx - 1) f[k].y = p[gx + 1];
+            if (gx >= -2 && gx < nx - 2) f[k].z = p[gx + 2];
+            if (gx >= -3 && gx < nx - 3) f[k].w = p[gx + 3];
+        }
     }
-    for (int i = threadIdx.x; i < n * n; i += blockDim.x) wk[i] = w[i];
+    for (int i = threadIdx.x; i < n * NW; i += 256) {
+        const int j = i / NW, k = i - j * NW;
+        wk[i] = k < n ? w[j * n + k] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = (int)threadIdx.x + 256 * k, ly = i / W4, c = i - ly * W4;
+        if (ly < H) tile[ly * P + (c & 1) * E + (c >> 1)] = f[k];
+    }
     __syncthreads();
-    const int ty = threadIdx.x % kBeamTY;      // lanes of a half-wave: 32 rows
-    const int tx = threadIdx.x / kBeamTY;      // 8 groups of 8 columns
-    float acc[kBeamOut];
+    constexpr int LX = kBeamTX / kBeamOut;
+    const int ty = (int)threadIdx.x / LX * kBeamRows;         // first of the lane's output rows
+    const int tx = (int)threadIdx.x % LX * kBeamOut;          // and columns
+    float acc[kBeamRows][kBeamOut];
 #pragma unroll
-    for (int q = 0; q < kBeamOut; ++q) acc[q] = 0.0f;
-    // out(y, x) = sum_{j, i} K[j][i] in(y + R - j, x + R - i) = sum K[j][i] tile[ty + 2R - j][lx + 2R - i];
-    // K is point-symmetric (K[j][i] = K[2R-j][2R-i]), so equally sum K[j][i] tile[ty + j][lx + i].
-    for (int j = 0; j < n; ++j) {
-        const float *row = tile + (ty + j) * P + tx * kBeamOut;
-        const float *kr = wk + j * n;
-        float win[kBeamOut];
+    for (int y = 0; y < kBeamRows; ++y)
 #pragma unroll
-        for (int q = 0; q < kBeamOut; ++q) win[q] = row[q];
-        int i = 0;
-        // 8 taps at a time with the next 8 values in a second window: the
-        // shifts become register renaming (row[i + 15] <= row[2R + 8], the pad)
-        for (; i + kBeamOut <= n; i += kBeamOut) {
-            float nxt[kBeamOut];
+        for (int q = 0; q < kBeamOut; ++q) acc[y][q] = 0.0f;
+    // out(y, x) = sum_{j, i} K[j][i] in(y + R - j, x + R - i); K is point-symmetric
+    // (K[j][i] = K[2R-j][2R-i]), so equally sum K[j][i] in(y - R + j, x - R + i).
+    // Row r of the tile is row j = r - y of the kernel for output row y.
+    auto row = [&](int r, auto first, auto last) {
+        float v[NV];
+        const float4 *src4 = tile + (ty + r) * P + tx / kBeamOut;
 #pragma unroll
-            for (int q = 0; q < kBeamOut; ++q) nxt[q] = row[i + kBeamOut + q];
-#pragma unroll
-            for (int t = 0; t < kBeamOut; ++t) {
-                const float k = kr[i + t];
-#pragma unroll
-                for (int q = 0; q < kBeamOut; ++q)
-                    acc[q] = fmaf(k, t + q < kBeamOut ? win[t + q] : nxt[t + q - kBeamOut], acc[q]);
-            }
-#pragma unroll
-            for (int q = 0; q < kBeamOut; ++q) win[q] = nxt[q];
+        for (int i = 0; i < NV / 4; ++i) {
+            const float4 f = src4[(i & 1) * E + (i >> 1)];
+            v[4 * i] = f.x; v[4 * i + 1] = f.y; v[4 * i + 2] = f.z; v[4 * i + 3] = f.w;
         }
-        for (; i < n; ++i) {
-            const float k = kr[i];
 #pragma unroll
-            for (int q = 0; q < kBeamOut; ++q) acc[q] = fmaf(k, win[q], acc[q]);
+        for (int y = decltype(first)::value; y <= decltype(last)::value; ++y) {
+            const float4 *k4 = (const float4 *)(wk + (r - y) * NW);
 #pragma unroll
-            for (int q = 0; q < kBeamOut - 1; ++q) win[q] = win[q + 1];
-            win[kBeamOut - 1] = row[i + kBeamOut];
+            for (int i4 = 0; i4 < NW / 4; ++i4) {
+                const float4 f = k4[i4];
+                const float k[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (4 * i4 + t < n)
+#pragma unroll
+                        for (int q = 0; q < kBeamOut; ++q) acc[y][q] = fmaf(k[t], v[RX - R + 4 * i4 + t + q], acc[y][q]);
+            }
+        }
+    };
+    constexpr std::integral_constant<int, 0> top{};
+    constexpr std::integral_constant<int, kBeamRows - 1> bottom{};
+    if constexpr (kBeamRows == 2) row(0, top, top);
+    for (int r = kBeamRows - 1; r < n; ++r) row(r, top, bottom);
+    if constexpr (kBeamRows == 2) row(n, bottom, bottom);
+#pragma unroll
+    for (int yy = 0; yy < kBeamRows; ++yy) {
+        const int y = y0 + ty + yy;
+        if (y >= ny) return;
+        float *dst = out + blockIdx.z * plane + (size_t)y * nx + x0 + tx;
+        if (VEC) {
+#pragma unroll
+            for (int q = 0; q < kBeamOut; q += 4)
+                if (x0 + tx + q < nx)
+                    *(float4 *)(dst + q) = make_float4(acc[yy][q], acc[yy][q + 1], acc[yy][q + 2], acc[yy][q + 3]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < kBeamOut; ++q)
+                if (x0 + tx + q < nx) dst[q] = acc[yy][q];
         }
     }
-    const int y = y0 + ty;
-    if (y >= ny) return;
-    float *dst = out + blockIdx.z * plane + (size_t)y * nx;
-#pragma unroll
-    for (int q = 0; q < kBeamOut; ++q) {
-        const int x = x0 + tx * kBeamOut + q;
-        if (x < nx) dst[x] = acc[q];
+}
+
+template <int R>
+static hipError_t launch_conv(const float *in, float *out, const float *w, int R_, int nch, int ny, int nx,
+                              hipStream_t st) {
+    if constexpr (R > RT_BEAM_MAX_RADIUS) {
+        return hipErrorInvalidValue;
+    } else {
+        if (R_ != R) return launch_conv<R + 1>(in, out, w, R_, nch, ny, nx, st);
+        const dim3 grid((nx + kBeamTX - 1) / kBeamTX, (ny + kBeamTY - 1) / kBeamTY, nch);
+        // rows of whole, aligned float4: every float4 of the tile is inside or outside as a whole
+        const bool vec = nx % 4 == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
+        if (vec) hipLaunchKernelGGL((beam_conv<R, true>), grid, dim3(256), 0, st, in, out, w, nx, ny);
+        else hipLaunchKernelGGL((beam_conv<R, false>), grid, dim3(256), 0, st, in, out, w, nx, ny);
+        return hipGetLastError();
     }
 }
 
@@ -170,10 +228,6 @@ extern "C" rt_status rt_beam_convolve(const float *in, float *out, int32_t nch, 
     hipLaunchKernelGGL(beam_weights, dim3(1), dim3(256), 0, st, w, R, (float)(1.0 / smaj), (float)(1.0 / smin),
                        (float)std::sin(pa), (float)std::cos(pa));
     if ((e = hipGetLastError()) != hipSuccess) return fail_hip(e, "beam weights launch");
-    const int W = kBeamTX + 2 * R, H = kBeamTY + 2 * R, P = W | 1;
-    const size_t lds = sizeof(float) * ((size_t)H * P + (size_t)n * n);
-    dim3 grid((nx + kBeamTX - 1) / kBeamTX, (ny + kBeamTY - 1) / kBeamTY, nch);
-    hipLaunchKernelGGL(beam_conv, grid, dim3(256), lds, st, in, out, w, nx, ny, R);
-    if ((e = hipGetLastError()) != hipSuccess) return fail_hip(e, "beam convolution launch");
+    if ((e = launch_conv<1>(in, out, w, R, nch, ny, nx, st)) != hipSuccess) return fail_hip(e, "beam convolution launch");
     return RT_OK;
 }
