@@ -41,8 +41,9 @@ class Server:
         rq.cube = _fptr(cube)
         rq.target = _fptr(target)
         g = grads or {}
-        rq.grads = L.rt_grads(_fptr(g.get("ln_nh2")), _fptr(g.get("temp_k")), _fptr(g.get("vphi_kms")),
-                              _fptr(g.get("z_lo_au")), _fptr(g.get("z_up_au")), _fptr(g.get("mlp_w")))
+        if g:                                  # (the struct starts as NULLs)
+            rq.grads = L.rt_grads(_fptr(g.get("ln_nh2")), _fptr(g.get("temp_k")), _fptr(g.get("vphi_kms")),
+                                  _fptr(g.get("z_lo_au")), _fptr(g.get("z_up_au")), _fptr(g.get("mlp_w")))
         if beam is not None:
             rq.beam = L.rt_beam(*(float(v) for v in beam))
         t = C.c_uint64()
