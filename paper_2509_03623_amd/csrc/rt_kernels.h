@@ -232,10 +232,10 @@ __device__ __forceinline__ Locus locate(const Shade &s, float px, float py, floa
     Locus L;
     const float rho2 = px * px + py * py;
     const bool on = rho2 > 0.0f;
-    L.inv_rho = on ? frsq(rho2) : 0.0f;
-    L.rho = rho2 * L.inv_rho;
+    L.rho = fsqrt(rho2);
+    L.inv_rho = on ? frcp(L.rho) : 0.0f;
     L.az = fabsf(pz);
-    float u = fmaf(0.5f, flog2(rho2), -s.log2_rmin) * s.u_scale;
+    float u = (flog2(L.rho) - s.log2_rmin) * s.u_scale;
     float v = L.az * L.inv_rho * s.inv_dzr;
     u = on ? u : -2.0f;
     v = on ? v : 0.0f;
