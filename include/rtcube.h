@@ -454,7 +454,13 @@ int32_t rt_abi_version(void);
  * ([host] out[n]); returns how many exist. */
 int32_t rt_constants(double *out, int32_t n);
 
-/* Tuning knobs (process-wide).  RT_OPT_CHANNEL_BLOCK: channels per lane of
+/* Tuning knobs (process-wide).  The marches go over line windows (only the
+ * channels whose depth at a sample is not 0 in float) unless one of their
+ * shapes is chosen here: RT_OPT_CHANNEL_BLOCK, RT_OPT_RAY_SPLIT,
+ * RT_OPT_FWD_GROUP or RT_OPT_THIN_EXPM1 0 for the forward march (the first
+ * two also for the 3-D one), RT_OPT_CKPT_SEGMENT, RT_OPT_ADJ_CHANNEL_BLOCK or
+ * RT_OPT_ADJ_PIXEL_LANES for the reverse march; the automatic values below are
+ * those of the marches so chosen.  RT_OPT_CHANNEL_BLOCK: channels per lane of
  * the forward march (8, 16, 24, 32, 48 or 64; 0 = automatic).
  * RT_OPT_THIN_EXPM1: 1 (default) evaluates 1 - e^-dtau of rt_render_cube's
  * march from its series on samples whose line-centre depth is small (below
@@ -476,7 +482,8 @@ int32_t rt_constants(double *out, int32_t n);
  * march, each taking a consecutive sub-chord (1, 2, 4 or 8; 0 = automatic).
  * RT_OPT_GRAD_ACCUM: 0 (default) accumulates the gradients of the adjoint
  * (per-workgroup partials in LDS, then atomics into one accumulator per node)
- * in float, 1 in double; the partials are float either way.  RT_OPT_ADJ_SCRATCH_CAP: bytes of adjoint
+ * in float, 1 in double; the partials are double for the most visited
+ * rows and the surfaces, float for the rest, either way.  RT_OPT_ADJ_SCRATCH_CAP: bytes of adjoint
  * scratch (sample tape, transmission checkpoints, cotangents) per pass; an
  * image whose scratch exceeds it is differentiated in bands of whole pixel
  * rows, at least one row per band (0 = default, 8 GiB).  The library keeps
