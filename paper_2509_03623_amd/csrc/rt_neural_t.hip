@@ -17,6 +17,7 @@
 // (deterministic).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "../../include/rtcube.h"
@@ -57,24 +58,51 @@ __device__ __forceinline__ void node_features(int n, int nr, int nz, float *f) {
         }
 }
 
-// LDS: per layer l the transposed weights WT_l [in][out] then b_l (forward),
+// LDS: per layer l the transposed weights WT_l [in][kNtRow] then b_l (forward),
 // or W_l [out][in] (backward); then two activation buffers [64][kNtNodes].
+// Rows of WT are 4 floats longer than the 64 outputs: neighbouring lanes write
+// neighbouring rows, which would all fall in one bank.
+constexpr int kNtRow = kNtW + 4;
+constexpr int fwd_off(int l) {
+    int o = 0;
+    for (int k = 0; k < l; ++k) o += layer_in(k) * kNtRow + kNtW;
+    return o;
+}
+// all weights and biases; the output unit's row as it is
+constexpr int kNtFwdFloats = fwd_off(4) + kNtW + 1;
+
+// A lane's loads are all in flight together.  With them one after another and
+// 64-float rows of WT nt_fwd took 70 us at 256 x 128 nodes, now 39 (what is
+// left: broadcast reads of the weights, four of 16 bytes per 16 FMAs).
 __device__ __forceinline__ void stage_weights(const float *W, float *sw, bool transposed) {
-    for (int p = threadIdx.x; p < RT_NT_PARAMS; p += blockDim.x) {
-        int l = 0;
-        while (l < 4 && p >= layer_off(l + 1)) ++l;
-        const int q = p - layer_off(l), in = layer_in(l), out = layer_out(l);
+    constexpr int NP = (RT_NT_PARAMS + kNtBlock - 1) / kNtBlock;
+    float v[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int p = (int)threadIdx.x + i * kNtBlock;
+        v[i] = W[p < RT_NT_PARAMS ? p : 0];
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int p = (int)threadIdx.x + i * kNtBlock;
+        if (p >= RT_NT_PARAMS) continue;
         int dst = p;
-        if (transposed && q < in * out) {
-            const int a = q / in, b = q - a * in;     // W[a][b]
-            dst = layer_off(l) + b * out + a;         // WT[b][a]
+        if (transposed) {
+            int l = 0;
+            while (l < 4 && p >= layer_off(l + 1)) ++l;
+            const int q = p - layer_off(l), in = l == 0 ? kNtIn : kNtW;
+            dst = fwd_off(l) + q;                             // the output unit's weights and bias
+            if (l < 4) {
+                const int a = q / in, b = q - a * in;         // W[a][b]
+                dst = fwd_off(l) + (q < in * kNtW ? b * kNtRow + a : q - in * kNtW + in * kNtRow);
+            }
         }
-        sw[dst] = W[p];
+        sw[dst] = v[i];
     }
 }
 
 // one dense layer, this lane's slice of outputs a = 16 q + c of node column
-// j: out[a] = act(sum_b W[a][b] in[b] + b[a]), with WT [in][out] in LDS; the
+// j: out[a] = act(sum_b W[a][b] in[b] + b[a]), with WT [in][kNtRow] in LDS; the
 // slice is also left in acc
 template <int IN, bool RELU>
 __device__ __forceinline__ void dense_slice(const float *wt, const float *bias, const float *hin, float *hout, int j,
@@ -85,7 +113,7 @@ __device__ __forceinline__ void dense_slice(const float *wt, const float *bias, 
     for (int b = 0; b < IN; ++b) {
         const float h = hin[b * kNtNodes + j];
 #pragma unroll
-        for (int c = 0; c < kNtSlice; ++c) acc[c] = fmaf(wt[b * kNtW + q * kNtSlice + c], h, acc[c]);
+        for (int c = 0; c < kNtSlice; ++c) acc[c] = fmaf(wt[b * kNtRow + q * kNtSlice + c], h, acc[c]);
     }
 #pragma unroll
     for (int c = 0; c < kNtSlice; ++c) {
@@ -98,7 +126,7 @@ __device__ __forceinline__ void dense_slice(const float *wt, const float *bias, 
 __global__ __launch_bounds__(kNtBlock) void nt_fwd(int nr, int nz, const float *__restrict__ W,
                                                    float *__restrict__ T, float *__restrict__ act) {
     extern __shared__ float sm[];
-    float *sw = sm, *h0 = sm + RT_NT_PARAMS, *h1 = h0 + kNtW * kNtNodes;
+    float *sw = sm, *h0 = sm + kNtFwdFloats, *h1 = h0 + kNtW * kNtNodes;
     stage_weights(W, sw, true);
     const int N = nr * nz, t = threadIdx.x, j = t % kNtNodes;
     const int q = __builtin_amdgcn_readfirstlane(t / kNtNodes);
@@ -116,13 +144,13 @@ __global__ __launch_bounds__(kNtBlock) void nt_fwd(int nr, int nz, const float *
     __syncthreads();
     float acc[kNtSlice];
     // hidden layer l reads one buffer and writes the other; act rows 16 + 64 l + a
-    dense_slice<kNtIn, true>(sw + layer_off(0), sw + layer_off(0) + kNtIn * kNtW, h0, h1, j, q, acc);
+    dense_slice<kNtIn, true>(sw + fwd_off(0), sw + fwd_off(0) + kNtIn * kNtRow, h0, h1, j, q, acc);
     if (store)
         for (int c = 0; c < kNtSlice; ++c) act[(size_t)(kNtIn + q * kNtSlice + c) * N + n] = acc[c];
     __syncthreads();
     float *hin = h1, *hout = h0;
     for (int l = 1; l < 4; ++l) {
-        dense_slice<kNtW, true>(sw + layer_off(l), sw + layer_off(l) + kNtW * kNtW, hin, hout, j, q, acc);
+        dense_slice<kNtW, true>(sw + fwd_off(l), sw + fwd_off(l) + kNtW * kNtRow, hin, hout, j, q, acc);
         if (store)
             for (int c = 0; c < kNtSlice; ++c)
                 act[(size_t)(kNtIn + l * kNtW + q * kNtSlice + c) * N + n] = acc[c];
@@ -133,7 +161,7 @@ __global__ __launch_bounds__(kNtBlock) void nt_fwd(int nr, int nz, const float *
     }
     // output unit (one lane per node): o = b_4 + sum_b W_4[0][b] h_4[b]
     if (q == 0) {
-        const float *w4 = sw + layer_off(4);
+        const float *w4 = sw + fwd_off(4);
         float o = w4[kNtW];
         for (int b = 0; b < kNtW; ++b) o = fmaf(w4[b], hin[b * kNtNodes + j], o);
         if (n < N) {
@@ -161,10 +189,15 @@ __global__ __launch_bounds__(kNtBlock) void nt_delta(int N, const float *__restr
     if (q == 0 && n < N) delta[(size_t)(kDeltaRows - 1) * N + n] = dlo;
     // dL/dz_4 = W_4^T dL/do masked by h_4 > 0
     const float *w4 = sw + layer_off(4);
+    // the masking activations, read ahead of their use (with the staged weights
+    // 83 -> 37 us at 256 x 128 nodes)
+    float hv[kNtSlice];
+#pragma unroll
+    for (int c = 0; c < kNtSlice; ++c) hv[c] = act[(size_t)(kNtIn + 3 * kNtW + q * kNtSlice + c) * N + nn];
+#pragma unroll
     for (int c = 0; c < kNtSlice; ++c) {
         const int a = q * kNtSlice + c;
-        const float h = act[(size_t)(kNtIn + 3 * kNtW + a) * N + nn];
-        const float v = h > 0.0f ? w4[a] * dlo : 0.0f;
+        const float v = hv[c] > 0.0f ? w4[a] * dlo : 0.0f;
         d0[a * kNtNodes + j] = v;
         if (n < N) delta[(size_t)(3 * kNtW + a) * N + n] = v;
     }
@@ -175,7 +208,10 @@ __global__ __launch_bounds__(kNtBlock) void nt_delta(int N, const float *__restr
         const float *wl = sw + layer_off(l);   // W_l [out][in]
         float acc[kNtSlice];
 #pragma unroll
-        for (int c = 0; c < kNtSlice; ++c) acc[c] = 0.0f;
+        for (int c = 0; c < kNtSlice; ++c) {
+            acc[c] = 0.0f;
+            hv[c] = act[(size_t)(kNtIn + (l - 1) * kNtW + q * kNtSlice + c) * N + nn];
+        }
 #pragma unroll 4
         for (int a = 0; a < kNtW; ++a) {
             const float g = cur[a * kNtNodes + j];
@@ -185,8 +221,7 @@ __global__ __launch_bounds__(kNtBlock) void nt_delta(int N, const float *__restr
 #pragma unroll
         for (int c = 0; c < kNtSlice; ++c) {
             const int b = q * kNtSlice + c;
-            const float h = act[(size_t)(kNtIn + (l - 1) * kNtW + b) * N + nn];
-            const float v = h > 0.0f ? acc[c] : 0.0f;
+            const float v = hv[c] > 0.0f ? acc[c] : 0.0f;
             nxt[b * kNtNodes + j] = v;
             if (n < N) delta[(size_t)((l - 1) * kNtW + b) * N + n] = v;
         }
@@ -208,10 +243,24 @@ __global__ __launch_bounds__(256) void nt_wgrad(int N, const float *__restrict__
     __shared__ float sA[kNtW][kNtChunk + 1], sB[kNtW][kNtChunk + 1];
     const int l = blockIdx.y, M = layer_out(l), K = layer_in(l);
     const int n0 = blockIdx.x * kNtChunk, t = threadIdx.x;
-    for (int idx = t; idx < kNtW * kNtChunk; idx += 256) {
-        const int r = idx / kNtChunk, k = idx - r * kNtChunk, n = n0 + k;
-        if (r < M) sA[r][k] = n < N ? delta[(size_t)(l == 4 ? kDeltaRows - 1 : l * kNtW + r) * N + n] : 0.0f;
-        if (r < K) sB[r][k] = n < N ? act[(size_t)(l == 0 ? r : kNtIn + (l - 1) * kNtW + r) * N + n] : 0.0f;
+    // eight rows' loads of a lane in flight at a time (84 -> 61 us at 256 x 128
+    // nodes; sixteen or all of them: the same)
+    constexpr int kRows = kNtW * kNtChunk / 256, kBatch = 8;
+    const int k = t % kNtChunk, n = n0 + k;
+    for (int i0 = 0; i0 < kRows; i0 += kBatch) {
+        float va[kBatch], vb[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const int r = (t + (i0 + i) * 256) / kNtChunk;
+            va[i] = r < M && n < N ? delta[(size_t)(l == 4 ? kDeltaRows - 1 : l * kNtW + r) * N + n] : 0.0f;
+            vb[i] = r < K && n < N ? act[(size_t)(l == 0 ? r : kNtIn + (l - 1) * kNtW + r) * N + n] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const int r = (t + (i0 + i) * 256) / kNtChunk;
+            if (r < M) sA[r][k] = va[i];
+            if (r < K) sB[r][k] = vb[i];
+        }
     }
     __syncthreads();
     float *out = partial + (size_t)blockIdx.x * RT_NT_PARAMS + layer_off(l);
@@ -308,7 +357,7 @@ rt_status validate_nt_grid(const rt_grid *g) {
     return RT_OK;
 }
 
-constexpr size_t kNtLds = sizeof(float) * (RT_NT_PARAMS + 2 * kNtW * kNtNodes);
+constexpr size_t kNtLds = sizeof(float) * (std::max(RT_NT_PARAMS, kNtFwdFloats) + 2 * kNtW * kNtNodes);
 
 hipError_t nt_lds_attr() {
     hipError_t e = hipFuncSetAttribute((const void *)nt_fwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNtLds);
