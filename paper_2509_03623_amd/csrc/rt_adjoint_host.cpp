@@ -30,11 +30,16 @@ static bool adjoint_windows() {
 // fewer than 2048 waves.  A second block halves the registers but writes and
 // adds a second slice of cotangents: 512^2 x 64 x 512 4.62 against 4.96 ms,
 // 256^2 x 48 x 256 0.70 against 0.84, but 96^2 x 64 x 256 0.38 against 0.35.
+// Channels per lane in steps of two from 8 on: 14 keep four waves a SIMD where
+// 16 leave three, 10 five where 12 leave four (54 channels at 512^2 x 512 1.67
+// against 1.78 ms, 40 at 256^2 x 256 0.53 against 0.55).
 void adjoint_shape(int nch, long npix, bool cube, int *cb, int *lanes, int *kseg) {
     if (adjoint_windows()) {
         int nblk = (nch + 63) / 64;
         if ((npix + 15) / 16 * nblk < 2048) nblk = (nch + 31) / 32;
-        *cb = std::min(16, ((nch + 4 * nblk - 1) / (4 * nblk) + 3) / 4 * 4);
+        const int most = (nch + 4 * nblk - 1) / (4 * nblk);
+        for (int c : {4, 8, 10, 12, 14, 16})
+            if (most <= c || c == 16) { *cb = c; break; }
         *lanes = kLanesPerPixel;
         *kseg = 0;
         return;

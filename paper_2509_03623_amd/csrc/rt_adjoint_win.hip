@@ -282,7 +282,9 @@ hipError_t launch_adj_march_win(int cb, int nsamp, int nx, int ny, int plane, co
     switch (cb) {
     case 4: return launch_win_t<4>(nsamp, nx, ny, plane, ch, win, uniform, tape, span, dl, target, cot, cube_out, st);
     case 8: return launch_win_t<8>(nsamp, nx, ny, plane, ch, win, uniform, tape, span, dl, target, cot, cube_out, st);
+    case 10: return launch_win_t<10>(nsamp, nx, ny, plane, ch, win, uniform, tape, span, dl, target, cot, cube_out, st);
     case 12: return launch_win_t<12>(nsamp, nx, ny, plane, ch, win, uniform, tape, span, dl, target, cot, cube_out, st);
+    case 14: return launch_win_t<14>(nsamp, nx, ny, plane, ch, win, uniform, tape, span, dl, target, cot, cube_out, st);
     case 16: return launch_win_t<16>(nsamp, nx, ny, plane, ch, win, uniform, tape, span, dl, target, cot, cube_out, st);
     default: return hipErrorInvalidValue;
     }

@@ -202,3 +202,9 @@ def test_channel_far_from_every_line():
     prob = synth.small_problem(nx=12, ny=12, nch=24, nsamp=40, nr=48, nz=24, seed=37)
     got = gpu_cube(prob.replace(v_kms=np.linspace(5e3, 5e6, 24)))
     assert np.all(got == 0.0)
+
+
+# one channel block of 10, 12, 14 or 16 a lane: the ends and one more
+@pytest.mark.parametrize("nch,order", [(40, "uneven"), (41, ""), (49, "falling"), (56, "uneven"), (57, "")])
+def test_reverse_march_block_ends(nch, order):
+    test_reverse_march(182, 181, nch, order)
