@@ -14,8 +14,14 @@ struct GradAcc {
 
 hipError_t zero_async(float *p, size_t n, hipStream_t st);
 hipError_t zero_async_d(double *p, size_t n, hipStream_t st);
-hipError_t to_float_async(const double *src, float *dst, size_t n, hipStream_t st);
-hipError_t copy_float_async(const float *src, float *dst, size_t n, hipStream_t st);
+// accumulators (double or float by option, at the offsets of doubles) and where they go (null: not asked for)
+struct GradCopy {
+    static constexpr int kCount = 5;
+    const double *src[kCount];
+    float *dst[kCount];
+    size_t n[kCount];
+};
+hipError_t launch_grad_copy(const GradCopy &o, hipStream_t st);
 // tape [nsamp][npix], ray records [npix], and each ray's run of samples with
 // K > 0 as span [npix] = (nsamp - first, last + 1), (0, 0) when it has none;
 // span_only: the tape holds valid entries only inside each ray's run (when

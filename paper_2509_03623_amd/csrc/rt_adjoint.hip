@@ -633,15 +633,15 @@ __global__ void fill_zero_d(double *p, size_t n) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0.0;
 }
 
-__global__ void to_float(const double *src, float *dst, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+// The accumulators (of type A, at the offsets of doubles) into the requested
+// outputs, one launch for all (a launch each took 4.5 us, whatever the size).
+template <typename A> __global__ void grad_copy(GradCopy o) {
+    const int k = blockIdx.y;
+    float *dst = o.dst[k];
+    if (!dst) return;
+    const A *src = (const A *)o.src[k];
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < o.n[k]; i += (size_t)gridDim.x * blockDim.x)
         dst[i] = (float)src[i];
-}
-
-// field accumulators held as float: copy them out (same layout as double)
-__global__ void copy_float(const float *src, float *dst, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        dst[i] = src[i];
 }
 
 hipError_t zero_async_d(double *p, size_t n, hipStream_t st) {
@@ -651,17 +651,14 @@ hipError_t zero_async_d(double *p, size_t n, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t copy_float_async(const float *src, float *dst, size_t n, hipStream_t st) {
-    if (!dst || n == 0) return hipSuccess;
-    const int blocks = (int)std::min<size_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(copy_float, dim3(blocks), dim3(256), 0, st, src, dst, n);
-    return hipGetLastError();
-}
-
-hipError_t to_float_async(const double *src, float *dst, size_t n, hipStream_t st) {
-    if (!dst || n == 0) return hipSuccess;
-    const int blocks = (int)std::min<size_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(to_float, dim3(blocks), dim3(256), 0, st, src, dst, n);
+hipError_t launch_grad_copy(const GradCopy &o, hipStream_t st) {
+    size_t most = 0;
+    for (int k = 0; k < GradCopy::kCount; ++k)
+        if (o.dst[k]) most = std::max(most, o.n[k]);
+    if (most == 0) return hipSuccess;
+    const dim3 grid((unsigned)std::min<size_t>((most + 255) / 256, 4096), GradCopy::kCount);
+    if (grad_accum_double()) hipLaunchKernelGGL(grad_copy<double>, grid, dim3(256), 0, st, o);
+    else hipLaunchKernelGGL(grad_copy<float>, grid, dim3(256), 0, st, o);
     return hipGetLastError();
 }
 

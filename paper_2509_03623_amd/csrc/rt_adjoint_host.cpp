@@ -215,17 +215,10 @@ rt_status adjoint_core(const rt_problem *p, const float *dl, const rt_grads *g, 
             if (e != hipSuccess) return fail_hip(e, "adjoint chain");
         }
     }
-    // accumulators are double or float (option), at the offsets of the double layout
-    auto acc_out = [&](size_t off, float *dst, size_t n) {
-        return grad_accum_double() ? to_float_async(ab + off, dst, n, st)
-                                   : copy_float_async((const float *)(ab + off), dst, n, st);
-    };
-    if ((e = acc_out(0, g->d_ln_nh2, nn)) != hipSuccess ||
-        (e = acc_out(nn, g->d_temp_k, nn)) != hipSuccess ||
-        (e = acc_out(2 * nn, g->d_vphi_kms, nn)) != hipSuccess ||
-        (e = acc_out(3 * nn, g->d_z_lo_au, nr)) != hipSuccess ||
-        (e = acc_out(3 * nn + nr, g->d_z_up_au, nr)) != hipSuccess)
-        return fail_hip(e, "gradient output");
+    const GradCopy out{{ab, ab + nn, ab + 2 * nn, ab + 3 * nn, ab + 3 * nn + nr},
+                       {g->d_ln_nh2, g->d_temp_k, g->d_vphi_kms, g->d_z_lo_au, g->d_z_up_au},
+                       {(size_t)nn, (size_t)nn, (size_t)nn, (size_t)nr, (size_t)nr}};
+    if ((e = launch_grad_copy(out, st)) != hipSuccess) return fail_hip(e, "gradient output");
     return RT_OK;
 }
 

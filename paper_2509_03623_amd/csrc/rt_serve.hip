@@ -192,14 +192,26 @@ __global__ __launch_bounds__(256) void l2_loss(const float *__restrict__ cube, c
 
 __global__ void zero_double(double *p) { *p = 0.0; }
 
-// L = sum (cube - target)^2 (double atomics)
-__global__ __launch_bounds__(256) void l2_value(const float *__restrict__ cube, const float *__restrict__ target,
-                                                size_t n, double *__restrict__ loss) {
+// sum (cube - target)^2 over the elements of a grid of blocks in x, added to
+// *loss by one double atomic a block; four loads of each array in flight a lane
+__device__ __forceinline__ void l2_sum(const float *__restrict__ cube, const float *__restrict__ target, size_t n,
+                                       double *__restrict__ loss) {
     __shared__ double part[256];
+    const size_t step = (size_t)gridDim.x * 256;
     double acc = 0.0;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const double r = (double)cube[i] - (double)target[i];
-        acc += r * r;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 4 * step) {
+        float c[4], t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool on = i + k * step < n;
+            c[k] = on ? cube[i + k * step] : 0.0f;
+            t[k] = on ? target[i + k * step] : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double r = (double)c[k] - (double)t[k];
+            acc += r * r;
+        }
     }
     part[threadIdx.x] = acc;
     __syncthreads();
@@ -210,9 +222,17 @@ __global__ __launch_bounds__(256) void l2_value(const float *__restrict__ cube, 
     if (threadIdx.x == 0) atomicAdd(loss, part[0]);
 }
 
+__global__ __launch_bounds__(256) void l2_value(const float *__restrict__ cube, const float *__restrict__ target,
+                                                size_t n, double *__restrict__ loss) {
+    l2_sum(cube, target, n, loss);
+}
+
 hipError_t launch_l2_value(const float *cube, const float *target, size_t n, double *loss, hipStream_t st) {
     hipLaunchKernelGGL(zero_double, dim3(1), dim3(1), 0, st, loss);
-    const int blocks = (int)std::min<size_t>((n + 255) / 256, 2048);
+    // the blocks' additions to one address queue up (about 10 ns each): a block
+    // for every 24 elements a lane, at most 1024.  256^2 x 48 (us): 2048 blocks
+    // 29, 1024 18, 512 14.5, 256 17; 512^2 x 64: 46, 41, 54, 93.
+    const int blocks = (int)std::min<size_t>((n + 255) / 256, std::clamp<size_t>(n / (256 * 24), 256, 1024));
     hipLaunchKernelGGL(l2_value, dim3(blocks), dim3(256), 0, st, cube, target, n, loss);
     return hipGetLastError();
 }
@@ -226,25 +246,14 @@ __global__ void zero_doubles(double *p, int n) {
 __global__ __launch_bounds__(256) void l2_batch(const ServeDesc *__restrict__ descs) {
     const ServeDesc &D = descs[blockIdx.y];
     if (!D.target) return;
-    __shared__ double part[256];
-    const size_t n = (size_t)D.nch * D.g.nx * D.g.ny;
-    double acc = 0.0;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const double r = (double)D.cube[i] - (double)D.target[i];
-        acc += r * r;
-    }
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicAdd(D.loss, part[0]);
+    l2_sum(D.cube, D.target, (size_t)D.nch * D.g.nx * D.g.ny, D.loss);
 }
 
 hipError_t launch_l2_batch(const ServeDesc *descs, int nreq, double *losses, size_t max_n, hipStream_t st) {
     hipLaunchKernelGGL(zero_doubles, dim3(1), dim3(256), 0, st, losses, nreq);
-    const int blocks = (int)std::min<size_t>((max_n + 255) / 256, 256);
+    // (64 blocks a request: 50 us a launch of 60 walkers' requests of 128^2 x 32
+    // on average, 128 blocks 56, 256 blocks 79: their additions queue up)
+    const int blocks = (int)std::min<size_t>((max_n + 255) / 256, 64);
     hipLaunchKernelGGL(l2_batch, dim3(blocks, nreq), dim3(256), 0, st, descs);
     return hipGetLastError();
 }
