@@ -45,6 +45,7 @@ hipError_t launch_adj_chain(const Geometry &g, const Shade &s, const float4 *ray
                             int nblk, const GradAcc &go, float4 *dO, hipStream_t st);
 bool chain_lds_fits(int nr, int nz);
 hipError_t launch_adj_chain_lds(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, float4 *cot,
-                                int nblk, const GradAcc &go, float4 *dO, hipStream_t st);
+                                int nblk, const GradAcc &go, float4 *dO, float *spare,
+                                hipStream_t st);
 
 } // namespace rt

@@ -377,12 +377,13 @@ struct FieldLds {
 // which it has consumed: (dL/dT at the sample, the cell's first node as
 // integer bits, the two bilinear weights), zero where there is none; the
 // second pass (adj_chain_lds_stored) then adds those into the T gradient
-// without shading the sample again.
+// without shading the sample again.  With vterm it leaves the v_phi term
+// there as well, for a third pass over the same nodes and weights.
 template <int FIELD, bool FIRST, typename A, bool STORE = false>
 __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade s, const float4 *__restrict__ rays,
                                                      const int2 *__restrict__ span, float4 *__restrict__ cot,
                                                      int nblk, GradAcc go, float4 *__restrict__ dO, int w0,
-                                                     int win) {
+                                                     int win, float *__restrict__ vterm) {
     // [2 nr] surfaces (FIRST), then the field's doubles and floats
     extern __shared__ double dyn[];
     __shared__ float4 ztab[kZTableNodes - 1];
@@ -433,6 +434,7 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
         if (FIRST && !STORE && nblk > 1 && in_run) cot[(size_t)k * npix + pix] = c;
         float4 dout = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         float4 tterm = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // STORE: the sample's T term
+        float vt = 0.0f;                                       // and its v_phi term
         if (r.w > 0.0f && (c.x != 0.0f || c.y != 0.0f || c.z != 0.0f || c.w != 0.0f)) {
             const float ds = r.w;
             const float t = ((float)k + 0.5f - 0.5f * (float)g.nsamp) * ds;
@@ -470,6 +472,7 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
                 }
             }
             if (FIELD == 2) gv = ga * q.b * tp.vfac;
+            if (STORE) vt = ga * q.b * tp.vfac;
             const float fu = L.fu, fv = L.fv;
             if (FIELD < 3 && gv != 0.0f) field.scatter(L.i0, L.j0, gv, fu, fv);
             if (FIRST && !s.mlp_o) {
@@ -486,7 +489,10 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
             }
         }
         if (FIRST && dO && pix < npix) dO[o_index(s, k, pix)] = dout;
-        if (STORE && in_run) cot[(size_t)k * npix + pix] = tterm;
+        if (STORE && in_run) {
+            cot[(size_t)k * npix + pix] = tterm;
+            if (vterm) vterm[(size_t)k * npix + pix] = vt;
+        }
         in_run = in_next;
         r = r_next;
         c = c_next;
@@ -501,12 +507,14 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
         }
 }
 
-// The temperature pass from the terms a STORE first pass left in slice 0
-// of the cotangents: no shading, only the bilinear scatter into the grid in
-// LDS and one flush, in the first pass's order of the samples.
-template <typename A>
+// The temperature pass (VPHI: that of v_phi) from the terms a STORE first pass
+// left in slice 0 of the cotangents (and in vterm): no shading, only the
+// bilinear scatter into the grid in LDS and one flush, in the first pass's
+// order of the samples.
+template <typename A, bool VPHI>
 __global__ __launch_bounds__(kChainThreads) void adj_chain_lds_stored(Geometry g, Shade s, const int2 *__restrict__ span,
-                                                             const float4 *__restrict__ cot, GradAcc go, int w0,
+                                                             const float4 *__restrict__ cot,
+                                                             const float *__restrict__ vterm, GradAcc go, int w0,
                                                              int win) {
     extern __shared__ double dyn[];
     const FieldLds field{dyn, (float *)(dyn + win * s.nz), s.nr, s.nz, w0, win};
@@ -531,8 +539,10 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds_stored(Geometry g
         for (int i = 0; i < NI; ++i) {
             const int2 run = span_of(ks[i], g.nsamp);
             t[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (pix[i] < npix && k[i] < g.nsamp && k[i] >= run.x && k[i] <= run.y)
+            if (pix[i] < npix && k[i] < g.nsamp && k[i] >= run.x && k[i] <= run.y) {
                 t[i] = cot[(size_t)k[i] * npix + pix[i]];
+                if (VPHI) t[i].x = vterm[(size_t)k[i] * npix + pix[i]];
+            }
         }
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -542,7 +552,7 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds_stored(Geometry g
             }
     }
     __syncthreads();
-    field.flush((A *)go.temp);
+    field.flush((A *)(VPHI ? go.vphi : go.temp));
 }
 
 // largest dynamic LDS the privatised chain may use (the LDS of a CU, less
@@ -567,7 +577,8 @@ static void chain_window(const Geometry &g, const Shade &s, size_t bytes, int *w
 
 template <int FIELD, bool FIRST, typename A, bool STORE = false>
 static hipError_t launch_chain_lds_t(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, float4 *cot,
-                                     int nblk, const GradAcc &go, float4 *dO, int nwg, hipStream_t st) {
+                                     int nblk, const GradAcc &go, float4 *dO, int nwg, hipStream_t st,
+                                     float *vterm = nullptr) {
     const size_t sb = FIRST ? 2 * (size_t)s.nr * sizeof(double) : 0;
     int w0 = 0, win = 0;
     if (FIELD < 3) chain_window(g, s, kChainLdsMax - sb, &w0, &win);
@@ -576,40 +587,52 @@ static hipError_t launch_chain_lds_t(const Geometry &g, const Shade &s, const fl
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)(fb + sb));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((adj_chain_lds<FIELD, FIRST, A, STORE>), dim3(nwg), dim3(kChainThreads), fb + sb, st, g, s, rays,
-                       span, cot, nblk, go, dO, w0, win);
+                       span, cot, nblk, go, dO, w0, win, vterm);
     return hipGetLastError();
 }
 
+template <typename A, bool VPHI>
+static hipError_t launch_chain_stored(const Geometry &g, const Shade &s, const int2 *span, const float4 *cot,
+                                      const float *vterm, const GradAcc &go, int nwg, hipStream_t st) {
+    int w0, win;
+    chain_window(g, s, 160 * 1024 - 1024, &w0, &win);
+    const size_t fb = sizeof(float) * (size_t)s.nz * (s.nr + win);
+    const hipError_t e = hipFuncSetAttribute((const void *)adj_chain_lds_stored<A, VPHI>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)fb);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((adj_chain_lds_stored<A, VPHI>), dim3(nwg), dim3(kChainThreads), fb, st, g, s, span, cot, vterm,
+                       go, w0, win);
+    return hipGetLastError();
+}
+
+// spare: a float a pixel-sample of scratch that nothing reads any more
 template <typename A>
 static hipError_t chain_lds_passes(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span,
-                                   float4 *cot, int nblk, const GradAcc &go, float4 *dO, int nwg, hipStream_t st) {
+                                   float4 *cot, int nblk, const GradAcc &go, float4 *dO, float *spare, int nwg,
+                                   hipStream_t st) {
     const bool want[3] = {go.ln_n != nullptr, go.temp != nullptr, go.vphi != nullptr};
-    if (want[0] && want[1] && !want[2]) {
-        // ln n and T: the first pass leaves the T terms for the second
-        hipError_t e = launch_chain_lds_t<0, true, A, true>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
+    if (want[0] && want[1]) {
+        // the first pass leaves the T terms for the second and, where asked
+        // for, the v_phi terms for the third (256^2 x 50 x 256: the three
+        // passes 227 us, with each shading its samples 253)
+        float *vterm = want[2] ? spare : nullptr;
+        hipError_t e = launch_chain_lds_t<0, true, A, true>(g, s, rays, span, cot, nblk, go, dO, nwg, st, vterm);
         if (e != hipSuccess) return e;
-        int w0, win;
-        chain_window(g, s, 160 * 1024 - 1024, &w0, &win);
-        const size_t fb = sizeof(float) * (size_t)s.nz * (s.nr + win);
-        e = hipFuncSetAttribute((const void *)adj_chain_lds_stored<A>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)fb);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(adj_chain_lds_stored<A>, dim3(nwg), dim3(kChainThreads), fb, st, g, s, span, cot, go, w0,
-                           win);
-        return hipGetLastError();
+        e = launch_chain_stored<A, false>(g, s, span, cot, nullptr, go, nwg, st);
+        if (e != hipSuccess || !want[2]) return e;
+        return launch_chain_stored<A, true>(g, s, span, cot, vterm, go, nwg, st);
     }
+    // the others have ln n without T, T or v_phi alone, T and v_phi, or neither
     bool first = true;
     hipError_t e = hipSuccess;
     for (int f = 0; f < 3; ++f) {
         if (!want[f]) continue;
-        if (first) {
+        if (first)
             e = f == 0 ? launch_chain_lds_t<0, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
               : f == 1 ? launch_chain_lds_t<1, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
                        : launch_chain_lds_t<2, true, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
-        } else {
-            e = f == 1 ? launch_chain_lds_t<1, false, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
-                       : launch_chain_lds_t<2, false, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
-        }
+        else
+            e = launch_chain_lds_t<2, false, A>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
         if (e != hipSuccess) return e;
         first = false;
     }
@@ -618,15 +641,15 @@ static hipError_t chain_lds_passes(const Geometry &g, const Shade &s, const floa
 }
 
 hipError_t launch_adj_chain_lds(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, float4 *cot,
-                                int nblk, const GradAcc &go, float4 *dO, hipStream_t st) {
+                                int nblk, const GradAcc &go, float4 *dO, float *spare, hipStream_t st) {
     int dev = 0, ncu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     const size_t items = (size_t)g.nsamp * (((size_t)g.nx * g.ny + kChainThreads - 1) / kChainThreads);
     const int nwg = (int)std::min<size_t>((size_t)ncu, items);
-    return grad_accum_double() ? chain_lds_passes<double>(g, s, rays, span, cot, nblk, go, dO, nwg, st)
-                               : chain_lds_passes<float>(g, s, rays, span, cot, nblk, go, dO, nwg, st);
+    return grad_accum_double() ? chain_lds_passes<double>(g, s, rays, span, cot, nblk, go, dO, spare, nwg, st)
+                               : chain_lds_passes<float>(g, s, rays, span, cot, nblk, go, dO, spare, nwg, st);
 }
 
 __global__ void fill_zero_d(double *p, size_t n) {

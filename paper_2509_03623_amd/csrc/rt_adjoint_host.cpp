@@ -210,7 +210,8 @@ rt_status adjoint_core(const rt_problem *p, const float *dl, const rt_grads *g, 
                                      cube_opt ? cube_opt + off : nullptr, st);
             if (e != hipSuccess) return fail_hip(e, "adjoint march");
             float4 *dOc = c0 == 0 ? dO : nullptr;
-            e = lds ? launch_adj_chain_lds(gb, sb, rays, span, cot, nblk, go, dOc, st)
+            // (the march has read the tape: its memory is free for the chain)
+            e = lds ? launch_adj_chain_lds(gb, sb, rays, span, cot, nblk, go, dOc, (float *)tape, st)
                     : launch_adj_chain(gb, sb, rays, span, cot, nblk, go, dOc, st);
             if (e != hipSuccess) return fail_hip(e, "adjoint chain");
         }
