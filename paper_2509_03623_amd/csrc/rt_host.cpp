@@ -421,7 +421,7 @@ void unit_windows(const Channels &ch, int cb, double dv, Windows *w) {
 // 69; 16384 85, 105, 70.  The parts meet in LDS, 512 cb bytes a part and
 // tile: past 32 KB a workgroup they cost more waves in flight than they add
 // (222^2 x 115 x 256, cb 32: two parts 127 us, four 160).
-void window_shape(int nch, long npix, int nsamp, int *cb, int *lsplit) {
+void window_shape(int nch, long npix, int nsamp, int *cb, int *lsplit, long want_waves) {
     static const int cands[] = {4, 8, 12, 16, 24, 32};
     const int nblk = (nch + 127) / 128;
     *cb = 32;
@@ -430,7 +430,7 @@ void window_shape(int nch, long npix, int nsamp, int *cb, int *lsplit) {
     const long waves = (npix + 15) / 16 * nblk;
     const int most = *cb <= 8 ? 3 : (*cb <= 16 ? 2 : 1);
     *lsplit = 0;
-    while (*lsplit < most && (waves << *lsplit) < 8192 && nsamp >= (32 << *lsplit)) ++*lsplit;
+    while (*lsplit < most && (waves << *lsplit) < want_waves && nsamp >= (32 << *lsplit)) ++*lsplit;
 }
 
 // lanes per pixel of the forward march of 64-channel blocks.  Measured on

@@ -34,7 +34,7 @@ bool uniform_spacing(const double *v, int n, double *dv);
 // spacing if uniform)
 void unit_windows(const Channels &ch, int cb, double dv, Windows *w);
 // channels per lane and log2 of the ray parts of the windowed marches
-void window_shape(int nch, long npix, int nsamp, int *cb, int *lsplit);
+void window_shape(int nch, long npix, int nsamp, int *cb, int *lsplit, long want_waves = 8192);
 bool thin_series();
 int forward_group_option();
 int ckpt_segment_option();

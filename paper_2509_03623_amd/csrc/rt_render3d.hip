@@ -337,7 +337,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CB <= 16 ? 
 // fade), the rest the latency of the gathers and waves of unequal work.
 // 512 x 96 x 256 grid, 256^2 x 512 samples, 64 channels: 1.30 ms as
 // march3_fwd, 0.43 ms with windows, 0.39 ms with the quad's gather (gather3),
-// 0.29 ms with the work order below.
+// 0.29 ms with the work order below, 0.25 ms with up to four ray parts.
 //
 // Block b runs on XCD b % 8, so consecutive work goes to an XCD in chunks of
 // 16 tiles: their neighbours share its L2's lines.  One run of tiles per XCD,
@@ -454,6 +454,13 @@ __global__ __launch_bounds__(512, CB <= 16 ? 4 : 2) void march3_win(Geometry3 g,
     for (int c = 0; c < CB; ++c)
         if (c0 + c * G + h < ch.n) cube[(size_t)(c0 + c * G + h) * ch_stride + pix] = I[c];
 }
+
+// Waves asked for before rays stop being parted: twice the axisymmetric march's,
+// since tiles at the sphere's edge and rays that miss the CO layer end early.
+// 8192 against 16384 (us): 256^2 x 64 293, 254; 256^2 x 20 237, 210; 360^2 x 64 434,
+// 395; 360^2 x 30 376, 337; the same at 128^2 to 200^2 (parts already at most) and
+// at 512^2.  32768: 360^2 x 30 357, the rest within 3 %.
+constexpr long kWinWaves3 = 16384;
 
 template <int CB>
 static hipError_t launch3_win(const Geometry3 &g, const Shade3 &s, const Channels &ch, const Windows &win, float *cube,
@@ -816,7 +823,7 @@ rt_status rt_render_cube_3d(const rt_problem3d *p, float *cube, void *stream) {
         if (windows) {
             int wcb, lsplit;
             double dv = 0.0;
-            window_shape(ch.n, npix, p->nsamp, &wcb, &lsplit);
+            window_shape(ch.n, npix, p->nsamp, &wcb, &lsplit, kWinWaves3);
             const bool uniform = uniform_spacing(p->spec.v_kms + c0, ch.n, &dv) && dv != 0.0;
             Windows win;
             unit_windows(ch, wcb, uniform ? dv : 0.0, &win);
