@@ -195,7 +195,10 @@ __global__ __launch_bounds__(512) void march_win(Geometry g, Shade s, Channels c
         vc[c] = ch.v[c0 + c * G + h];
     }
     // every lane of a wave with a live ray takes part (the lane exchanges need
-    // them all); the others' samples are off
+    // them all), also in the steps of the other pixels' units.  A ray that
+    // misses the grid goes beside it: no opacity, and no read of nodes that no
+    // ray of the image samples or of network outputs that nobody wrote
+    const float px = live ? r.px : 4.0f * g.rc;
     if (__ballot(live) != 0) {
         const float half = 0.5f * (float)g.nsamp;
         const float v0 = ch.v[c0];
@@ -208,7 +211,7 @@ __global__ __launch_bounds__(512) void march_win(Geometry g, Shade s, Channels c
         for (int k = kf + split * len; k < k1; k += G) {
             const int kk = min(k + h, k1 - 1);
             const float t = ((float)kk + 0.5f - half) * r.ds;
-            const SampleQ own = shade_sample<NEURAL>(s, ztab, r.px, fmaf(t, r.wy, r.pmy), fmaf(t, r.wz, r.pmz), r.ds,
+            const SampleQ own = shade_sample<NEURAL>(s, ztab, px, fmaf(t, r.wy, r.pmy), fmaf(t, r.wz, r.pmz), r.ds,
                                                      o_index(s, kk, pix));
             const float own_lk = flog2(own.K);
             const unsigned mask =
