@@ -51,6 +51,9 @@ __device__ __forceinline__ void serve_item(const ServeDesc &D, const float4 *zta
         Tr[c] = 1.0f;
         vc[c] = D.vch[c0 + c * G + h];
     }
+    // (a ray that misses the grid goes beside it, as in rt_forward.hip: no
+    // opacity, and no read of nodes that no ray of the image samples)
+    const float px = live ? r.px : 4.0f * g.rc;
     if (__ballot(live) != 0) {
         const float half = 0.5f * (float)g.nsamp;
         const float v0 = D.vch[c0];
@@ -61,7 +64,7 @@ __device__ __forceinline__ void serve_item(const ServeDesc &D, const float4 *zta
         for (int k = kf + split * len; k < k1; k += G) {
             const int kk = min(k + h, k1 - 1);
             const float t = ((float)kk + 0.5f - half) * r.ds;
-            const SampleQ own = shade_sample<false>(D.s, ztab, r.px, fmaf(t, r.wy, r.pmy), fmaf(t, r.wz, r.pmz), r.ds, 0);
+            const SampleQ own = shade_sample<false>(D.s, ztab, px, fmaf(t, r.wy, r.pmy), fmaf(t, r.wz, r.pmz), r.ds, 0);
             const float own_lk = flog2(own.K);
             const unsigned mask =
                 or_over_pixels(unit_mask<CB, G, UNIFORM>(own, own_lk, live && k + h < k1, v0, win, 0));

@@ -83,3 +83,31 @@ def test_network_outputs_nobody_wrote(incl, fp32):
             assert np.abs(cube - ref).max() <= 1e-5 * ref.max()
         else:
             assert np.linalg.norm(cube - ref) <= 1e-2 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("order", ["", "uneven"])
+def test_bad_nodes_in_a_served_batch(order):
+    import paper_2509_03623_amd as rt
+    probs = []
+    for field, bad, nch in [("temp_k", np.nan, 24), ("ln_nh2", np.inf, 24), ("vphi_kms", np.nan, 40), ("", 0.0, 24)]:
+        prob = inclined(nch=nch, dv=9.6 / nch)
+        if field:
+            t = getattr(prob, field).copy()
+            t[44:] = bad
+            prob = prob.replace(**{field: t})
+        if order:
+            prob = prob.replace(v_kms=prob.v_kms + 0.02 * np.sin(np.arange(nch) * 1.7))
+        probs.append(prob)
+    scenes = [rt.scene_from_problem(p) for p in probs]
+    cubes = [torch.full((s.nch, s.ny, s.nx), float("nan"), device="cuda") for s in scenes]
+    torch.cuda.synchronize()
+    print(f"[gpu] missed rays, served {order}", flush=True)
+    with rt.Server(max_slots=8, streams=2) as sv:
+        tickets = [sv.submit(s, c) for s, c in zip(scenes, cubes)]
+        assert all(sv.wait(t)["state"] == "done" for t in tickets)
+    torch.cuda.synchronize()
+    for p, s, c in zip(probs, scenes, cubes):
+        cube = c.cpu().numpy().astype(np.float64)
+        ref = check_dark(p, cube, s.live_mask())
+        finite = np.isfinite(ref).all(0)
+        assert np.abs(cube - ref)[:, finite].max() <= 1e-5 * ref[:, finite].max()
