@@ -143,6 +143,7 @@ struct RaySetup {
 // cancellation in (s_c + h) - (s_c - h).  Chords cut by both constraints use
 // the end points directly.
 __device__ __forceinline__ RaySetup ray_setup(const Geometry &g, int p, int q) {
+#pragma clang fp contract(off)   // alike in every kernel (locate)
     RaySetup r;
     const float X = ((float)p + 0.5f - g.xc) * g.d_pix;
     const float Y = ((float)q + 0.5f - g.yc) * g.d_pix;
@@ -228,9 +229,13 @@ struct Locus {
     float taper;             // density fade one cell beyond the grid
 };
 
+// The network is evaluated where the taper is above 0 and read where another
+// kernel finds it above 0, so both must round alike: every step is written
+// out, and the compiler may not choose what to contract.
 __device__ __forceinline__ Locus locate(const Shade &s, float px, float py, float pz) {
+#pragma clang fp contract(off)
     Locus L;
-    const float rho2 = px * px + py * py;
+    const float rho2 = fmaf(py, py, px * px);
     const bool on = rho2 > 0.0f;
     L.rho = fsqrt(rho2);
     L.inv_rho = on ? frcp(L.rho) : 0.0f;
