@@ -28,8 +28,8 @@ hipError_t mlp_prepare(const float *flat, int precision, void *buf, MlpDev *w, h
 // out is written at the points where the march reads the network
 hipError_t mlp_forward(const Geometry &g, const Shade &s, const MlpDev &w, int precision, size_t M, float4 *out,
                        hipStream_t st);
-// list: device scratch of mlp_backward_list_bytes (the list of the points
-// whose dL/do counts, with its chunks' counts; FP32: and the slabs)
+// list: device scratch of mlp_backward_list_bytes (the list of the points with
+// any dL/do != 0, with its chunks' counts; FP32: and the slabs)
 size_t mlp_backward_list_bytes(size_t M, int precision);
 hipError_t mlp_backward(const Geometry &g, const Shade &s, const MlpDev &w, int precision, size_t M,
                         const float4 *dO, uint32_t *list, float *dW, hipStream_t st);

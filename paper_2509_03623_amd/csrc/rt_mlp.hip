@@ -472,66 +472,32 @@ __device__ __forceinline__ void br_issue(__bf16 *dst, const gbf16 *src, int wv, 
 
 __device__ __forceinline__ void br_wait() { __builtin_amdgcn_s_waitcnt(0); }
 
-// The points whose dL/do counts, in order, for the backward kernels.  A point
-// adds its dL/do times the network's local derivatives to every weight's
-// gradient: with dL/do = 0 (no opacity there) nothing, and with dL/do below
-// 2^-26 / M of the largest, M such points together less than a quarter of the
-// float rounding of the largest one's own term.  Those are left out; the tails
-// of the layer and of the density, most of the points with any opacity,
-// are such (256^2 x 256 samples: the BF16 backward 8.8 -> 6.1 ms).  Four
-// launches over kLiveChunks chunks of the points: the largest
-// dL/do of each chunk, the count of each, a scan of the counts, then each
+// The points with any dL/do != 0, in order, for the backward kernels.  dL/do = 0
+// at a point (no opacity there) makes every layer's dL/dz zero: the point adds
+// nothing to any gradient, so the backward takes the others only, packed 64 to
+// a pass.  A point with however small a dL/do stays: it may be all that some
+// weight's gradient has (a neuron that is silent wherever dL/do is large).
+// Three launches over kLiveChunks chunks of the points: the
+// count of each chunk, a scan of the counts, then each
 // chunk writing its points' indices (1024 consecutive points at a time, each
 // lane's place from a ballot within its wave and the waves' counts in LDS).
 // list: [0] the number of points, [1 ...] their indices; then the chunks'
-// counts, offsets and largest values.
+// counts and offsets.
 constexpr int kLiveChunks = 4096;
 
-// largest |component| of dL/do, as ordered bits (NaN above infinity above the rest)
-__device__ __forceinline__ uint32_t grad_bits(const float4 *dO, size_t m) {
+__device__ __forceinline__ bool live_point(const float4 *dO, size_t m) {
     const float4 d = dO[m];
-    return max(max(__float_as_uint(d.x) & 0x7fffffffu, __float_as_uint(d.y) & 0x7fffffffu),
-               __float_as_uint(d.z) & 0x7fffffffu);
-}
-
-__device__ __forceinline__ uint32_t block_max(uint32_t v, uint32_t *slot) {
-    if (threadIdx.x == 0) *slot = 0u;
-    __syncthreads();
-    if (v) atomicMax(slot, v);
-    __syncthreads();
-    return *slot;
-}
-
-__global__ __launch_bounds__(1024) void mlp_live_max(const float4 *__restrict__ dO, size_t M, size_t chunk,
-                                                     uint32_t *__restrict__ peaks) {
-    __shared__ uint32_t slot;
-    const size_t b0 = (size_t)blockIdx.x * chunk, b1 = min(M, b0 + chunk);
-    uint32_t v = 0;
-    for (size_t i = b0 + threadIdx.x; i < b1; i += 1024) v = max(v, grad_bits(dO, i));
-    v = block_max(v, &slot);
-    if (threadIdx.x == 0) peaks[blockIdx.x] = v;
-}
-
-// bits that a point's grad_bits must exceed, from the chunks' largest (whole
-// workgroup); 0 (any dL/do != 0) where the largest is not finite
-__device__ __forceinline__ uint32_t live_floor(const uint32_t *peaks, int nb, size_t M, uint32_t *slot) {
-    uint32_t v = 0;
-    for (int i = threadIdx.x; i < nb; i += 1024) v = max(v, peaks[i]);
-    v = block_max(v, slot);
-    __syncthreads();
-    return v < 0x7f800000u ? __float_as_uint(__uint_as_float(v) * (0x1p-26f / (float)M)) : 0u;
+    return d.x != 0.0f || d.y != 0.0f || d.z != 0.0f;
 }
 
 __global__ __launch_bounds__(1024) void mlp_live_count(const float4 *__restrict__ dO, size_t M, size_t chunk,
-                                                       const uint32_t *__restrict__ peaks,
                                                        uint32_t *__restrict__ counts) {
-    __shared__ uint32_t slot, tot;
-    const uint32_t floor_bits = live_floor(peaks, gridDim.x, M, &slot);
+    __shared__ uint32_t tot;
     if (threadIdx.x == 0) tot = 0u;
     __syncthreads();
     const size_t b0 = (size_t)blockIdx.x * chunk, b1 = min(M, b0 + chunk);
     uint32_t n = 0;
-    for (size_t i = b0 + threadIdx.x; i < b1; i += 1024) n += grad_bits(dO, i) > floor_bits ? 1u : 0u;
+    for (size_t i = b0 + threadIdx.x; i < b1; i += 1024) n += live_point(dO, i) ? 1u : 0u;
     if (n) atomicAdd(&tot, n);
     __syncthreads();
     if (threadIdx.x == 0) counts[blockIdx.x] = tot;
@@ -566,17 +532,15 @@ __global__ __launch_bounds__(1024) void mlp_live_scan(const uint32_t *__restrict
 }
 
 __global__ __launch_bounds__(1024) void mlp_live_write(const float4 *__restrict__ dO, size_t M, size_t chunk,
-                                                       const uint32_t *__restrict__ peaks,
                                                        const uint32_t *__restrict__ offsets,
                                                        uint32_t *__restrict__ list) {
-    __shared__ uint32_t wsum[16], slot;
-    const uint32_t floor_bits = live_floor(peaks, gridDim.x, M, &slot);
+    __shared__ uint32_t wsum[16];
     const uint32_t t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const size_t b0 = (size_t)blockIdx.x * chunk, b1 = min(M, b0 + chunk);
     uint32_t done = offsets[blockIdx.x];   // the same in every lane
     for (size_t c0 = b0; c0 < b1; c0 += 1024) {
         const size_t i = c0 + t;
-        const bool f = i < b1 && grad_bits(dO, i) > floor_bits;
+        const bool f = i < b1 && live_point(dO, i);
         const uint64_t mk = __ballot(f);
         if (lane == 0) wsum[wv] = (uint32_t)__popcll(mk);
         __syncthreads();
@@ -632,8 +596,8 @@ __global__ __launch_bounds__(kBrThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     const int col = 16 * pt + lc;                                 // this lane's point within the pass
     // layer 0's weights for the first pass (each pass stages the next's)
     br_issue<kW * kRrRow0>(SW, (const gbf16 *)(uint64_t)w.Wr, wv, lane);
-    // the points with any dL/do that counts, listed in order (list[0] of
-    // them), 64 to a pass
+    // the points with any dL/do != 0, listed in order (list[0] of them), 64 to
+    // a pass
     const uint32_t npts = list[0];
     const uint32_t npass = (npts + kBrPts - 1) / kBrPts;
     for (uint32_t ip = blockIdx.x; ip < npass; ip += gridDim.x) {
@@ -1381,7 +1345,7 @@ hipError_t mlp_forward(const Geometry &g, const Shade &s, const MlpDev &w, int p
 static size_t fr_bwd_groups(size_t M) { return std::min<size_t>((M + kBrPts - 1) / kBrPts, 256); }
 
 size_t mlp_backward_list_bytes(size_t M, int precision) {
-    const size_t list = (sizeof(uint32_t) * (1 + M + 3 * (size_t)kLiveChunks) + 255) / 256 * 256;
+    const size_t list = (sizeof(uint32_t) * (1 + M + 2 * (size_t)kLiveChunks) + 255) / 256 * 256;
     return list + (precision == RT_MLP_BF16 ? 0 : sizeof(floatx4) * kFrSlab * fr_bwd_groups(M));
 }
 
@@ -1395,16 +1359,15 @@ hipError_t mlp_backward(const Geometry &g, const Shade &s, const MlpDev &w, int 
     // chunks of at least 1024 points, at most kLiveChunks of them
     const size_t chunk = std::max<size_t>(1024, (M + kLiveChunks - 1) / kLiveChunks);
     const int nb = (int)((M + chunk - 1) / chunk);
-    uint32_t *counts = list + 1 + M, *offsets = counts + kLiveChunks, *peaks = offsets + kLiveChunks;
-    hipLaunchKernelGGL(mlp_live_max, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks);
-    hipLaunchKernelGGL(mlp_live_count, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks, counts);
+    uint32_t *counts = list + 1 + M, *offsets = counts + kLiveChunks;
+    hipLaunchKernelGGL(mlp_live_count, dim3(nb), dim3(1024), 0, st, dO, M, chunk, counts);
     hipLaunchKernelGGL(mlp_live_scan, dim3(1), dim3(1024), 0, st, counts, nb, offsets, list);
-    hipLaunchKernelGGL(mlp_live_write, dim3(nb), dim3(1024), 0, st, dO, M, chunk, peaks, offsets, list);
+    hipLaunchKernelGGL(mlp_live_write, dim3(nb), dim3(1024), 0, st, dO, M, chunk, offsets, list);
     if (precision == RT_MLP_BF16) {
         const unsigned grid = (unsigned)std::min<size_t>(passes, (size_t)ncu);
         hipLaunchKernelGGL(mlp_bwd_rr, dim3(grid), dim3(kBrThreads), 0, st, g, s, w, M, dO, list, dW);
     } else {
-        const size_t list_b = (sizeof(uint32_t) * (1 + M + 3 * (size_t)kLiveChunks) + 255) / 256 * 256;
+        const size_t list_b = (sizeof(uint32_t) * (1 + M + 2 * (size_t)kLiveChunks) + 255) / 256 * 256;
         hipLaunchKernelGGL(mlp_bwd_fr, dim3((unsigned)fr_bwd_groups(M)), dim3(256), 0, st, g, s, w, M, dO, list, dW,
                            (floatx4 *)((char *)list + list_b));
     }

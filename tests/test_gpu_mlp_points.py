@@ -90,3 +90,43 @@ def test_not_finite(bad, fp32):
 def test_no_cotangent(fp32):
     _, g = both(problem(), fp32, np.zeros((8, 14, 16)))
     assert np.all(g["mlp_w"] == 0.0) and np.all(g["temp_k"] == 0.0)
+
+
+def tail_neuron_weights(seed, zt):
+    """A network whose last neuron of every layer is silent (0 in float) below
+    zt of the grid's height and of order 1 above, and acts on the temperature."""
+    from synth.mlp import MLP_DEPTH, MLP_WIDTH, layer_shapes, make_mlp_weights
+    flat = make_mlp_weights(seed)
+    n, off, parts = MLP_WIDTH - 1, 0, []
+    for li, (o, i) in enumerate(layer_shapes()):
+        W = flat[off:off + o * i].reshape(o, i).copy()
+        b = flat[off + o * i:off + o * i + o].copy()
+        off += o * i + o
+        if li:
+            W[:, n] = 0.0
+        if li < MLP_DEPTH:
+            W[n] = 0.0
+            W[n, 48 if li == 0 else n] = (-2000.0, 1.0, 1.0, 0.02)[li]       # feature 48: cos(pi z)
+            b[n] = (2000.0 * np.cos(np.pi * zt), -150.0, -150.0, 0.0)[li]
+        else:
+            W[2, n] = 0.01
+        parts += [W.ravel(), b]
+    return np.concatenate(parts).astype(np.float32), off - 3 - MLP_WIDTH + n
+
+
+@pytest.mark.parametrize("fp32", [True, False])
+def test_neuron_that_only_the_faintest_points_drive(fp32):
+    """The gradient of a weight whose neuron is silent wherever dL/do is large
+    comes whole from points with 1e-17 of the largest.  Bars: FP32 as above;
+    BF16 0.3, its features' 2^-9 times the 2000 of the first weight being about
+    a twentieth of the neuron's range."""
+    prob = problem(nz=96)
+    w, at = tail_neuron_weights(4, 0.8)
+    prob = prob.replace(mlp_w=w)
+    cot = np.ones((8, 14, 16))
+    leaves = torch_ref.as_leaves(prob)
+    torch_ref.cube(prob, leaves).sum().backward()
+    ref = leaves["mlp_w"].grad.numpy()
+    assert 1e-30 < abs(ref[at]) < 1e-15 * np.abs(ref).max()
+    _, g = both(prob, fp32, cot)
+    assert abs(g["mlp_w"].ravel()[at] - ref[at]) <= (1e-3 if fp32 else 0.3) * abs(ref[at])
