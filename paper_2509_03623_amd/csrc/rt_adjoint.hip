@@ -366,11 +366,30 @@ struct FieldLds {
     }
 };
 
+// The two surface vectors in LDS, [lower nr][upper nr]: doubles, or floats where
+// doubles do not fit beside the grid (256 x 148 nodes, say: a whole image's chain
+// passes would else scatter to memory).
+template <typename T> struct SurfLds {
+    T *v;
+    __device__ __forceinline__ void clear(int n) const {
+        for (int i = threadIdx.x; i < n; i += kChainThreads) v[i] = (T)0;
+    }
+    __device__ __forceinline__ void add(int i, float a, float b) const {
+        unsafeAtomicAdd(v + i, (T)a);
+        unsafeAtomicAdd(v + i + 1, (T)b);
+    }
+    template <typename A> __device__ __forceinline__ void flush(A *dst, int from, int n) const {
+        if (!dst) return;
+        for (int i = threadIdx.x; i < n; i += kChainThreads)
+            if (v[from + i] != (T)0) atomicAdd(dst + i, (A)v[from + i]);
+    }
+};
+
 // Chain pass with the gradient of one field privatised in LDS.  Persistent
 // workgroups take their items (ChainItems), accumulate
 // field FIELD (0 ln n, 1 T, 2 v_phi, 3 none) over the whole grid in LDS, and
 // flush it once with atomics into the accumulators of type A;
-// the FIRST pass also accumulates the two surface vectors (LDS, double) and
+// the FIRST pass also accumulates the two surface vectors (LDS) and
 // writes dL/do.
 // With STORE (the first pass, FIELD 0) each sample inside a ray's run also
 // leaves the temperature term of its chain in slice 0 of the cotangents,
@@ -379,7 +398,7 @@ struct FieldLds {
 // second pass (adj_chain_lds_stored) then adds those into the T gradient
 // without shading the sample again.  With vterm it leaves the v_phi term
 // there as well, for a third pass over the same nodes and weights.
-template <int FIELD, bool FIRST, typename A, bool STORE = false>
+template <int FIELD, bool FIRST, typename A, typename S, bool STORE>
 __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade s, const float4 *__restrict__ rays,
                                                      const int2 *__restrict__ span, float4 *__restrict__ cot,
                                                      int nblk, GradAcc go, float4 *__restrict__ dO, int w0,
@@ -388,12 +407,12 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
     extern __shared__ double dyn[];
     __shared__ float4 ztab[kZTableNodes - 1];
     const int nr = s.nr;
-    double *surf = dyn;
-    double *fd = dyn + (FIRST ? 2 * nr : 0);
+    const SurfLds<S> surf{(S *)dyn};
+    double *fd = dyn + (FIRST ? 2 * nr * sizeof(S) / sizeof(double) : 0);
     const FieldLds field{fd, (float *)(fd + (FIELD < 3 ? win * s.nz : 0)), nr, s.nz, w0, win};
     for (int i = threadIdx.x; i < kZTableNodes - 1; i += kChainThreads) ztab[i] = s.ztab[i];
     if (FIELD < 3) field.clear();
-    if (FIRST) for (int i = threadIdx.x; i < 2 * nr; i += kChainThreads) surf[i] = 0.0;
+    if (FIRST) surf.clear(2 * nr);
     __syncthreads();
     const int npix = g.nx * g.ny;
     // An item's loads (the ray, and the cotangents if the sample is in the ray's
@@ -478,14 +497,8 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
             if (FIRST && !s.mlp_o) {
                 const float gzu = gKK * tp.sa * tp.iw * kLn2;
                 const float gzl = -gKK * tp.sb * tp.iw * kLn2;
-                if (go.zlo && gzl != 0.0f) {
-                    unsafeAtomicAdd(surf + L.i0, (double)(gzl * (1.0f - fu)));
-                    unsafeAtomicAdd(surf + L.i0 + 1, (double)(gzl * fu));
-                }
-                if (go.zup && gzu != 0.0f) {
-                    unsafeAtomicAdd(surf + nr + L.i0, (double)(gzu * (1.0f - fu)));
-                    unsafeAtomicAdd(surf + nr + L.i0 + 1, (double)(gzu * fu));
-                }
+                if (go.zlo && gzl != 0.0f) surf.add(L.i0, gzl * (1.0f - fu), gzl * fu);
+                if (go.zup && gzu != 0.0f) surf.add(nr + L.i0, gzu * (1.0f - fu), gzu * fu);
             }
         }
         if (FIRST && dO && pix < npix) dO[o_index(s, k, pix)] = dout;
@@ -500,11 +513,10 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds(Geometry g, Shade
     __syncthreads();
     A *dst = (A *)(FIELD == 0 ? go.ln_n : (FIELD == 1 ? go.temp : (FIELD == 2 ? go.vphi : nullptr)));
     if (FIELD < 3 && dst) field.flush(dst);
-    if (FIRST)
-        for (int i = threadIdx.x; i < nr; i += kChainThreads) {
-            if (go.zlo && surf[i] != 0.0) atomicAdd((A *)go.zlo + i, (A)surf[i]);
-            if (go.zup && surf[nr + i] != 0.0) atomicAdd((A *)go.zup + i, (A)surf[nr + i]);
-        }
+    if (FIRST) {
+        surf.flush((A *)go.zlo, 0, nr);
+        surf.flush((A *)go.zup, nr, nr);
+    }
 }
 
 // The temperature pass (VPHI: that of v_phi) from the terms a STORE first pass
@@ -559,7 +571,11 @@ __global__ __launch_bounds__(kChainThreads) void adj_chain_lds_stored(Geometry g
 // the partition table)
 constexpr size_t kChainLdsMax = 160 * 1024 - sizeof(float4) * (kZTableNodes - 1) - 1024;
 
+// the grid and the surfaces as floats
 bool chain_lds_fits(int nr, int nz) {
+    return (size_t)nr * nz * sizeof(float) + 2 * (size_t)nr * sizeof(float) <= kChainLdsMax;
+}
+static bool chain_surf_double(int nr, int nz) {
     return (size_t)nr * nz * sizeof(float) + 2 * (size_t)nr * sizeof(double) <= kChainLdsMax;
 }
 
@@ -575,20 +591,30 @@ static void chain_window(const Geometry &g, const Shade &s, size_t bytes, int *w
     *w0 = std::max(0, (int)std::min<double>(s.nr, std::max(0.0, top)) - *win);
 }
 
+template <int FIELD, bool FIRST, typename A, typename S, bool STORE>
+static hipError_t launch_chain_lds_s(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, float4 *cot,
+                                     int nblk, const GradAcc &go, float4 *dO, int nwg, hipStream_t st, float *vterm) {
+    const size_t sb = FIRST ? 2 * (size_t)s.nr * sizeof(S) : 0;
+    int w0 = 0, win = 0;
+    if (FIELD < 3) chain_window(g, s, kChainLdsMax - sb, &w0, &win);
+    const size_t fb = FIELD < 3 ? sizeof(float) * (size_t)s.nz * (s.nr + win) : 0;
+    hipError_t e = hipFuncSetAttribute((const void *)adj_chain_lds<FIELD, FIRST, A, S, STORE>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)(fb + sb));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((adj_chain_lds<FIELD, FIRST, A, S, STORE>), dim3(nwg), dim3(kChainThreads), fb + sb, st, g, s,
+                       rays, span, cot, nblk, go, dO, w0, win, vterm);
+    return hipGetLastError();
+}
+
 template <int FIELD, bool FIRST, typename A, bool STORE = false>
 static hipError_t launch_chain_lds_t(const Geometry &g, const Shade &s, const float4 *rays, const int2 *span, float4 *cot,
                                      int nblk, const GradAcc &go, float4 *dO, int nwg, hipStream_t st,
                                      float *vterm = nullptr) {
-    const size_t sb = FIRST ? 2 * (size_t)s.nr * sizeof(double) : 0;
-    int w0 = 0, win = 0;
-    if (FIELD < 3) chain_window(g, s, kChainLdsMax - sb, &w0, &win);
-    const size_t fb = FIELD < 3 ? sizeof(float) * (size_t)s.nz * (s.nr + win) : 0;
-    hipError_t e = hipFuncSetAttribute((const void *)adj_chain_lds<FIELD, FIRST, A, STORE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)(fb + sb));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((adj_chain_lds<FIELD, FIRST, A, STORE>), dim3(nwg), dim3(kChainThreads), fb + sb, st, g, s, rays,
-                       span, cot, nblk, go, dO, w0, win, vterm);
-    return hipGetLastError();
+    if constexpr (FIRST) {
+        if (!chain_surf_double(s.nr, s.nz))
+            return launch_chain_lds_s<FIELD, FIRST, A, float, STORE>(g, s, rays, span, cot, nblk, go, dO, nwg, st, vterm);
+    }
+    return launch_chain_lds_s<FIELD, FIRST, A, double, STORE>(g, s, rays, span, cot, nblk, go, dO, nwg, st, vterm);
 }
 
 template <typename A, bool VPHI>

@@ -208,3 +208,10 @@ def test_channel_far_from_every_line():
 @pytest.mark.parametrize("nch,order", [(40, "uneven"), (41, ""), (49, "falling"), (56, "uneven"), (57, "")])
 def test_reverse_march_block_ends(nch, order):
     test_reverse_march(182, 181, nch, order)
+
+
+# grids that leave no room for the surfaces as doubles
+@pytest.mark.parametrize("nr,nz", [(256, 148), (295, 128)])
+@pytest.mark.parametrize("double", [0, 1])
+def test_chain_rows_with_float_surfaces(nr, nz, double):
+    test_chain_rows(nr, nz, None, double)
