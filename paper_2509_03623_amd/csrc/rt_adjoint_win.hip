@@ -10,11 +10,13 @@
 // wave needs (rt_kernels.h, "line windows").  A channel outside the window has
 // x = 0 to float, so J, both depth sums and every cotangent stay as they are.
 //
-// Faint samples have loops of their own.  Sweep 1 (K < 2^-26): 1 - 2^-x is
-// x ln2 to the bit and the depth goes to the low word of the sum.  Sweep 2
-// (K < 2^-40): besides, the transmission is kept from the last sample that
-// was not faint; a million of them (the most a ray may have) change it by
-// less than 1e-6, five hundred by 5e-10.
+// Faint samples, K < 2^-26 / nsamp, have loops of their own in both sweeps.
+// 1 - 2^-x is x ln2 to the bit there, the depth goes to the low word of the sum,
+// and in sweep 2 the transmission is kept from the last sample that was not
+// faint: all of a ray's faint samples together, 2^-26 at most, change it by less
+// than half its last bit.  The bound falls with the number of samples so that
+// this holds for the longest rays, and is one for both sweeps so that sweep 2
+// takes from the high word what sweep 1 put there.
 //
 // Bound: VALU issue and, at 16 channels a lane, the registers of sweep 2 (sums,
 // w, J, u and the velocity of each channel: 137, three waves per SIMD; held to
@@ -28,7 +30,8 @@
 
 namespace rt {
 
-constexpr float kStillLog2K = -40.0f;   // sweep 2's faint samples
+// log2 of the faint samples' bound: -26 - ceil(log2 nsamp)
+__device__ __forceinline__ float faint_log2(int nsamp) { return -26.0f - (float)(32 - __clz(nsamp - 1)); }
 
 template <int CB, bool CUBE, bool UNIFORM>
 __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, int plane, int nblk, Channels ch,
@@ -54,6 +57,7 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
     // this lane's own run of samples with opacity (empty: first > last)
     int2 ks = inside ? span_of(span[pix], nsamp) : make_int2(nsamp, -1);
     const int kf = wave_min(ks.x), kl = wave_max(ks.y);
+    const float faint = faint_log2(nsamp);
     float vc[CB], th[CB], tl[CB], J[CB], w[CB];
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
@@ -78,7 +82,7 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
     auto sweep1 = [&](int k, const float4 &e) {
         const float own_lk = flog2(e.y);
         const unsigned mask = own_mask(e, own_lk, in_run(k));
-        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < kFaintLog2K));
+        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < faint));
         const unsigned long long thick = __builtin_amdgcn_ballot_w64(!(own_lk < kThinLog2K));
         auto step = [&](auto jc) {
             constexpr int N = decltype(jc)::value;
@@ -173,7 +177,7 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
         next = entry(k - G);
         const float own_lk = flog2(e.y);
         const unsigned mask = own_mask(e, own_lk, on);
-        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < kStillLog2K));
+        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < faint));
         const unsigned long long thick = __builtin_amdgcn_ballot_w64(!(own_lk < kThinLog2K));
         float4 res = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         auto step = [&](auto jc) {
@@ -191,7 +195,10 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
                 ca += gd;
                 cb = fmaf(-vc[c], gd, cb);
             };
-            // adds x to the running sum (never the smaller operand) and renews u
+            // adds x to the running sum, minus the depth of this sample and of
+            // those in front of it, as sweep 1 put them there, so never the
+            // smaller operand but for rounding (which then costs an ulp of x),
+            // and renews u
             auto renew = [&](int c, float x) {
                 const float sum = th[c] + x;
                 tl[c] += x - (sum - th[c]);

@@ -215,3 +215,39 @@ def test_reverse_march_block_ends(nch, order):
 @pytest.mark.parametrize("double", [0, 1])
 def test_chain_rows_with_float_surfaces(nr, nz, double):
     test_chain_rows(nr, nz, None, double)
+
+
+@pytest.mark.parametrize("log2k", [np.log2(13.45) - 30, np.log2(12.6) - 30, -40.5])
+def test_longest_rays_of_faint_samples(log2k):
+    """Rays of 2^20 equal samples with depths of log2 K each: the windowed reverse
+    march against the one over all channels.  Both form J alike to the bit and hold
+    the depth in two words, so they differ by a few roundings of the transmission
+    and of the sums (1e-5).  A depth summed in one word is off by up to half an ulp
+    of the sum a sample, and the gradient by 1.4e-5 at samples of 12.6 ulps."""
+    import paper_2509_03623_amd as rt
+    from paper_2509_03623_amd import _lib as L
+    n = 1 << 20
+    small = synth.slab_problem(nsamp=64, m=1, nch=1, dv=0.03, nx=4, ny=4)
+    thick, thin = (oracle.render(small.replace(x_co=x)).max() for x in (1e2, 1e-14))
+    inside = 62 / 64 * n                                     # samples in the layer
+    x_co = 1e-14 * np.log(2.0) * 2.0 ** log2k * inside / (thin / thick)
+    prob = synth.slab_problem(nsamp=n, m=n // 64, nch=1, dv=0.03, nx=4, ny=4, x_co=x_co)
+    prob = prob.replace(intensity_scale=synth.disk.rj_kelvin_scale(prob.line))
+    sc = rt.scene_from_problem(prob)
+    cot = torch.as_tensor(1.0 + 0.5 * np.random.Generator(np.random.PCG64(9)).standard_normal((1, 4, 4)),
+                          dtype=torch.float32, device="cuda")
+    print(f"[gpu] longest rays, log2 K = {log2k}", flush=True)
+
+    def grads():
+        g = rt.render_adjoint(sc, cot, want=("ln_nh2", "temp_k"))
+        return {k: v.cpu().numpy().astype(np.float64) for k, v in g.items()}
+    got = grads()
+    rt.set_option(L.RT_OPT_ADJ_CHANNEL_BLOCK, 16)
+    try:
+        want = grads()
+    finally:
+        rt.set_option(L.RT_OPT_ADJ_CHANNEL_BLOCK, 0)
+    for k in got:
+        err = np.linalg.norm(got[k] - want[k]) / np.linalg.norm(want[k])
+        print(k, err, flush=True)
+        assert np.linalg.norm(want[k]) > 0 and err <= 1e-5, k
