@@ -68,3 +68,24 @@ def test_polar_wedges(incl, wedge):
     if lo is not None:
         prob = replace(prob, grid=replace(prob.grid, th_min=lo, th_max=hi))
     check(prob)
+
+
+@pytest.mark.parametrize("half,nsamp", [(1e-4, 1 << 17), (1e-3, 1 << 19)])
+def test_thinnest_wedges(half, nsamp):
+    """A wedge whose crossing is a few samples of the ray: the windowed march finds
+    every crossing that the march over the whole chord does (bar: the march's own)."""
+    import paper_2509_03623_amd as rt
+    from paper_2509_03623_amd import _lib as L
+    grid = replace(S3.Grid3Spec(20, 6, 8), th_min=0.5 * math.pi - half, th_max=0.5 * math.pi + half)
+    n = 40 if nsamp < 1 << 18 else 20
+    prob = S3.uniform_problem3(grid, nx=n, ny=n, nch=3, nsamp=nsamp, incl=55.0, pa=30.0, fov_au=2.0 * grid.r_max_au)
+    sc = rt.scene3d_from_problem(prob)
+    print(f"[gpu] windows3 wedge {half} ns={nsamp}", flush=True)
+    got = rt.render3d(sc)
+    rt.set_option(L.RT_OPT_CHANNEL_BLOCK, 8)
+    try:
+        want = rt.render3d(sc)
+    finally:
+        rt.set_option(L.RT_OPT_CHANNEL_BLOCK, 0)
+    peak = float(want.max())
+    assert peak > 0 and float((got - want).abs().max()) <= TOL * peak
