@@ -45,6 +45,7 @@
 
 #include "rt_adjoint.h"
 #include "rt_host.h"
+#include "rt_mlp.h"
 #include "rt_serve.h"
 
 using namespace rt;
@@ -120,7 +121,7 @@ uint64_t footprint(const rt_request &r, bool grad_batched) {
     const uint64_t npix = (uint64_t)p.cam.nx * p.cam.ny, cube = 4ull * p.spec.nch * npix;
     const uint64_t M = npix * p.nsamp;
     uint64_t b = 4 * (3 * nn + 2 * nr) + cube;
-    if (p.mlp) b += 4ull * RT_MLP_PARAMS + 16 * M + (1u << 20);
+    if (p.mlp) b += 4ull * RT_MLP_PARAMS + 16 * M + (1u << 20);   // weights, outputs, prepared weights
     if (r.kind == RT_REQ_FWD_LOSS) b += cube;   // target
     if (r.kind == RT_REQ_FWD_LOSS && r.beam.bmaj_px > 0.0) {
         // convolved cube and the beam's weights (stream workspaces)
@@ -142,7 +143,8 @@ uint64_t footprint(const rt_request &r, bool grad_batched) {
         const uint64_t row = adjoint_bytes_per_pixel(ch, (long)npix, p.nsamp, true) * (uint64_t)p.cam.nx;
         b += workspace_round(std::min<uint64_t>(row * p.cam.ny,
                                                 std::max<uint64_t>(row, adjoint_scratch_cap() / row * row)));
-        if (p.mlp) b += 16 * M + 4ull * RT_MLP_PARAMS;
+        // dL/do, the list of its points (FP32: and the slabs), weight gradients
+        if (p.mlp) b += 16 * M + mlp_backward_list_bytes(M, p.mlp->precision) + 4ull * RT_MLP_PARAMS;
     }
     return b;
 }

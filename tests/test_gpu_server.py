@@ -536,3 +536,33 @@ def test_release_forgets_finished_tickets():
             with pytest.raises(rt.RtError) as e:
                 sv.poll(t)
             assert e.value.status == L.RT_ENOTFOUND
+
+
+@pytest.mark.parametrize("fp32", [True, False])
+def test_network_gradient_is_charged_its_scratch(fp32):
+    """A network gradient request is refused where the budget does not hold the
+    memory that the call takes: outputs, dL/do, the list of the points, and in FP32
+    the slabs of the backward's workgroups."""
+    import ctypes as C
+    import re
+    rt = _rt()
+    from paper_2509_03623_amd import _lib as L
+    prob = synth.small_problem(nx=90, ny=83, nch=12, nsamp=128, nr=40, nz=20, seed=6, dv=0.3, mlp_seed=4)
+    sc = rt.scene_from_problem(prob, mlp_precision=rt.RT_MLP_FP32 if fp32 else rt.RT_MLP_BF16)
+    M = 90 * 83 * 128
+    f = L.lib()["_ZN2rt23mlp_backward_list_bytesEmi"]
+    f.restype = C.c_size_t
+    listed = f(C.c_size_t(M), C.c_int(sc.mlp_precision))
+    assert listed >= 4 * M + (256 * 36 * 256 * 16 if fp32 else 0)
+    cube = torch.empty((sc.nch, sc.ny, sc.nx), device="cuda")
+    grads = {"mlp_w": torch.empty_like(sc.mlp_w)}
+    print(f"[gpu] server network charge fp32={fp32}", flush=True)
+    with rt.Server(hbm_budget_bytes=1 << 20, max_slots=1, streams=1) as sv:
+        with pytest.raises(rt.RtError) as e:
+            sv.submit(sc, cube, target=torch.zeros_like(cube), grads=grads)
+    assert e.value.status == L.RT_ETOOBIG
+    charge = int(re.search(r"needs (\d+) bytes", str(e.value)).group(1))
+    # the two workspaces, which grow in steps of 64 MiB (accumulators; tape and one
+    # slice of cotangents), cube and target, and what the network takes
+    step = 64 << 20
+    assert charge >= step + -(-32 * M // step) * step + 8 * cube.numel() + 32 * M + listed
