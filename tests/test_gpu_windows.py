@@ -251,3 +251,29 @@ def test_longest_rays_of_faint_samples(log2k):
         err = np.linalg.norm(got[k] - want[k]) / np.linalg.norm(want[k])
         print(k, err, flush=True)
         assert np.linalg.norm(want[k]) > 0 and err <= 1e-5, k
+
+
+@pytest.mark.parametrize("field", ["temp_k", "ln_nh2", "vphi_kms", "z_up_au"])
+@pytest.mark.parametrize("nch", [40, 130])
+@pytest.mark.parametrize("rows", [(36, 40), (44, 48)])
+def test_no_nan_ray_is_hidden(field, nch, rows):
+    """Every ray that the march over all channels makes NaN is NaN in the windowed
+    march, in every channel: what it leaves out reads no field.  (Not the other way
+    round: the march over all channels passes over a NaN sample where no other ray
+    of its wave has opacity.)"""
+    import paper_2509_03623_amd as rt
+    from paper_2509_03623_amd import _lib as L
+    prob = synth.small_problem(nx=16, ny=14, nch=nch, nsamp=80, nr=48, nz=24, seed=36, dv=8.0 / nch)
+    t = getattr(prob, field).copy()
+    t[rows[0]:rows[1]] = np.nan
+    prob = prob.replace(**{field: t})
+    ref = np.isnan(oracle.render(prob)).any(0)
+    bad = np.isnan(gpu_cube(prob))
+    rt.set_option(L.RT_OPT_CHANNEL_BLOCK, 16)
+    try:
+        plain = np.isnan(gpu_cube(prob)).any(0)
+    finally:
+        rt.set_option(L.RT_OPT_CHANNEL_BLOCK, 0)
+    assert plain.any() and np.array_equal(bad.any(0), bad.all(0))
+    assert not (plain & ~bad.any(0)).any()
+    assert not (bad.any(0) & ~ref).any()
