@@ -10,11 +10,12 @@
 //
 // beam_weights (one workgroup) evaluates the (2R+1)^2 weights in float,
 // normalises them by their workgroup-reduced sum and stores them.  beam_conv: one
-// workgroup per 64 x 64 output tile of one channel, compiled for each R; the
+// workgroup per 64 x 64 output tile of one channel (64 x 32 in small launches),
+// compiled for each R; the
 // tile plus its halo is staged in LDS (zeros outside the image), all of a
 // lane's float4 loads in flight together, with the weights; each lane forms 8
-// consecutive outputs of two rows from the float4 of a tile row it reads once,
-// the taps and their window all in registers by constant index.
+// consecutive outputs of two rows (or one) from the float4 of a tile row it reads
+// once, the taps and their window all in registers by constant index.
 //
 // Bound: FMA issue, (2R+1)^2 FMAs per output; with three registers read of
 // which two are often of one bank an FMA takes 3.3 cycles of the 2 it could.
@@ -32,8 +33,9 @@
 
 namespace rt {
 
-constexpr int kBeamOut = 8, kBeamRows = 2;                 // outputs of a lane: columns, rows
-constexpr int kBeamTX = 64, kBeamTY = 256 / (kBeamTX / kBeamOut) * kBeamRows;
+constexpr int kBeamOut = 8;                                // outputs of a lane: columns, and 1 or 2 rows
+constexpr int kBeamTX = 64;
+constexpr int beam_ty(int rows) { return 256 / (kBeamTX / kBeamOut) * rows; }
 // halo left and right in whole float4; values of a tile row that a lane reads
 // (from its first column of the halo); half of the float4 of a tile row, stored
 // even ones first (a lane's outputs are two float4 wide, so that neighbouring
@@ -64,15 +66,16 @@ __global__ __launch_bounds__(256) void beam_weights(float *__restrict__ w, int R
     for (int i = threadIdx.x; i < nn; i += blockDim.x) w[i] = weight(i) * inv;
 }
 
-template <int R, bool VEC>
+template <int R, bool VEC, int ROWS>
 __global__ __launch_bounds__(256) void beam_conv(const float *__restrict__ in, float *__restrict__ out,
                                                  const float *__restrict__ w, int nx, int ny) {
     constexpr int n = 2 * R + 1, NW = (n + 3) / 4 * 4;       // taps of a row, padded to whole float4
+    constexpr int TY = beam_ty(ROWS);
     constexpr int RX = beam_halo(R), W4 = kBeamTX / 4 + RX / 2;   // a tile row in float4
-    constexpr int H = kBeamTY + 2 * R, P = beam_pitch(R), E = beam_half(R), NV = beam_values(R);
+    constexpr int H = TY + 2 * R, P = beam_pitch(R), E = beam_half(R), NV = beam_values(R);
     __shared__ float4 tile[H * P];
     __shared__ __attribute__((aligned(16))) float wk[n * NW];
-    const int x0 = blockIdx.x * kBeamTX, y0 = blockIdx.y * kBeamTY;
+    const int x0 = blockIdx.x * kBeamTX, y0 = blockIdx.y * TY;
     const size_t plane = (size_t)nx * ny;
     const float *src = in + blockIdx.z * plane;
     constexpr int NL = (H * W4 + 255) / 256;                 // all loads of a lane in flight at once
@@ -104,11 +107,11 @@ __global__ __launch_bounds__(256) void beam_conv(const float *__restrict__ in, f
     }
     __syncthreads();
     constexpr int LX = kBeamTX / kBeamOut;
-    const int ty = (int)threadIdx.x / LX * kBeamRows;         // first of the lane's output rows
+    const int ty = (int)threadIdx.x / LX * ROWS;         // first of the lane's output rows
     const int tx = (int)threadIdx.x % LX * kBeamOut;          // and columns
-    float acc[kBeamRows][kBeamOut];
+    float acc[ROWS][kBeamOut];
 #pragma unroll
-    for (int y = 0; y < kBeamRows; ++y)
+    for (int y = 0; y < ROWS; ++y)
 #pragma unroll
         for (int q = 0; q < kBeamOut; ++q) acc[y][q] = 0.0f;
     // out(y, x) = sum_{j, i} K[j][i] in(y + R - j, x + R - i); K is point-symmetric
@@ -138,12 +141,12 @@ __global__ __launch_bounds__(256) void beam_conv(const float *__restrict__ in, f
         }
     };
     constexpr std::integral_constant<int, 0> top{};
-    constexpr std::integral_constant<int, kBeamRows - 1> bottom{};
-    if constexpr (kBeamRows == 2) row(0, top, top);
-    for (int r = kBeamRows - 1; r < n; ++r) row(r, top, bottom);
-    if constexpr (kBeamRows == 2) row(n, bottom, bottom);
+    constexpr std::integral_constant<int, ROWS - 1> bottom{};
+    if constexpr (ROWS == 2) row(0, top, top);
+    for (int r = ROWS - 1; r < n; ++r) row(r, top, bottom);
+    if constexpr (ROWS == 2) row(n, bottom, bottom);
 #pragma unroll
-    for (int yy = 0; yy < kBeamRows; ++yy) {
+    for (int yy = 0; yy < ROWS; ++yy) {
         const int y = y0 + ty + yy;
         if (y >= ny) return;
         float *dst = out + blockIdx.z * plane + (size_t)y * nx + x0 + tx;
@@ -160,6 +163,14 @@ __global__ __launch_bounds__(256) void beam_conv(const float *__restrict__ in, f
     }
 }
 
+// Launches of at most one two-row tile a CU (256) have a wave on each SIMD, which
+// issues no more than an FMA in 5 cycles: from R = 8 on one row a lane, twice the
+// waves, is faster there.  Two rows and one, us: 65 x 65 x 8 R = 8 16.8, 11.8, R =
+// 23 97, 56; 256 tiles R = 8 16.4, 15.1, R = 23 93, 79; but 256 tiles R = 5 10.6,
+// 12.8, and 384 tiles R = 8 17.7, 18.6, 512 R = 23 113, 140.
+constexpr long kBeamFew = 256;
+constexpr int kBeamFewR = 8;
+
 template <int R>
 static hipError_t launch_conv(const float *in, float *out, const float *w, int R_, int nch, int ny, int nx,
                               hipStream_t st) {
@@ -167,11 +178,18 @@ static hipError_t launch_conv(const float *in, float *out, const float *w, int R
         return hipErrorInvalidValue;
     } else {
         if (R_ != R) return launch_conv<R + 1>(in, out, w, R_, nch, ny, nx, st);
-        const dim3 grid((nx + kBeamTX - 1) / kBeamTX, (ny + kBeamTY - 1) / kBeamTY, nch);
+        const unsigned tx = (nx + kBeamTX - 1) / kBeamTX;
+        const dim3 one(tx, (ny + beam_ty(1) - 1) / beam_ty(1), nch), two(tx, (ny + beam_ty(2) - 1) / beam_ty(2), nch);
         // rows of whole, aligned float4: every float4 of the tile is inside or outside as a whole
         const bool vec = nx % 4 == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
-        if (vec) hipLaunchKernelGGL((beam_conv<R, true>), grid, dim3(256), 0, st, in, out, w, nx, ny);
-        else hipLaunchKernelGGL((beam_conv<R, false>), grid, dim3(256), 0, st, in, out, w, nx, ny);
+        if constexpr (R >= kBeamFewR) {
+            if ((long)two.x * two.y * two.z <= kBeamFew) {
+                hipLaunchKernelGGL((beam_conv<R, false, 1>), one, dim3(256), 0, st, in, out, w, nx, ny);
+                return hipGetLastError();
+            }
+        }
+        if (vec) hipLaunchKernelGGL((beam_conv<R, true, 2>), two, dim3(256), 0, st, in, out, w, nx, ny);
+        else hipLaunchKernelGGL((beam_conv<R, false, 2>), two, dim3(256), 0, st, in, out, w, nx, ny);
         return hipGetLastError();
     }
 }

@@ -38,3 +38,11 @@ def test_every_radius(radius):
 @pytest.mark.parametrize("shift", [0, 1])
 def test_tile_edges(ny, nx, shift):
     check((2, ny, nx), (5.0, 3.0, -40.0), 30, shift)
+
+
+# one and two rows a lane: 256 tiles and one more, at the smallest radius with both forms and the largest
+@pytest.mark.parametrize("radius", [7, 8, 24])
+@pytest.mark.parametrize("nch", [256, 257])
+@pytest.mark.parametrize("ny,nx", [(31, 64), (33, 61)])
+def test_few_tiles_and_one_more(radius, nch, ny, nx):
+    check((nch, ny, nx), (2.3548 * (radius - 0.4) / 3.0, 3.0, -40.0), 31)
