@@ -482,8 +482,9 @@ int32_t rt_constants(double *out, int32_t n);
  * march, each taking a consecutive sub-chord (1, 2, 4 or 8; 0 = automatic).
  * RT_OPT_GRAD_ACCUM: 0 (default) accumulates the gradients of the adjoint
  * (per-workgroup partials in LDS, then atomics into one accumulator per node)
- * in float, 1 in double; the partials are double for the most visited
- * rows and the surfaces, float for the rest, either way.  RT_OPT_ADJ_SCRATCH_CAP: bytes of adjoint
+ * in float, 1 in double; the partials are double for the most visited rows and
+ * the surfaces (as far as LDS holds them), float for the rest, either way.
+ * RT_OPT_ADJ_SCRATCH_CAP: bytes of adjoint
  * scratch (sample tape, transmission checkpoints, cotangents) per pass; an
  * image whose scratch exceeds it is differentiated in bands of whole pixel
  * rows, at least one row per band (0 = default, 8 GiB).  The library keeps

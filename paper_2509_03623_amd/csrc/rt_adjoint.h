@@ -36,7 +36,7 @@ hipError_t launch_adj_march(int cb, int kseg, int lanes, int nsamp, int npix, in
                             float shift, const float4 *tape, const int2 *span, const float *dl, const float *target,
                             float *ckpt, float4 *cot, float *cube_out, hipStream_t st);
 // reverse march over line windows (kseg 0): four lanes per pixel of cb = 4, 8,
-// 12 or 16 channels, the band's image nx x ny
+// 10, 12, 14 or 16 channels, the band's image nx x ny
 hipError_t launch_adj_march_win(int cb, int nsamp, int nx, int ny, int plane, const Channels &ch, const Windows &win,
                                 bool uniform, const float4 *tape, const int2 *span, const float *dl,
                                 const float *target, float4 *cot, float *cube_out, hipStream_t st);

@@ -18,7 +18,7 @@
 // once, the taps and their window all in registers by constant index.
 //
 // Bound: FMA issue, (2R+1)^2 FMAs per output; with three registers read of
-// which two are often of one bank an FMA takes 3.3 cycles of the 2 it could.
+// which two are often of one bank an FMA takes 3 cycles of the 2 it could.
 // 512^2 x 64 channels, R = 8: 109 us a call; 153 with 4-byte reads and stores
 // and the taps in a loop.  Same loop of calls, back to back: R = 3 55 (90), R = 4
 // 48 (88), R = 8 134 (175), R = 12 221 (280), R = 23 804 (1036); 150 x 133 x 40,

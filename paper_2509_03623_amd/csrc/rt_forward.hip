@@ -156,7 +156,8 @@ __global__ __launch_bounds__(256) void march_fwd_group(Geometry g, Shade s, Chan
 // to unit rounds further from the reverse march's d than a fit should see.
 // UNIFORM: evenly spaced channels, whose unit masks need no comparisons.
 //
-// Bound: VALU issue (98 % of the cycles at 4 cycles an instruction: the shading
+// Bound: VALU issue (512^2 x 64 x 512: an instruction every 4.6 cycles of a SIMD,
+// where an FMA takes 4 and one in nine is a transcendental of 8; the shading
 // of a sample about 640 cycles a wave, a faint channel slot 25, a thin one 32).
 // Measured, disks of the full-size family, us: 512^2 x 64 x 512 1417 -> 665,
 // 222^2 x 115 x 256 592 -> 145, 256^2 x 48 x 256 390 -> 101 (march_fwd_group

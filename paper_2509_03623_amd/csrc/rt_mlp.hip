@@ -1,9 +1,10 @@
 // rt_mlp.hip -- neural CO layer on the matrix cores.
 //
 // Network: 16 Fourier frequencies on the two normalised grid coordinates of a
-// sample (64 features) -> 4 SiLU layers of width 128 -> 3 outputs.  It is
-// evaluated at every (pixel, sample) point of the render, point index
-// m = k * npix + pix.
+// sample (64 features) -> 4 SiLU layers of width 128 -> 3 outputs.  Its points
+// are the (pixel, sample) points of the render, index m = k * npix + pix; the
+// forward evaluates those that the march reads, the backward those with a
+// gradient.
 //
 // The BF16 path runs mlp_fwd_rr and mlp_bwd_rr; the FP32 path runs mlp_fwd_fr
 // and mlp_bwd_fr, the same designs on v_mfma_f32_16x16x4_f32.
@@ -331,9 +332,11 @@ __global__ __launch_bounds__(NT) void mlp_fwd_rr(Geometry g, Shade s, MlpDev w, 
 // derivative, conversions, the row writes) and the staging of the weights (240
 // KB a pass; without it 3.5 ms where it takes 4.4).  A single wave issues no
 // more than one vector instruction in 5 cycles, two of them twice that.  256^2
-// x 256 samples: four waves with all neurons of 16 points each 6.0 ms, eight
-// waves 5.1, rows written two points at once 4.85, LDS rows without conflicts
-// 4.7, weights fetched from scalar addresses 4.4.
+// x 256 samples (over two thirds of its points): four waves with all neurons of
+// 16 points each 6.0 ms, eight waves 5.1, rows written two points at once 4.85,
+// LDS rows without conflicts 4.7, weights fetched from scalar addresses 4.4; over
+// all points 6.4, with 44 % of the vector units' cycles and 16 % of the matrix
+// units' taken.
 constexpr int kBrPts = 64;                 // points per workgroup pass
 constexpr int kBrThreads = 512;
 // global-memory views (the pass loop launders the weight pointers, which
@@ -819,8 +822,8 @@ __global__ __launch_bounds__(kBrThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 // Bound: the FP32 matrix rate (157 TFLOP/s; 32 cycles an instruction).  The
 // tiled kernels before these read every operand from LDS or L2 at its use, one
 // tile after another through LDS, over every point: 90 x 83 px x 128 samples
-// 5.76 -> 0.80 ms forward (65 TFLOP/s over the points that are read), 12.8 ->
-// 2.06 ms backward (one wave per SIMD: its activations, LDS rows and barriers
+// 5.76 -> 0.82 ms forward (the matrix units busy 68 % of the time), 12.8 ->
+// 2.38 ms backward (43 %) (one wave per SIMD: its activations, LDS rows and barriers
 // run beside nothing).
 constexpr int kFrRow0 = kF + 8, kFrRow = kW + 8;      // padded rows (floats)
 constexpr size_t kFrWeightElems = (size_t)kW * kFrRow0 + 3 * (size_t)kW * kFrRow;
@@ -1059,7 +1062,7 @@ __device__ __forceinline__ float fr_rowsum(const float *X, int r, int half) {
 // The passes of mlp_bwd_rr in FP32: one workgroup of four waves per CU, 64
 // listed points a pass, 16 per wave; the recomputed forward parks z of every
 // layer and the features lane-privately in the workgroup's slab of global
-// memory (147 KB, 38 MB for the chip: it stays in the caches; LDS holds the
+// memory (147 KB, 38 MB for the chip: past the L2s, in the memory-side cache; LDS holds the
 // weights and the point-major rows), and the weight gradient accumulates in 232
 // registers of each wave over all passes.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void mlp_bwd_fr(

@@ -1,6 +1,7 @@
 // rt_mlp_host.cpp -- render and adjoint entry points with the neural CO
-// layer: prepare the weights, evaluate the network at every (pixel, sample)
-// point, march with its outputs, and (adjoint) backpropagate into the weights.
+// layer: prepare the weights, evaluate the network at the (pixel, sample) points
+// that the march reads, march with its outputs, and (adjoint) backpropagate into
+// the weights.
 #include <hip/hip_runtime.h>
 
 #include "rt_adjoint.h"
@@ -17,7 +18,8 @@ struct Scratch {
 };
 } // namespace
 
-// prepared weights + network outputs for every point of the render
+// prepared weights + network outputs for the points of the render (written where
+// the march reads them)
 static rt_status mlp_setup(const rt_problem *p, Geometry *geo, Shade *sh, MlpDev *w, Scratch *ws, float4 **out,
                            size_t extra_point_bytes, void **extra, hipStream_t st) {
     rt_status rs = build_launch(p, geo, sh);

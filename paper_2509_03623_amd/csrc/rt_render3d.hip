@@ -92,8 +92,6 @@ __device__ __forceinline__ float partition3(const Shade3 &s, const float4 *tab, 
     return partition_fn(z, tab, log2t);
 }
 
-// Channel-independent shading of one sample (cf. physics() of the
-// axisymmetric march): S, line-centre depth K (log2 units), and d = a - v b.
 // Where a sample falls on the grid: its cell and the fractions in it, valid
 // indices for a sample beyond the fade too (taper 0).
 struct Cell3 {
@@ -148,7 +146,9 @@ __device__ __forceinline__ void locate3_nodes(const Shade3 &s, float px, float p
     c.n1 = b00 + (uint32_t)k1;
 }
 
-// The line physics of the fields of a sample, A = (ln n, T, x_CO, v_r), vt and vp.
+// The line physics of the fields of a sample, A = (ln n, T, x_CO, v_r), vt and vp
+// (cf. physics() of the axisymmetric march): S, line-centre depth K (log2 units),
+// and d = a - v b.
 __device__ __forceinline__ SampleQ physics3(const Shade3 &s, const float4 *tab, const Cell3 &c, float4 A, float vt,
                                             float vp, float px, float py, float pz, float ds) {
     const float ln_n = A.x, T = A.y, xco = A.z, vr = A.w;
@@ -332,9 +332,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CB <= 16 ? 
 // Windowed march (rt_forward.hip, march_win): four lanes per pixel with the
 // channels interleaved over them, 4 x 4 pixels a wave, the rays in parts over
 // the waves of a workgroup, over the samples that can lie in the polar wedge;
-// a wave passes over steps beyond the fade and steps without CO.  Bound: half
-// the time the vector units (cells and physics of the samples inside the
-// fade), the rest the latency of the gathers and waves of unequal work.
+// a wave passes over steps beyond the fade and steps without CO.  Bound: 62 %
+// of the time issue of vector instructions (cells and physics of the samples
+// inside the fade), the rest the latency of the gathers (58 % of a wave's time is
+// spent waiting for loads) and waves of unequal work.
 // 512 x 96 x 256 grid, 256^2 x 512 samples, 64 channels: 1.30 ms as
 // march3_fwd, 0.43 ms with windows, 0.39 ms with the quad's gather (gather3),
 // 0.29 ms with the work order below, 0.25 ms with up to four ray parts.
