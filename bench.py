@@ -36,18 +36,25 @@ TRANS_SLOTS = 4
 # (line-centre depth below the series threshold) 1 - 2^-x comes from its
 # cubic series instead of the second exp2: d (FMA), x (FMA + exp2), series
 # (2 FMA + mul), t = Tr (1 - att), I += t S (FMA), Tr -= t  ->  14 FLOP in
-# 8 VALU + 1 TRANS.  The census of each render gives the thin share.
+# 8 VALU + 1 TRANS.  On a faint one (below 2^-26, where Tr cannot change) it is
+# x ln2: d (FMA), x (FMA + exp2), x ln2, Tr ., I += . S (FMA)  ->  9 FLOP in 5
+# VALU + 1 TRANS.  A channel whose depth is 0 in float is left out.
 LOOP_FLOP, LOOP_VALU, LOOP_TRANS = 11, 6, 2
 THIN_FLOP, THIN_VALU, THIN_TRANS = 14, 8, 1
+FAINT_FLOP, FAINT_VALU, FAINT_TRANS = 9, 5, 1
+LOOP_SLOTS = (LOOP_VALU + TRANS_SLOTS * LOOP_TRANS, THIN_VALU + TRANS_SLOTS * THIN_TRANS,
+              FAINT_VALU + TRANS_SLOTS * FAINT_TRANS)
+THIN_DEPTH, FAINT_DEPTH, LEAST_DEPTH = 0.04508422, 2.0 ** -26, 2.0 ** -126   # log2 units
 # Channel-independent shading of one pixel-sample, shared by the channels of
 # a lane: position, grid fetch and bilinear interpolation, density, CO mask,
 # partition function, populations, source function, width, projected
 # velocity, log2 of the line-centre depth.
 SHADE_FLOP, SHADE_VALU, SHADE_TRANS = 151, 100, 15
+SHADE_SLOTS = SHADE_VALU + TRANS_SLOTS * SHADE_TRANS
 # The 3-D march's shading of one pixel-sample (spherical coordinates, radial
 # refinement, two atan2, trilinear fetch of six fields, physics, projected
 # velocity), counted in the compiled sample loop of march3_fwd<24, 4>: 307
-# VALU + 16 transcendental = 371 issue slots, shared by a lane's channels.
+# VALU + 16 transcendental = 371 issue slots, shared by a pixel's channels.
 SHADE3_SLOTS = 307 + 4 * 16
 
 
@@ -59,10 +66,10 @@ SHADE3_SLOTS = 307 + 4 * 16
 # was taken on: the hash of those files is checked at run time.
 FWD_TRAFFIC = {"sources": ("paper_2509_03623_amd/csrc/rt_forward.hip", "paper_2509_03623_amd/csrc/rt_kernels.h",
                            "paper_2509_03623_amd/csrc/rt_launch.h"),
-               "sha256": "6ea039cd02742bf7d552e6ef90fd250c8277a33ca373562feed8ec088c478f49",
+               "sha256": "bdc1f77b06cc331e75889223614e27995d480a94f96cdd2db179636d0851c806",
                "fetch_scale": 1048576 / 524302.5, "write_scale": 1.0,
                # seed -> (FETCH_SIZE KiB, WRITE_SIZE KiB), mean of three launches each
-               "disks": {2000: (1196.8, 65536.0), 2001: (1184.7, 65536.0), 2002: (1343.3, 65536.0), 2003: (1291.7, 65536.0), 2004: (1150.5, 65536.0), 2005: (1193.9, 65536.0), 2006: (1309.5, 65536.0), 2007: (1454.9, 65536.0)}}
+               "disks": {2000: (1056.0, 67336.0), 2001: (1180.5, 66883.4), 2002: (1020.1, 66717.2), 2003: (1022.1, 66603.4), 2004: (1140.8, 66795.7), 2005: (1081.2, 66616.6), 2006: (1087.6, 67474.1), 2007: (1103.6, 66957.6)}}
 
 
 def measured_traffic(seed: int):
@@ -85,20 +92,32 @@ def log(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def algorithmic(nch: int, cb: int, thin: float = 0.0, emit: float = 1.0, shaded: float = 1.0):
-    """(FLOP per ray-sample, issue slots per ray-sample) of the march: the
-    shading of the share `shaded` of the pixel-samples inside the grid's
-    edge taper (shared by the cb channels that use it; the others stop
-    after locating the sample, not counted) and the channel loop on the
-    share `emit` with any opacity, `thin` of those on the series form.  A
-    sample with K = 0 changes no channel: the march skips its channel loop
-    wherever no ray of the wave has opacity at that sample, so only the
-    samples with opacity are counted as loop work (a lower bound on what the
-    lanes execute)."""
-    flop = emit * ((1.0 - thin) * LOOP_FLOP + thin * THIN_FLOP) + shaded * SHADE_FLOP / cb
-    slots = (emit * ((1.0 - thin) * (LOOP_VALU + TRANS_SLOTS * LOOP_TRANS) +
-                     thin * (THIN_VALU + TRANS_SLOTS * THIN_TRANS)) +
-             shaded * (SHADE_VALU + TRANS_SLOTS * SHADE_TRANS) / cb)
+def marched_shares(dump, prob, live, rays=256, seed=97):
+    """(thick, thin, faint) shares of the ray-samples that the windowed march
+    takes through each of its channel loops: those with a depth that is not 0
+    in float, by the largest depth of their sample over the channels, from the
+    oracle's depths (dump: its ray dump) on seeded random rays that cross the
+    grid.  (A line centre between or beyond the channels is deeper than any of
+    them, so some work counts as that of a cheaper loop, none as a dearer.)"""
+    import numpy as np
+    q, p = np.nonzero(live)
+    pick = np.random.Generator(np.random.PCG64(seed)).choice(len(p), size=min(rays, len(p)), replace=False)
+    n = np.zeros(3)
+    for i in pick:
+        depth = dump(prob, int(p[i]), int(q[i]))[2] / np.log(2.0)
+        most, counted = depth.max(axis=1), (depth >= LEAST_DEPTH).sum(axis=1)
+        thick, faint = most >= THIN_DEPTH, most < FAINT_DEPTH
+        n += [counted[thick].sum(), counted[~thick & ~faint].sum(), counted[faint].sum()]
+    return n / (len(pick) * prob.nsamp * len(prob.v_kms))
+
+
+def algorithmic(nch: int, shares, shaded: float, shade_flop: float, shade_slots: float):
+    """(FLOP per ray-sample, issue slots per ray-sample) of the windowed march:
+    the shading of the share `shaded` of the pixel-samples inside the grid's
+    edge taper, once for a pixel's channels (the others stop after locating the
+    sample, not counted), and the channel loops of marched_shares."""
+    flop = sum(a * b for a, b in zip(shares, (LOOP_FLOP, THIN_FLOP, FAINT_FLOP))) + shaded * shade_flop / nch
+    slots = sum(a * b for a, b in zip(shares, LOOP_SLOTS)) + shaded * shade_slots / nch
     return flop, slots
 
 
@@ -144,30 +163,6 @@ def micro_rates(L):
         if lib.rt_microbench(k, iters, C.byref(v)) == 0:
             out[name] = v.value
     return out
-
-
-def auto_shape(nch: int, npix: int, nsamp: int):
-    """The library's automatic (channel block, ray split) of the forward
-    march (same rule as its host code)."""
-    cb = next((c for c in (8, 16, 24, 32, 48, 64) if c >= nch), 64)
-    waves = lambda c, ns: ((npix * ns + 63) // 64) * ((nch + c - 1) // c)
-    if cb == 64 and waves(64, 1) < 4096:
-        cb = 32
-    max_split = 1 if cb >= 64 else (4 if cb >= 48 else 8)
-    ns = 1
-    while ns < max_split and waves(cb, ns) < 4096 and nsamp >= 32 * ns:
-        ns *= 2
-    return cb, ns
-
-
-def auto_shape3(nch: int, npix: int, nsamp: int):
-    """The library's automatic (channel block, ray split) of the 3-D march."""
-    cb = next((c for c in (8, 16, 24, 32, 48, 64) if c >= nch), 64)
-    waves = lambda ns: ((npix * ns + 63) // 64) * ((nch + cb - 1) // cb)
-    ns = 2 if nsamp >= 128 else 1
-    while ns < 8 and waves(2 * ns) <= 1024 and nsamp >= 128 * ns:
-        ns *= 2
-    return cb, ns
 
 
 def cpu_model() -> str:
@@ -321,19 +316,10 @@ def main():
     thin = per_seed[med]["thin_fraction"]
     emit = per_seed[med]["emitting_fraction"]
     shaded = per_seed[med]["shaded_fraction"]
-    cb, split = auto_shape(sc.nch, sc.nx * sc.ny, sc.nsamp)
-    cb = rt.get_option(L.RT_OPT_CHANNEL_BLOCK) or cb
-    split = rt.get_option(L.RT_OPT_RAY_SPLIT) or split
-    # without a chosen shape the march goes over line windows, four lanes of 16
-    # channels to a pixel (the shading shared by 64); the work credited below
-    # is still the channel loop of every channel at the samples with opacity
-    chosen = [rt.get_option(o) for o in (L.RT_OPT_CHANNEL_BLOCK, L.RT_OPT_RAY_SPLIT, L.RT_OPT_FWD_GROUP)]
-    group = chosen[2] or 4
-    if not any(chosen):
-        kname = "march_win"
-    else:
-        kname = f"march_fwd_group<{group}>" if cb == 64 and split == 1 and group > 1 else "march_fwd"
-    flop, slots = algorithmic(sc.nch, cb, thin, emit, shaded)
+    # the march goes over line windows, four lanes of 16 channels to a pixel
+    import oracle
+    shares = marched_shares(oracle.ray_dump, prob, sc.live_mask())
+    flop, slots = algorithmic(sc.nch, shares, shaded, SHADE_FLOP, SHADE_SLOTS)
     achieved = flop * rs / (kern_ms * 1e-3) / 1e12
     peak = flop / slots * LANE_SLOTS_PER_S / 1e12
     out = {
@@ -356,11 +342,13 @@ def main():
                    "parallelism": "single GPU"},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": measured_traffic(med),
-                     "kernel": kname, "kernel_ms": kern_ms, "disk": med,
+                     "kernel": "march_win", "kernel_ms": kern_ms, "disk": med,
                      "emitting_fraction": emit, "thin_fraction_of_emitting": thin, "shaded_fraction": shaded,
                      "flop_per_ray_sample": flop, "issue_slots_per_ray_sample": slots,
-                     "work_credited": "shading inside the taper; the channel loop of every channel at samples with "
-                                      "opacity (march_win leaves out the channels whose depth is 0 in float)",
+                     "marched_fraction": float(shares.sum()),
+                     "marched_thick_thin_faint": [float(x) for x in shares],
+                     "work_credited": "shading of the samples inside the taper; the channel loop of the channels "
+                                      "whose depth is not 0 in float (the oracle's depths on 256 seeded rays)",
                      "hbm_bytes_algorithmic": 4 * sc.nch * sc.nx * sc.ny + 4 * (3 * sc.nr * sc.nz + 2 * sc.nr)},
         "disks": {str(sd): v for sd, v in per_seed.items()},
     }
@@ -368,11 +356,10 @@ def main():
     log("instruction-class issue rates")
     mr = micro_rates(L)
     if "loop_thick_ray_samples_per_s" in mr and "loop_thin_ray_samples_per_s" in mr:
-        # the march's measured mix: the channel loop at its measured rates
-        # (thin share on the series form) plus the shading's issue slots
-        sh = shaded * (SHADE_VALU + TRANS_SLOTS * SHADE_TRANS) / cb / LANE_SLOTS_PER_S
-        t_rs = emit * ((1.0 - thin) / mr["loop_thick_ray_samples_per_s"] +
-                       thin / mr["loop_thin_ray_samples_per_s"]) + sh
+        # the march's measured mix: the thick and thin channel loops at their
+        # measured rates, the faint loop's and the shading's issue slots
+        t_rs = (shares[0] / mr["loop_thick_ray_samples_per_s"] + shares[1] / mr["loop_thin_ray_samples_per_s"] +
+                (shares[2] * LOOP_SLOTS[2] + shaded * SHADE_SLOTS / sc.nch) / LANE_SLOTS_PER_S)
         mr["mix_roof_ray_samples_per_s"] = 1.0 / t_rs
         out["roofline"]["frac_of_measured_mix"] = (rs / (kern_ms * 1e-3)) * t_rs
     out["micro"] = mr
@@ -415,10 +402,12 @@ def bench_render3d(rt, dev, args):
     once per snapshot) is timed on its own.  Ray-samples count the samples of
     the rays that cross the bounding sphere (live_fraction of them; the
     others do no work); alu_frac credits the full shading of the samples
-    inside the grid's fade and the channel loop of those with opacity only
-    (the march skips the rest), from the census."""
+    inside the grid's fade, from the census, and the channel loop of the channels
+    whose depth is not 0 in float (marched_fraction of the ray-samples, from the
+    oracle's depths on seeded rays of the 256^2 image)."""
     import numpy as np
     import torch
+    import oracle
     from synth import disk3d as S3
     grid = S3.Grid3Spec(512, 96, 256)
     base = S3.make_problem3(grid, seed=65, nx=256, ny=256, nch=20, dv=0.25, nsamp=512, incl=40.0, pa=30.0)
@@ -426,6 +415,7 @@ def bench_render3d(rt, dev, args):
     planes = [t(a) for a in (base.ln_nh2, base.temp_k, base.x_co, base.v_r_kms, base.v_theta_kms, base.v_phi_kms)]
     sc0 = rt.scene3d_from_problem(base, device=dev)
     nodes = sc0.nodes
+    live0 = sc0.live_mask()
     steps = max(5, args.steps // 2)
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -463,22 +453,16 @@ def bench_render3d(rt, dev, args):
         live = cen["rays"] / (npx * npx)
         # samples without opacity count as thin in the census
         thin = (cen["thin_pixel_samples"] - (n_all - n_em)) / max(n_em, 1)
-        cb, ns = auto_shape3(nch, npx * npx, 512)
-        nchb = -(-nch // cb)
-        loop = ((1.0 - thin) * (LOOP_VALU + TRANS_SLOTS * LOOP_TRANS) +
-                thin * (THIN_VALU + TRANS_SLOTS * THIN_TRANS))
-        # the channel loop of the samples with opacity and the full shading of
-        # those inside the grid's fade, per channel block (the rest skipped)
-        slots = nchb * (n_em * cb * loop + n_in * SHADE3_SLOTS)
+        shares = marched_shares(oracle.ray_dump3, base.replace(v_kms=synth_channels(nch, 0.25)), live0, rays=64)
+        slots = sc.ray_samples * algorithmic(nch, shares, n_in / max(n_all, 1), 0.0, SHADE3_SLOTS)[1]
         hbm = 24 * grid.nr * grid.nt * grid.nphi + 4 * nch * npx * npx
         out[name] = {"ms": wall * 1e3, "kernel_ms": kern * 1e3, "ray_samples_per_s": sc.ray_samples / wall,
                      "live_fraction": live, "emitting_fraction": n_em / max(n_all, 1),
                      "shaded_fraction": n_in / max(n_all, 1), "thin_fraction_of_emitting": thin,
-                     "channel_block": cb, "ray_split": ns,
+                     "kernel": "march3_win", "marched_fraction": float(shares.sum()),
                      "alu_frac": slots / LANE_SLOTS_PER_S / kern, "hbm_frac": hbm / kern / 8e12}
         log(f"3-D {name}: {wall * 1e3:.3f} ms, {sc.ray_samples / wall:.3e} ray-samples/s")
     if not args.no_cpu:
-        import oracle
         rng = np.random.Generator(np.random.PCG64(98))
         n = 2000
         px, py = rng.integers(0, 256, n).astype(np.int32), rng.integers(0, 256, n).astype(np.int32)
