@@ -10,13 +10,15 @@
 // wave needs (rt_kernels.h, "line windows").  A channel outside the window has
 // x = 0 to float, so J, both depth sums and every cotangent stay as they are.
 //
-// Faint samples, K < 2^-26 / nsamp, have loops of their own in both sweeps.
-// 1 - 2^-x is x ln2 to the bit there, the depth goes to the low word of the sum,
-// and in sweep 2 the transmission is kept from the last sample that was not
-// faint: all of a ray's faint samples together, 2^-26 at most, change it by less
-// than half its last bit.  The bound falls with the number of samples so that
-// this holds for the longest rays, and is one for both sweeps so that sweep 2
-// takes from the high word what sweep 1 put there.
+// Faint samples have loops of their own: 1 - 2^-x is x ln2 to the bit there.
+// Sweep 1, K < min(2^-26, nsamp^-2): the depth goes to the low word of the sum
+// alone.  That word stays under nsamp K, so a ray's additions to it are off by
+// less than 2^-25 in all, half the last bit of the transmission.  Sweep 2, K <
+// min(2^-40, 2^-26 / nsamp): besides, the transmission is kept from the last
+// sample that was not faint; a ray's faint samples together change it by less than
+// half its last bit.  Up to 8192 samples the bounds are 2^-26 and 2^-40, and a
+// kernel of its own has them as literals (146 x 88 x 16 x 457: 272 us, and 280 with
+// the bounds in registers; 2^-26 / nsamp for both sweeps: 288).
 //
 // Bound: VALU issue (512^2 x 64 x 512: an instruction every 5.5 cycles of a SIMD,
 // 4 being an FMA's) and, at 16 channels a lane, the registers of sweep 2 (sums,
@@ -31,10 +33,19 @@
 
 namespace rt {
 
-// log2 of the faint samples' bound: -26 - ceil(log2 nsamp)
-__device__ __forceinline__ float faint_log2(int nsamp) { return -26.0f - (float)(32 - __clz(nsamp - 1)); }
+// log2 of the faint samples' bounds: nsamp rounded up to a power of two, or for up to
+// 2^kLongLog2 samples (LONG false) literals
+constexpr int kLongLog2 = 13;
+template <bool LONG>
+__device__ __forceinline__ float faint_sum(int nsamp) {
+    return LONG ? -2.0f * (float)(32 - __clz(nsamp - 1)) : -2.0f * kLongLog2;
+}
+template <bool LONG>
+__device__ __forceinline__ float faint_still(int nsamp) {
+    return LONG ? -fmaxf(40.0f, (float)(26 + 32 - __clz(nsamp - 1))) : -40.0f;
+}
 
-template <int CB, bool CUBE, bool UNIFORM>
+template <int CB, bool CUBE, bool UNIFORM, bool LONG>
 __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, int plane, int nblk, Channels ch,
                                                      Windows win, const float4 *__restrict__ tape,
                                                      const int2 *__restrict__ span,
@@ -58,7 +69,7 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
     // this lane's own run of samples with opacity (empty: first > last)
     int2 ks = inside ? span_of(span[pix], nsamp) : make_int2(nsamp, -1);
     const int kf = wave_min(ks.x), kl = wave_max(ks.y);
-    const float faint = faint_log2(nsamp);
+    const float faint1 = faint_sum<LONG>(nsamp), faint2 = faint_still<LONG>(nsamp);
     float vc[CB], th[CB], tl[CB], J[CB], w[CB];
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
@@ -83,7 +94,7 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
     auto sweep1 = [&](int k, const float4 &e) {
         const float own_lk = flog2(e.y);
         const unsigned mask = own_mask(e, own_lk, in_run(k));
-        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < faint));
+        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < faint1));
         const unsigned long long thick = __builtin_amdgcn_ballot_w64(!(own_lk < kThinLog2K));
         auto step = [&](auto jc) {
             constexpr int N = decltype(jc)::value;
@@ -178,7 +189,7 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
         next = entry(k - G);
         const float own_lk = flog2(e.y);
         const unsigned mask = own_mask(e, own_lk, on);
-        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < faint));
+        const unsigned long long bright = __builtin_amdgcn_ballot_w64(!(own_lk < faint2));
         const unsigned long long thick = __builtin_amdgcn_ballot_w64(!(own_lk < kThinLog2K));
         float4 res = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         auto step = [&](auto jc) {
@@ -196,10 +207,11 @@ __global__ __launch_bounds__(256) void adj_march_win(int nsamp, int nx, int ny, 
                 ca += gd;
                 cb = fmaf(-vc[c], gd, cb);
             };
-            // adds x to the running sum, minus the depth of this sample and of
-            // those in front of it, as sweep 1 put them there, so never the
-            // smaller operand but for rounding (which then costs an ulp of x),
-            // and renews u
+            // adds x to the running sum and renews u.  The sum is minus the depth
+            // of this sample and of those in front of it, so not the smaller
+            // operand, but for rounding and for the samples that sweep 1 put in
+            // the low word: there the correction may be off by an ulp of x (2^-49,
+            // under 2^-29 for a ray)
             auto renew = [&](int c, float x) {
                 const float sum = th[c] + x;
                 tl[c] += x - (sum - th[c]);
@@ -273,13 +285,17 @@ static hipError_t launch_win_t(int nsamp, int nx, int ny, int plane, const Chann
     const long tiles = (long)((nx + 7) / 8) * ((ny + 7) / 8);
     const dim3 grid((unsigned)((tiles + 7) / 8 * 8 * nblk));
     const bool cube = target || cube_out;
-#define RT_WIN_CASE(C, U)                                                                                          \
-    if (cube == C && uniform == U) {                                                                              \
-        hipLaunchKernelGGL((adj_march_win<CB, C, U>), grid, dim3(256), 0, st, nsamp, nx, ny, plane, nblk, ch, win, \
-                           tape, span, dl, target, cot, cube_out);                                                \
-        return hipGetLastError();                                                                                 \
+    const bool lng = nsamp > 1 << kLongLog2;
+#define RT_WIN_CASE(C, U, L)                                                                                     \
+    if (cube == C && uniform == U && lng == L) {                                                                 \
+        hipLaunchKernelGGL((adj_march_win<CB, C, U, L>), grid, dim3(256), 0, st, nsamp, nx, ny, plane, nblk, ch, \
+                           win, tape, span, dl, target, cot, cube_out);                                          \
+        return hipGetLastError();                                                                                \
     }
-    RT_WIN_CASE(true, true) RT_WIN_CASE(true, false) RT_WIN_CASE(false, true) RT_WIN_CASE(false, false)
+    RT_WIN_CASE(true, true, false) RT_WIN_CASE(true, false, false)
+    RT_WIN_CASE(false, true, false) RT_WIN_CASE(false, false, false)
+    RT_WIN_CASE(true, true, true) RT_WIN_CASE(true, false, true)
+    RT_WIN_CASE(false, true, true) RT_WIN_CASE(false, false, true)
 #undef RT_WIN_CASE
     return hipErrorInvalidValue;
 }

@@ -218,15 +218,14 @@ def test_chain_rows_with_float_surfaces(nr, nz, double):
 
 
 @pytest.mark.parametrize("log2k", [np.log2(13.45) - 30, np.log2(12.6) - 30, -40.5])
-def test_longest_rays_of_faint_samples(log2k):
-    """Rays of 2^20 equal samples with depths of log2 K each: the windowed reverse
+def test_longest_rays_of_faint_samples(log2k, n=1 << 20):
+    """Rays of n equal samples with depths of log2 K each: the windowed reverse
     march against the one over all channels.  Both form J alike to the bit and hold
     the depth in two words, so they differ by a few roundings of the transmission
     and of the sums (1e-5).  A depth summed in one word is off by up to half an ulp
     of the sum a sample, and the gradient by 1.4e-5 at samples of 12.6 ulps."""
     import paper_2509_03623_amd as rt
     from paper_2509_03623_amd import _lib as L
-    n = 1 << 20
     small = synth.slab_problem(nsamp=64, m=1, nch=1, dv=0.03, nx=4, ny=4)
     thick, thin = (oracle.render(small.replace(x_co=x)).max() for x in (1e2, 1e-14))
     inside = 62 / 64 * n                                     # samples in the layer
@@ -251,6 +250,14 @@ def test_longest_rays_of_faint_samples(log2k):
         err = np.linalg.norm(got[k] - want[k]) / np.linalg.norm(want[k])
         print(k, err, flush=True)
         assert np.linalg.norm(want[k]) > 0 and err <= 1e-5, k
+
+
+# the longest ray of the kernel with literal bounds and the shortest of the other,
+# at depths on both sides of either one's bounds (the same tolerance)
+@pytest.mark.parametrize("n", [8192, 8193])
+@pytest.mark.parametrize("log2k", [-25.5, -27.5, -40.5])
+def test_rays_at_the_literal_bounds(n, log2k):
+    test_longest_rays_of_faint_samples(log2k, n)
 
 
 @pytest.mark.parametrize("field", ["temp_k", "ln_nh2", "vphi_kms", "z_up_au"])
